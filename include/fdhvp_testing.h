@@ -46,6 +46,18 @@ fdh_status fdh_testing_gemm_pair(int32_t M0, int32_t N0, int32_t K0, int32_t bat
                                  const void* B1, const void* A21, const void* B21, float* C1, float alpha,
                                  int32_t tile, void* hip_stream);
 
+/* The two channel products of a linear layer as an HVP launches them:
+ *   C = alpha (A B^T + A2 B2^T) and, unless C1 is NULL, C1 = alpha A B^T,
+ * operands laid out as for fdh_testing_gemm, both outputs float32
+ * [batch][M][N].  With scratch (device memory, 256-byte aligned) contractions
+ * whose output tiles do not fill the chip are cut into parts that are added
+ * afterwards; scratch_bytes = 0 keeps every contraction whole.  Enqueued on
+ * hip_stream; returns without waiting. */
+fdh_status fdh_testing_gemm_channels(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t batch, int32_t a_kmajor,
+                                     int32_t b_kmajor, const void* A, const void* B, const void* A2, const void* B2,
+                                     float* C, float* C1, float alpha, void* scratch, size_t scratch_bytes,
+                                     void* hip_stream);
+
 /* on != 0 makes the next fdh_set_workspace plan the unfused attention path
  * (score, probability and score-gradient matrices in the workspace, MFMA
  * GEMMs and row kernels) even where the fused kernels apply (bf16 operands,

@@ -346,10 +346,10 @@ extern "C" fdh_status fdh_testing_gemm(int32_t dtype, int32_t M, int32_t N, int3
   hipError_t r;
   if (dtype == FDH_BF16) {
     if (fdh::gemm_check<fdh::bf16_t>(g)) return FDH_ERR_UNSUPPORTED;
-    r = fdh::gemm<fdh::bf16_t>(g, (hipStream_t)hip_stream);
+    r = fdh::gemm<fdh::bf16_t>(&g, 1, fdh::GemmScratch{}, (hipStream_t)hip_stream);
   } else if (dtype == FDH_F32) {
     if (fdh::gemm_check<float>(g)) return FDH_ERR_UNSUPPORTED;
-    r = fdh::gemm<float>(g, (hipStream_t)hip_stream);
+    r = fdh::gemm<float>(&g, 1, fdh::GemmScratch{}, (hipStream_t)hip_stream);
   } else {
     return FDH_ERR_INVALID_ARG;
   }
@@ -391,6 +391,44 @@ extern "C" fdh_status fdh_testing_gemm_pair(int32_t M0, int32_t N0, int32_t K0, 
     if (a.M < 8 || a.N < 8 || fdh::gemm_check<fdh::bf16_t>(a)) return FDH_ERR_UNSUPPORTED;
   }
   const hipError_t r = fdh::gemm_pair<fdh::bf16_t>(g[0], g[1], (hipStream_t)hip_stream);
+  return r == hipSuccess ? FDH_OK : FDH_ERR_HIP;
+}
+
+extern "C" fdh_status fdh_testing_gemm_channels(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t batch,
+                                                int32_t a_kmajor, int32_t b_kmajor, const void* A, const void* B,
+                                                const void* A2, const void* B2, float* C, float* C1, float alpha,
+                                                void* scratch, size_t scratch_bytes, void* hip_stream) {
+  if (!A || !B || !A2 || !B2 || !C || M < 0 || N < 0 || K < 0 || batch < 1 || (scratch_bytes && !scratch) ||
+      (uintptr_t)scratch % 256)
+    return FDH_ERR_INVALID_ARG;
+  fdh::GemmArgs g[2];
+  const void* As[2] = {A, A2};
+  const void* Bs[2] = {B, B2};
+  for (int q = 0; q < 2; ++q) {
+    fdh::GemmArgs& a = g[q];
+    a.M = M; a.N = N; a.K = K; a.nbatch = batch; a.inner_count = 1;
+    a.npairs = 2 - q;
+    for (int p = 0; p < 2; ++p) {
+      a.A[p].ptr = As[p];
+      a.A[p].s_row = a_kmajor ? K : 1;
+      a.A[p].s_k = a_kmajor ? 1 : M;
+      a.A[p].s_outer = (int64_t)M * K;
+      a.B[p].ptr = Bs[p];
+      a.B[p].s_row = b_kmajor ? K : 1;
+      a.B[p].s_k = b_kmajor ? 1 : N;
+      a.B[p].s_outer = (int64_t)N * K;
+    }
+    a.C = q ? C1 : C; a.ldc = N; a.c_outer = (int64_t)M * N;
+    a.alpha = alpha;
+  }
+  const int n = C1 ? 2 : 1;
+  for (int q = 0; q < n; ++q)
+    if (dtype == FDH_BF16 ? fdh::gemm_check<fdh::bf16_t>(g[q]) : fdh::gemm_check<float>(g[q])) return FDH_ERR_UNSUPPORTED;
+  const fdh::GemmScratch sc{(float*)scratch, scratch_bytes};
+  hipError_t r;
+  if (dtype == FDH_BF16) r = fdh::gemm<fdh::bf16_t>(g, n, sc, (hipStream_t)hip_stream);
+  else if (dtype == FDH_F32) r = fdh::gemm<float>(g, n, sc, (hipStream_t)hip_stream);
+  else return FDH_ERR_INVALID_ARG;
   return r == hipSuccess ? FDH_OK : FDH_ERR_HIP;
 }
 

@@ -150,6 +150,7 @@ class Engine : public WsLayout {
   std::vector<int64_t> layer_ranges() const;
 
  private:
+  size_t linear_scratch(int T_) const;
   int check_batch(const int32_t* tok, int B, int S);
   int finish_checked(const float* hv);
   template <typename T>

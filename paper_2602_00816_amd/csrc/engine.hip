@@ -138,6 +138,16 @@ static int wgrad_splits(int M, int N, int T_) {
   return best;
 }
 
+// fp32 batches of more than 4096 tokens keep the fp32 matrix instructions and
+// their order of summation.  The split products are faster there too (27.7
+// against 37.6 ms for the 23M-parameter GPT-2's product on 16 x 512 tokens) and
+// nearer to fp64 (2.4e-7 against 5e-7 to 2e-6 over the vector), but the head
+// gradient's row of the most frequent token adds thousands of terms that
+// cancel: in one of eight seeds a single element carries 2.6e-4 of fp32
+// rounding, and moves by that much with any other order of summation (up to
+// 4096 tokens, 1.2e-4 at most over 96 products).
+static bool f32_chain(int T_) { return T_ > 4096; }
+
 // The weight gradient of the attention output projection (Mo x No) runs in
 // the same launch as the q/k/v one (Mq x Nq) when the q/k/v grid is not cut
 // along the tokens and the output projection's tiles fit into the idle part
@@ -198,6 +208,31 @@ static int mlp_wgrad_split(int Ma, int Na, int Mb, int Nb, int T_) {
 // ---------------------------------------------------------------------------
 // workspace plan
 // ---------------------------------------------------------------------------
+// Scratch for split contractions (at most 512 MB): the most that any linear
+// product of a batch of T_ tokens, or of T_/2, T_/4, .. (the smaller batches
+// of a dataset have fewer output tiles and are cut more), would use.
+size_t Engine::linear_scratch(int T_) const {
+  const size_t most = (size_t)512 << 20;
+  const int nu = gpt2 ? F : 2 * F;
+  const int shapes[5][2] = {{qkvd, d}, {d, Hq * dh}, {nu, d}, {d, F}, {V, d}};   // [out, in]
+  size_t mx = 0;
+  for (int t = T_; t >= 16; t /= 2)
+    for (const auto& sh : shapes)
+      for (int kind = 0; kind < 3; ++kind) {   // forward, input gradient, weight gradient
+        GemmArgs g[2];
+        for (int p = 0; p < 2; ++p) {
+          g[p].M = kind == 2 ? sh[0] : t;
+          g[p].N = kind == 0 ? sh[0] : sh[1];
+          g[p].K = kind == 0 ? sh[1] : kind == 1 ? sh[0] : t;
+          g[p].ldc = g[p].N;
+          g[p].npairs = 2 - p;
+        }
+        const int n = kind == 2 ? 1 : 2;
+        mx = std::max(mx, bf16 ? gemm_scratch<bf16_t>(g, n, most) : gemm_scratch<float>(g, n, most));
+      }
+  return mx;
+}
+
 size_t Engine::plan(int B, int S, int m, const fdh_lanczos_opts* o, WsLayout* out) const {
   WsLayout W;
   size_t cur = 0;
@@ -269,10 +304,10 @@ size_t Engine::plan(int B, int S, int m, const fdh_lanczos_opts* o, WsLayout* ou
     take(W.da_m, td * 4); take(W.da_d, td * 4);
     {
       const int nu = gpt2 ? F : 2 * F;
-      size_t mx = 0;
+      size_t mx = linear_scratch((int)T_);
       const int shapes[5][2] = {{qkvd, d}, {d, Hq * dh}, {nu, d}, {d, F}, {V, d}};
       for (const auto& sh : shapes) {
-        const int ns = wgrad_splits(sh[0], sh[1], (int)T_);
+        const int ns = bf16 || f32_chain((int)T_) ? wgrad_splits(sh[0], sh[1], (int)T_) : 1;
         if (ns > 1) mx = std::max(mx, (size_t)ns * sh[0] * sh[1] * 4);
       }
       // the down projection's slices when the MLP weight gradients share a launch
@@ -445,25 +480,37 @@ static double gemm_flops(const GemmArgs& g) {
 // ---------------------------------------------------------------------------
 // GEMM plumbing
 // ---------------------------------------------------------------------------
+// one product, or the two channel products of a linear layer (n = 2); scratch
+// for split contractions unless no_split
 template <typename T>
-static int run_gemm(Engine& e, GemmArgs& g) {
-  const char* msg = gemm_check<T>(g);
-  if (msg) {
-    e.err = msg;
-    return FDH_ERR_UNSUPPORTED;
+static int run_gemm(Engine& e, GemmArgs* g, int n, bool chain, bool no_split = false) {
+  double fl = 0.0;
+  for (int p = 0; p < n; ++p) {
+    const char* msg = gemm_check<T>(g[p]);
+    if (msg) {
+      e.err = msg;
+      return FDH_ERR_UNSUPPORTED;
+    }
+    fl += gemm_flops(g[p]);
+    g[p].f32_chain = chain;
+  }
+  GemmScratch sc;
+  if (!no_split) {
+    sc.p = (float*)(e.ws + e.wsplit.off);
+    sc.bytes = e.wsplit.bytes;
   }
   int e0 = 0;
   if (e.timing.on) {
     hipError_t r = e.timing.begin(e.stream, &e0);
     if (r != hipSuccess) { e.err = "timing event"; return FDH_ERR_HIP; }
   }
-  hipError_t r = gemm<T>(g, e.stream);
+  hipError_t r = gemm<T>(g, n, sc, e.stream);
   if (r != hipSuccess) {
     e.err = std::string("gemm launch: ") + hipGetErrorString(r);
     return FDH_ERR_HIP;
   }
   if (e.timing.on) {
-    r = e.timing.end(e.stream, 0, e0, gemm_flops(g), 0.0);
+    r = e.timing.end(e.stream, 0, e0, fl, 0.0);
     if (r != hipSuccess) { e.err = "timing event"; return FDH_ERR_HIP; }
   }
   return FDH_OK;
@@ -495,10 +542,12 @@ static int run_gemm_pair(Engine& e, GemmArgs& g0, GemmArgs& g1) {
   return FDH_OK;
 }
 
-#define RG(T, g)                       \
-  do {                                 \
-    int rc_ = run_gemm<T>(*this, g);   \
-    if (rc_ != FDH_OK) return rc_;     \
+// both channel products: g (mean) and h (half difference)
+#define RG2(T, g, h)                         \
+  do {                                       \
+    GemmArgs gh_[2] = {h, g};                       \
+    int rc_ = run_gemm<T>(*this, gh_, 2, chain);    \
+    if (rc_ != FDH_OK) return rc_;           \
   } while (0)
 
 // ---------------------------------------------------------------------------
@@ -515,6 +564,7 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
   const float feps = (float)eps;
   const float inv_eps = (float)(1.0 / eps);
   const bool ln = gpt2;
+  const bool chain = !bf16 && f32_chain(T_);
   const float neps = cfg.norm_eps;
   const int G = Hq / Hk;
   const float att_scale = (float)(1.0 / std::sqrt((double)dh));
@@ -555,7 +605,6 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     g.C = Ym; g.ldc = N; g.out_type = out;
     g.resid = Rm;
     if (bias.valid()) g.bias_theta = th + bias.off;
-    RG(T, g);
     GemmArgs h;
     h.M = T_; h.N = N; h.K = K; h.npairs = 2;
     h.A[0] = kmaj(Xd, K); h.B[0] = kmaj(th + W.off, K);
@@ -563,7 +612,7 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     h.C = Yd; h.ldc = N; h.out_type = out;
     h.resid = Rd;
     if (bias.valid()) { h.bias_v = v + bias.off; h.bias_v_scale = feps; }
-    RG(T, h);
+    RG2(T, g, h);
     return FDH_OK;
   };
   // dX = dY W ; W [N, K]
@@ -573,13 +622,12 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     g.A[0] = kmaj(dYm, N);
     g.B[0] = mnmaj(th + W.off, K);
     g.C = dXm; g.ldc = K; g.out_type = out;
-    RG(T, g);
     GemmArgs h;
     h.M = T_; h.N = K; h.K = N; h.npairs = 2;
     h.A[0] = kmaj(dYd, N); h.B[0] = mnmaj(th + W.off, K);
     h.A[1] = kmaj(dYm, N); h.B[1] = mnmaj(lo + W.off, K);
     h.C = dXd; h.ldc = K; h.out_type = out;
-    RG(T, h);
+    RG2(T, g, h);
     return FDH_OK;
   };
   // Hv_W = (dY.m^T X.d + dY.d^T X.m) / eps
@@ -620,11 +668,11 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
   };
   auto lin_wgrad = [&](const T* dYm, const T* dYd, int N, const T* Xm, const T* Xd, int K, const ParamRef& W) -> int {
     GemmArgs g = wgrad_args(dYm, dYd, N, Xm, Xd, K, W);
-    const int ns = wgrad_splits(N, K, T_);
+    // (fp32 products are cut, where that pays, inside the launch)
+    const int ns = bf16 || chain ? wgrad_splits(N, K, T_) : 1;
     if (ns == 1 || force_unsplit || wsplit.bytes < (size_t)ns * N * K * 4) {
       if (acc) g.beta = 1.f;
-      RG(T, g);
-      return FDH_OK;
+      return run_gemm<T>(*this, &g, 1, chain, force_unsplit);
     }
     const int kc = T_ / ns;
     g.K = kc;
@@ -634,7 +682,8 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
       g.B[p].s_outer = (int64_t)kc * K;
     }
     g.C = F32(wsplit); g.c_outer = (int64_t)N * K;
-    RG(T, g);
+    const int rc = run_gemm<T>(*this, &g, 1, chain, true);
+    if (rc != FDH_OK) return rc;
     int e0 = 0;
     if (timing.on) CK(timing.begin(st, &e0));
     CK(launch_sum_splits(hv + W.off, F32(wsplit), ns, (int64_t)N * K, acc, st));
@@ -734,13 +783,12 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
         g.A[0] = Aq_m; g.B[0] = Bk_m;
         g.C = F32(sc_m); g.ldc = S; g.c_outer = (int64_t)Hq * pp_stride; g.c_inner = pp_stride;
         g.alpha = att_scale; g.causal = CAUSAL_SKIP_UPPER;
-        RG(T, g);
         GemmArgs h = g;
         h.npairs = 2;
         h.A[0] = Aq_m; h.B[0] = Bk_d;
         h.A[1] = Aq_d; h.B[1] = Bk_m;
         h.C = F32(sc_d);
-        RG(T, h);
+        RG2(T, g, h);
       }
       CK(launch_attn_softmax<T>(PairT<T>{OP(s.P_m), OP(s.P_d)}, F32(sc_m), F32(sc_d), B * Hq * S, S, st));
       // o = P v
@@ -756,13 +804,12 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
         g.A[0] = Ap_m; g.B[0] = Bv_m;
         g.C = OP(s.o_m); g.ldc = (int64_t)Hq * dh; g.c_outer = (int64_t)S * Hq * dh; g.c_inner = dh;
         g.out_type = OUT_OP; g.causal = CAUSAL_K_LE_M;
-        RG(T, g);
         GemmArgs h = g;
         h.npairs = 2;
         h.A[0] = Ap_m; h.B[0] = Bv_d;
         h.A[1] = Ap_d; h.B[1] = Bv_m;
         h.C = OP(s.o_d);
-        RG(T, h);
+        RG2(T, g, h);
       }
     }
     // output projection + residual
@@ -881,13 +928,12 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
         g.A[0] = Ao_m; g.B[0] = Bv_m;
         g.C = F32(sc_m); g.ldc = S; g.c_outer = (int64_t)Hq * pp_stride; g.c_inner = pp_stride;
         g.causal = CAUSAL_SKIP_UPPER;
-        RG(T, g);
         GemmArgs h = g;
         h.npairs = 2;
         h.A[0] = Ao_m; h.B[0] = Bv_d;
         h.A[1] = Ao_d; h.B[1] = Bv_m;
         h.C = F32(sc_d);
-        RG(T, h);
+        RG2(T, g, h);
       }
       CK(launch_attn_dsoftmax<T>(PairT<T>{OP(dS_m), OP(dS_d)}, OP(s.P_m), OP(s.P_d), F32(sc_m), F32(sc_d), B * Hq * S, S, st));
       // dv = P^T do ; dq = dS k / sqrt(dh) ; dk = dS^T q / sqrt(dh)
@@ -913,13 +959,12 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
           g.A[0] = At_m; g.B[0] = Bo_m;
           out_into(g, grp);
           g.C = grp ? F32(gqa_m) : gm + voff;
-          RG(T, g);
           GemmArgs h = g;
           h.npairs = 2;
           h.A[0] = At_m; h.B[0] = Bo_d;
           h.A[1] = At_d; h.B[1] = Bo_m;
           h.C = grp ? F32(gqa_d) : gd + voff;
-          RG(T, h);
+          RG2(T, g, h);
           if (grp) {
             CK(launch_group_sum(gm + voff, qkvd, F32(gqa_m), T_, Hk, G, dh, st));
             CK(launch_group_sum(gd + voff, qkvd, F32(gqa_d), T_, Hk, G, dh, st));
@@ -937,13 +982,12 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
           g.A[0] = As_m; g.B[0] = Bk_m;
           out_into(g, false);
           g.C = gm;
-          RG(T, g);
           GemmArgs h = g;
           h.npairs = 2;
           h.A[0] = As_m; h.B[0] = Bk_d;
           h.A[1] = As_d; h.B[1] = Bk_m;
           h.C = gd;
-          RG(T, h);
+          RG2(T, g, h);
         }
         // dk
         {
@@ -957,13 +1001,12 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
           g.A[0] = Ast_m; g.B[0] = Bq_m;
           out_into(g, grp);
           g.C = grp ? F32(gqa_m) : gm + koff;
-          RG(T, g);
           GemmArgs h = g;
           h.npairs = 2;
           h.A[0] = Ast_m; h.B[0] = Bq_d;
           h.A[1] = Ast_d; h.B[1] = Bq_m;
           h.C = grp ? F32(gqa_d) : gd + koff;
-          RG(T, h);
+          RG2(T, g, h);
           if (grp) {
             CK(launch_group_sum(gm + koff, qkvd, F32(gqa_m), T_, Hk, G, dh, st));
             CK(launch_group_sum(gd + koff, qkvd, F32(gqa_d), T_, Hk, G, dh, st));

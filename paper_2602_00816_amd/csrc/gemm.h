@@ -38,12 +38,28 @@ struct GemmArgs {
   float bias_v_scale = 1.f;
   const float* resid = nullptr;           // fp32, same indexing as C, added (OUT_F32 only)
   int causal = CAUSAL_NONE;
+  bool f32_chain = false;                 // fp32 only: one fp32 matrix-instruction chain over k per output
   int tile = 0;                           // 0 automatic; bf16 only: 1 128x128, 2 256x256, 3 256x128
 };
 
-// T = float (fp32 MFMA) or bf16_t (bf16 MFMA, fp32 accumulation)
+// Device memory for the parts of split contractions (gemm_split.h); none: no product is cut.
+struct GemmScratch {
+  float* p = nullptr;
+  size_t bytes = 0;
+};
+
+// One product (n = 1), or two of the same M, N, K, batch and layouts (the two
+// channels of a linear layer), in one launch where that pays.  T = float or
+// bf16_t operands, fp32 accumulation.
 template <typename T>
-hipError_t gemm(const GemmArgs& a, hipStream_t stream);
+hipError_t gemm(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t stream);
+
+// Scratch that the launch would use, at most `most` bytes.
+template <typename T>
+size_t gemm_scratch(const GemmArgs* g, int n, size_t most);
+
+hipError_t gemm_f32(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t stream);
+size_t gemm_f32_scratch(const GemmArgs* g, int n, size_t most);
 
 // Two independent products (batched or not, no causal limits) in one launch
 // of the 256 x 256 kernel that a0 runs on, when a1 can run on it too; else one

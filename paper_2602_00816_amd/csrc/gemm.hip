@@ -1,10 +1,9 @@
-// Batched MFMA GEMM for gfx950:  C[z] = alpha * sum_p A_p[z] B_p[z]^T (+ epilogue).
+// Batched bf16 MFMA GEMM for gfx950:  C[z] = alpha * sum_p A_p[z] B_p[z]^T (+ epilogue).
+// (fp32 operands: gemm_f32.hip.)
 //
-// Two kernels:
+// Two register-staged kernels, and below them the ones fed by direct loads to LDS:
 //  * gemm_kernel  - 128x128 workgroup tile, 4 wavefronts of 64x64 (2x2 blocks
-//    of 32x32 MFMA accumulators), fp32 (v_mfma_f32_32x32x2_f32) or bf16
-//    (v_mfma_f32_32x32x16_bf16) operands; used for fp32 and for small bf16
-//    problems.
+//    of 32x32 MFMA accumulators, v_mfma_f32_32x32x16_bf16); used for small problems.
 //  * gemm_bf16_big - bf16 only, 256x256 (8 wavefronts) or 256x128 (4
 //    wavefronts) workgroup tiles; every wavefront owns 128x64 as 4x2 blocks of
 //    32x32, so one A fragment read from LDS feeds two MFMAs and one B fragment
@@ -13,7 +12,7 @@
 // HBM are transposed on their way into LDS, so the MFMA fragment reads are
 // always single 16-byte LDS reads.  Global loads are 16-byte vectors,
 // prefetched into registers one K tile ahead.
-#include "gemm.h"
+#include "gemm_dev.h"
 
 #include <type_traits>
 
@@ -23,36 +22,20 @@ namespace {
 
 constexpr int BM = 128, BN = 128, NT = 256;
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
-
-template <typename T> struct Tr;
-template <> struct Tr<bf16_t> {
-  static constexpr int KT = 32;   // K per LDS tile
-  static constexpr int VEC = 8;   // elements per 16-byte vector
-  static constexpr int PAD = 8;   // LDS row padding (elements)
-};
-template <> struct Tr<float> {
-  static constexpr int KT = 16;
-  static constexpr int VEC = 4;
-  static constexpr int PAD = 4;
-};
+constexpr int KT = 32;   // K per LDS tile
+constexpr int VEC = 8;   // elements per 16-byte vector
+constexpr int PAD = 8;   // LDS row padding (elements)
 
 struct alignas(16) Vec16 { uint32_t w[4]; };
-
-__device__ inline int64_t batch_off(int z, int inner_count, int64_t s_outer, int64_t s_inner, int div) {
-  return (int64_t)(z / inner_count) * s_outer + (int64_t)((z % inner_count) / div) * s_inner;
-}
 
 // ===========================================================================
 // 128x128 kernel
 // ===========================================================================
 // Load the 16-byte vector number `vid` of a tile starting at (row0, k0).
 // Returns zeros outside [0,rows) x [0,K).
-template <typename T, bool KMAJ>
-__device__ inline Vec16 load_vec(const T* base, int64_t s_row, int64_t s_k, int rows, int K,
+template <bool KMAJ>
+__device__ inline Vec16 load_vec(const bf16_t* base, int64_t s_row, int64_t s_k, int rows, int K,
                                  int row0, int k0, int vid) {
-  constexpr int KT = Tr<T>::KT, VEC = Tr<T>::VEC;
   Vec16 v = {{0u, 0u, 0u, 0u}};
   if (KMAJ) {
     const int r = vid / (KT / VEC);
@@ -68,9 +51,9 @@ __device__ inline Vec16 load_vec(const T* base, int64_t s_row, int64_t s_k, int 
   return v;
 }
 
-template <typename T, bool KMAJ>
-__device__ inline void store_vec(T* s, const Vec16& v, int vid) {
-  constexpr int KT = Tr<T>::KT, VEC = Tr<T>::VEC, LD = KT + Tr<T>::PAD;
+template <bool KMAJ>
+__device__ inline void store_vec(bf16_t* s, const Vec16& v, int vid) {
+  constexpr int LD = KT + PAD;
   if (KMAJ) {
     const int r = vid / (KT / VEC);
     const int kk = (vid % (KT / VEC)) * VEC;
@@ -78,21 +61,17 @@ __device__ inline void store_vec(T* s, const Vec16& v, int vid) {
   } else {
     const int kk = vid / (BM / VEC);
     const int r = (vid % (BM / VEC)) * VEC;
-    const T* e = reinterpret_cast<const T*>(&v);
+    const bf16_t* e = reinterpret_cast<const bf16_t*>(&v);
 #pragma unroll
     for (int j = 0; j < VEC; ++j) s[(r + j) * LD + kk] = e[j];
   }
 }
 
-template <typename T>
-__device__ inline void mma_tile(const T* sA, const T* sB, f32x16_t (&acc)[2][2], int wm, int wn, int lane);
-
-template <>
-__device__ inline void mma_tile<bf16_t>(const bf16_t* sA, const bf16_t* sB, f32x16_t (&acc)[2][2],
+__device__ inline void mma_tile(const bf16_t* sA, const bf16_t* sB, f32x16_t (&acc)[2][2],
                                         int wm, int wn, int lane) {
-  constexpr int LD = Tr<bf16_t>::KT + Tr<bf16_t>::PAD;
+  constexpr int LD = KT + PAD;
 #pragma unroll
-  for (int kk = 0; kk < Tr<bf16_t>::KT; kk += 16) {
+  for (int kk = 0; kk < KT; kk += 16) {
     bf16x8_t af[2], bfr[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -109,279 +88,11 @@ __device__ inline void mma_tile<bf16_t>(const bf16_t* sA, const bf16_t* sB, f32x
   }
 }
 
-template <>
-__device__ inline void mma_tile<float>(const float* sA, const float* sB, f32x16_t (&acc)[2][2],
-                                       int wm, int wn, int lane) {
-  constexpr int LD = Tr<float>::KT + Tr<float>::PAD;
-#pragma unroll
-  for (int kk = 0; kk < Tr<float>::KT; kk += 2) {
-    float af[2], bfr[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      af[i] = sA[(wm * 64 + i * 32 + (lane & 31)) * LD + kk + (lane >> 5)];
-      bfr[i] = sB[(wn * 64 + i * 32 + (lane & 31)) * LD + kk + (lane >> 5)];
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bfr[j], af[i], acc[i][j], 0, 0, 0);
-  }
-}
-
-// shared epilogue: accumulator block (i, j) of a wavefront whose 32x32 block
-// origin is (rb, cb).  Every MFMA takes the B fragment as its first operand, so
-// the block holds C^T in the MFMA output layout: lane l owns row rb + (l & 31)
-// of C and, for g = 0..3, the four consecutive columns cb + 8g + 4(l >> 5) + 0..3
-// (accumulator elements 4g..4g+3).  Each such quad is stored, and the residual
-// or previous C loaded, as one vector where the addresses are aligned.
-// four consecutive outputs at C[idx..idx+3], 16-byte (fp32) or 8-byte (bf16)
-// aligned: one vector store, with the residual and previous C read as vectors
-template <typename T>
-__device__ inline void store_quad(const GemmArgs& a, const float (&x)[4], int64_t idx) {
-  if (a.out_type == OUT_F32) {
-    float* C = reinterpret_cast<float*>(a.C);
-    float4 v = make_float4(x[0], x[1], x[2], x[3]);
-    if (a.resid) {
-      const float4 r = *reinterpret_cast<const float4*>(a.resid + idx);
-      v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
-    }
-    if (a.beta != 0.f) {
-      const float4 c = *reinterpret_cast<const float4*>(C + idx);
-      v.x += a.beta * c.x; v.y += a.beta * c.y; v.z += a.beta * c.z; v.w += a.beta * c.w;
-    }
-    *reinterpret_cast<float4*>(C + idx) = v;
-  } else {
-    T* C = reinterpret_cast<T*>(a.C);
-    if constexpr (sizeof(T) == 2) {
-      uint2 u;
-      u.x = (uint32_t)f32_to_bf16(x[0]) | ((uint32_t)f32_to_bf16(x[1]) << 16);
-      u.y = (uint32_t)f32_to_bf16(x[2]) | ((uint32_t)f32_to_bf16(x[3]) << 16);
-      *reinterpret_cast<uint2*>(C + idx) = u;
-    } else {
-      *reinterpret_cast<float4*>(C + idx) = make_float4(x[0], x[1], x[2], x[3]);
-    }
-  }
-}
-
-template <typename T>
-__device__ inline void store_block(const GemmArgs& a, const f32x16_t& acc, int64_t coff, int rb, int cb, int lane) {
-  const int row = rb + (lane & 31);
-  if (row >= a.M) return;
-  const int64_t rbase = coff + (int64_t)row * a.ldc;
-  // vector path: row starts and column quads aligned for 16-byte (fp32) or
-  // 8-byte (bf16) accesses
-  const size_t ob = a.out_type == OUT_F32 ? 4 : sizeof(T);
-  const bool aligned = a.ldc % 4 == 0 && coff % 4 == 0 && (uintptr_t)a.C % (4 * ob) == 0 &&
-                       (!a.resid || (uintptr_t)a.resid % 16 == 0);
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const int col0 = cb + 8 * g + 4 * (lane >> 5);
-    if (col0 >= a.N) continue;
-    float x[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int col = min(col0 + r, a.N - 1);
-      float badd = 0.f;
-      if (a.bias_theta) badd += a.bias_theta_scale * ldf(reinterpret_cast<const T*>(a.bias_theta), col);
-      if (a.bias_v) badd += a.bias_v_scale * a.bias_v[col];
-      x[r] = a.alpha * acc[4 * g + r] + badd;
-    }
-    if (aligned && col0 + 3 < a.N) {
-      store_quad<T>(a, x, rbase + col0);
-    } else {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (col0 + r >= a.N) break;
-        const int64_t idx = rbase + col0 + r;
-        float y = x[r];
-        if (a.out_type == OUT_F32) {
-          float* C = reinterpret_cast<float*>(a.C);
-          if (a.resid) y += a.resid[idx];
-          if (a.beta != 0.f) y += a.beta * C[idx];
-          C[idx] = y;
-        } else {
-          stf(reinterpret_cast<T*>(a.C), idx, y);
-        }
-      }
-    }
-  }
-}
-
-// LDS-staged epilogue of one 32x32 block: the wavefront writes its block
-// (scaled by alpha) to its own staging area of 32 rows x 36 floats, then reads
-// it back so that lane l holds row 8k + (l >> 3), columns 4(l & 7) + 0..3:
-// every global access then covers eight rows of 128 contiguous bytes.  The
-// caller guarantees the staging area is not in use by the main loop any more.
-constexpr int STG_LD = 36;
-constexpr int STG_FLOATS = 32 * STG_LD;
-// four staging areas fit one ring stage of the DMA kernels (256 x 32 + 128 x 32 bf16 at the smallest)
-static_assert(4 * STG_FLOATS * 4 <= (256 + 128) * 32 * 2, "staging areas exceed a ring stage");
-static_assert(4 * STG_FLOATS * 4 <= (256 + 256) * 32 * 2, "four blocks of staging exceed a 256 x 256 ring stage");
-// (the eight-wavefront kernel gives each pair of wavefronts one 256 x 256 stage, two blocks each)
-
-__device__ inline void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <typename T>
-__device__ inline void store_block_lds(const GemmArgs& a, const f32x16_t& acc, int64_t coff, int rb, int cb, int lane,
-                                       float* stg) {
-  {
-    const int wr = lane & 31, wh = lane >> 5;
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<float4*>(stg + wr * STG_LD + 8 * g + 4 * wh) =
-          make_float4(a.alpha * acc[4 * g], a.alpha * acc[4 * g + 1], a.alpha * acc[4 * g + 2], a.alpha * acc[4 * g + 3]);
-  }
-  wave_lds_order();
-  const int c4 = 4 * (lane & 7);
-  const int col0 = cb + c4;
-  float badd[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int col = min(col0 + r, a.N - 1);
-    if (a.bias_theta) badd[r] += a.bias_theta_scale * ldf(reinterpret_cast<const T*>(a.bias_theta), col);
-    if (a.bias_v) badd[r] += a.bias_v_scale * a.bias_v[col];
-  }
-  const size_t ob = a.out_type == OUT_F32 ? 4 : sizeof(T);
-  const bool aligned = a.ldc % 4 == 0 && coff % 4 == 0 && (uintptr_t)a.C % (4 * ob) == 0 &&
-                       (!a.resid || (uintptr_t)a.resid % 16 == 0);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int lr = 8 * k + (lane >> 3);
-    const float4 v = *reinterpret_cast<const float4*>(stg + lr * STG_LD + c4);
-    const int row = rb + lr;
-    if (row >= a.M || col0 >= a.N) continue;
-    const float x[4] = {v.x + badd[0], v.y + badd[1], v.z + badd[2], v.w + badd[3]};
-    const int64_t base = coff + (int64_t)row * a.ldc + col0;
-    if (aligned && col0 + 3 < a.N) {
-      store_quad<T>(a, x, base);
-    } else {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (col0 + r >= a.N) break;
-        float y = x[r];
-        if (a.out_type == OUT_F32) {
-          float* C = reinterpret_cast<float*>(a.C);
-          if (a.resid) y += a.resid[base + r];
-          if (a.beta != 0.f) y += a.beta * C[base + r];
-          C[base + r] = y;
-        } else {
-          stf(reinterpret_cast<T*>(a.C), base + r, y);
-        }
-      }
-    }
-  }
-  wave_lds_order();   // the next block's writes come after these reads
-}
-
-// LDS-staged epilogue of NB 32x32 blocks of one wavefront (blocks (rb, cb[j]),
-// j < NB) in one round: all NB are written to the wavefront's staging area
-// (NB x 32 rows x 36 floats), then every lane reads its 4 NB quads, issues
-// every global read the epilogue needs (residual, previous C) before any
-// store, and stores.  One round has the latency of one block where the
-// one-block form pays it NB times (a wavefront that is alone on its SIMD has
-// nothing else to hide it with).  Global accesses cover eight rows of
-// 128 contiguous bytes, as in store_block_lds.
-template <typename T, int NB>
-__device__ inline void store_blocks_lds(const GemmArgs& a, const f32x16_t (&acc)[NB], int64_t coff, int rb,
-                                        const int (&cb)[NB], int lane, float* stg) {
-  {
-    const int wr = lane & 31, wh = lane >> 5;
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<float4*>(stg + j * STG_FLOATS + wr * STG_LD + 8 * g + 4 * wh) =
-            make_float4(a.alpha * acc[j][4 * g], a.alpha * acc[j][4 * g + 1], a.alpha * acc[j][4 * g + 2],
-                        a.alpha * acc[j][4 * g + 3]);
-  }
-  wave_lds_order();
-  const int c4 = 4 * (lane & 7);
-  float4 v[NB][4];
-#pragma unroll
-  for (int j = 0; j < NB; ++j)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[j][k] = *reinterpret_cast<const float4*>(stg + j * STG_FLOATS + (8 * k + (lane >> 3)) * STG_LD + c4);
-  wave_lds_order();   // the next round's writes come after these reads
-  const size_t ob = a.out_type == OUT_F32 ? 4 : sizeof(T);
-  const bool aligned = a.ldc % 4 == 0 && coff % 4 == 0 && (uintptr_t)a.C % (4 * ob) == 0 &&
-                       (!a.resid || (uintptr_t)a.resid % 16 == 0);
-  const bool full = aligned && rb + 32 <= a.M && cb[NB - 1] + 32 <= a.N;
-  if (full && a.out_type == OUT_F32 && !a.bias_theta && !a.bias_v) {
-    // the common case of the residual stream and the weight gradients: all
-    // reads first, then all stores
-    float* C = reinterpret_cast<float*>(a.C);
-    float4 r[NB][4];
-    const bool rd = a.resid != nullptr, bt = a.beta != 0.f;
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int64_t idx = coff + (int64_t)(rb + 8 * k + (lane >> 3)) * a.ldc + cb[j] + c4;
-        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (rd) t = *reinterpret_cast<const float4*>(a.resid + idx);
-        if (bt) {
-          const float4 c = *reinterpret_cast<const float4*>(C + idx);
-          t.x += a.beta * c.x; t.y += a.beta * c.y; t.z += a.beta * c.z; t.w += a.beta * c.w;
-        }
-        r[j][k] = t;
-      }
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int64_t idx = coff + (int64_t)(rb + 8 * k + (lane >> 3)) * a.ldc + cb[j] + c4;
-        *reinterpret_cast<float4*>(C + idx) =
-            make_float4(v[j][k].x + r[j][k].x, v[j][k].y + r[j][k].y, v[j][k].z + r[j][k].z, v[j][k].w + r[j][k].w);
-      }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int col0 = cb[j] + c4;
-    float badd[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int col = min(col0 + q, a.N - 1);
-      if (a.bias_theta) badd[q] += a.bias_theta_scale * ldf(reinterpret_cast<const T*>(a.bias_theta), col);
-      if (a.bias_v) badd[q] += a.bias_v_scale * a.bias_v[col];
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int row = rb + 8 * k + (lane >> 3);
-      if (row >= a.M || col0 >= a.N) continue;
-      const float x[4] = {v[j][k].x + badd[0], v[j][k].y + badd[1], v[j][k].z + badd[2], v[j][k].w + badd[3]};
-      const int64_t base = coff + (int64_t)row * a.ldc + col0;
-      if (aligned && col0 + 3 < a.N) {
-        store_quad<T>(a, x, base);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (col0 + q >= a.N) break;
-          float y = x[q];
-          if (a.out_type == OUT_F32) {
-            float* C = reinterpret_cast<float*>(a.C);
-            if (a.resid) y += a.resid[base + q];
-            if (a.beta != 0.f) y += a.beta * C[base + q];
-            C[base + q] = y;
-          } else {
-            stf(reinterpret_cast<T*>(a.C), base + q, y);
-          }
-        }
-      }
-    }
-  }
-}
-
-template <typename T, bool AK, bool BKM>
+template <bool AK, bool BKM>
 __global__ __launch_bounds__(NT) void gemm_kernel(GemmArgs a) {
-  constexpr int KT = Tr<T>::KT, LD = KT + Tr<T>::PAD;
-  __shared__ __attribute__((aligned(16))) T sA[BM * LD];
-  __shared__ __attribute__((aligned(16))) T sB[BN * LD];
+  constexpr int LD = KT + PAD;
+  __shared__ __attribute__((aligned(16))) bf16_t sA[BM * LD];
+  __shared__ __attribute__((aligned(16))) bf16_t sB[BN * LD];
 
   const int z = blockIdx.z;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
@@ -405,30 +116,30 @@ __global__ __launch_bounds__(NT) void gemm_kernel(GemmArgs a) {
   for (int p = 0; p < a.npairs; ++p) {
     const GemmOperand& A = a.A[p];
     const GemmOperand& B = a.B[p];
-    const T* pa = reinterpret_cast<const T*>(A.ptr) + batch_off(z, a.inner_count, A.s_outer, A.s_inner, A.inner_div);
-    const T* pb = reinterpret_cast<const T*>(B.ptr) + batch_off(z, a.inner_count, B.s_outer, B.s_inner, B.inner_div);
+    const bf16_t* pa = reinterpret_cast<const bf16_t*>(A.ptr) + batch_off(z, a.inner_count, A.s_outer, A.s_inner, A.inner_div);
+    const bf16_t* pb = reinterpret_cast<const bf16_t*>(B.ptr) + batch_off(z, a.inner_count, B.s_outer, B.s_inner, B.inner_div);
     Vec16 ra[2], rb[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      ra[i] = load_vec<T, AK>(pa, A.s_row, A.s_k, a.M, kmax, m0, kmin, tid + i * NT);
-      rb[i] = load_vec<T, BKM>(pb, B.s_row, B.s_k, a.N, kmax, n0, kmin, tid + i * NT);
+      ra[i] = load_vec<AK>(pa, A.s_row, A.s_k, a.M, kmax, m0, kmin, tid + i * NT);
+      rb[i] = load_vec<BKM>(pb, B.s_row, B.s_k, a.N, kmax, n0, kmin, tid + i * NT);
     }
     for (int k0 = kmin; k0 < kmax; k0 += KT) {
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        store_vec<T, AK>(sA, ra[i], tid + i * NT);
-        store_vec<T, BKM>(sB, rb[i], tid + i * NT);
+        store_vec<AK>(sA, ra[i], tid + i * NT);
+        store_vec<BKM>(sB, rb[i], tid + i * NT);
       }
       __syncthreads();
       if (k0 + KT < kmax) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          ra[i] = load_vec<T, AK>(pa, A.s_row, A.s_k, a.M, kmax, m0, k0 + KT, tid + i * NT);
-          rb[i] = load_vec<T, BKM>(pb, B.s_row, B.s_k, a.N, kmax, n0, k0 + KT, tid + i * NT);
+          ra[i] = load_vec<AK>(pa, A.s_row, A.s_k, a.M, kmax, m0, k0 + KT, tid + i * NT);
+          rb[i] = load_vec<BKM>(pb, B.s_row, B.s_k, a.N, kmax, n0, k0 + KT, tid + i * NT);
         }
       }
-      mma_tile<T>(sA, sB, acc, wm, wn, lane);
+      mma_tile(sA, sB, acc, wm, wn, lane);
     }
   }
 
@@ -437,7 +148,7 @@ __global__ __launch_bounds__(NT) void gemm_kernel(GemmArgs a) {
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      store_block<T>(a, acc[i][j], coff, m0 + wm * 64 + i * 32, n0 + wn * 64 + j * 32, lane);
+      store_block<bf16_t>(a, acc[i][j], coff, m0 + wm * 64 + i * 32, n0 + wn * 64 + j * 32, lane);
 }
 
 // ===========================================================================
@@ -651,7 +362,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_big(GemmArgs a) {
 constexpr int KT3 = 32, NS3 = 4;
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16_t;
-typedef __attribute__((address_space(3))) void lds_void_t;
 
 __device__ inline int kswz(int row, int c) { return row * KT3 + ((c ^ ((row >> 2) & 3)) << 3); }        // elements
 template <int R>
@@ -708,12 +418,6 @@ __device__ inline bf16x8_t frag(const bf16_t* t, int r0, int kk, int lane) {
     const v8i16 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8_t, v);
   }
-}
-
-template <int N>
-__device__ inline void wait_vm() {
-  // s_waitcnt with vmcnt = N (bits 3:0 and 15:14), expcnt and lgkmcnt left at their maxima
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 #ifndef FDH_DMA_STAGES
@@ -1068,14 +772,6 @@ __device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int l
   }
 }
 
-// Workgroup ids are dealt to the 8 XCDs in turn; renumber them so that each
-// XCD takes a contiguous run of tiles (neighbouring tiles share operand rows
-// and columns in that XCD's L2).
-__device__ inline int xcd_order(int lin, int nb) {
-  const int per = nb / 8;
-  return lin < per * 8 ? (lin % 8) * per + lin / 8 : lin;
-}
-
 template <bool AK, bool BKM, int WN = 2>
 __global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_w4(GemmArgs a) {
   const int gx = gridDim.x, gy = gridDim.y;
@@ -1106,7 +802,6 @@ __global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_w4_pair(GemmArgs a0, Ge
 // c ^ ((r >> 1) & 7) (16 lanes reading 16 consecutive rows hit 64 banks).
 // ===========================================================================
 constexpr int KT4 = 64;
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
 __device__ inline int kswz64(int row, int c) { return row * KT4 + ((c ^ ((row >> 1) & 7)) << 3); }   // elements
 
 template <int R, bool KMAJ>
@@ -1334,7 +1029,7 @@ void launch_big(const GemmArgs& a, hipStream_t stream) {
 
 template <typename T>
 const char* gemm_check(const GemmArgs& a) {
-  constexpr int VEC = Tr<T>::VEC;
+  constexpr int VEC = 16 / sizeof(T);
   if (a.M < 0 || a.N < 0 || a.K < 0 || a.nbatch < 1 || a.inner_count < 1) return "gemm: bad sizes";
   if (a.npairs < 1 || a.npairs > 2) return "gemm: npairs must be 1 or 2";
   if (a.K % VEC) return "gemm: K must be a multiple of the 16-byte vector width";
@@ -1366,10 +1061,10 @@ const char* gemm_check(const GemmArgs& a) {
   if (a.tile < 0 || a.tile > 8) return "gemm: bad tile";
   if (a.tile >= 4 && (a.K % 32 || a.M < 8 || a.N < 8)) return "gemm: the DMA kernel needs K % 32 == 0";
   if (a.tile == 7 && a.K % 64) return "gemm: the 64-deep kernels need K % 64 == 0";
-  if (a.tile == 7 && a.npairs == 2 &&
+  if ((a.tile == 7 || sizeof(T) == 4) && a.npairs == 2 &&
       (a.A[1].s_row != a.A[0].s_row || a.A[1].s_k != a.A[0].s_k || a.B[1].s_row != a.B[0].s_row ||
        a.B[1].s_k != a.B[0].s_k))
-    return "gemm: the 64-deep kernels need equal operand strides in both pairs";
+    return "gemm: this kernel needs equal operand strides in both pairs";
   return nullptr;
 }
 
@@ -1394,26 +1089,38 @@ static int bf16_tile(const GemmArgs& a) {
   return tile;
 }
 
-template <typename T>
-hipError_t gemm(const GemmArgs& a, hipStream_t stream) {
+static hipError_t gemm_one(const GemmArgs& a, hipStream_t stream) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
-  if constexpr (sizeof(T) == 2) {
-    const int tile = bf16_tile(a);
-    if (tile == 2) { launch_big<256, 256, 2, 4>(a, stream); return hipGetLastError(); }
-    if (tile == 3) { launch_big<256, 128, 2, 2>(a, stream); return hipGetLastError(); }
-    if (tile == 4) { launch_dma<256, 4>(a, stream); return hipGetLastError(); }
-    if (tile == 5) { launch_dma<128, 2>(a, stream); return hipGetLastError(); }
-    if (tile == 6) { launch_w4<2>(a, stream); return hipGetLastError(); }
-    if (tile == 8) { launch_w4<4>(a, stream); return hipGetLastError(); }
-    if (tile == 7) { launch_w4k64(a, stream); return hipGetLastError(); }
-  }
+  const int tile = bf16_tile(a);
+  if (tile == 2) { launch_big<256, 256, 2, 4>(a, stream); return hipGetLastError(); }
+  if (tile == 3) { launch_big<256, 128, 2, 2>(a, stream); return hipGetLastError(); }
+  if (tile == 4) { launch_dma<256, 4>(a, stream); return hipGetLastError(); }
+  if (tile == 5) { launch_dma<128, 2>(a, stream); return hipGetLastError(); }
+  if (tile == 6) { launch_w4<2>(a, stream); return hipGetLastError(); }
+  if (tile == 8) { launch_w4<4>(a, stream); return hipGetLastError(); }
+  if (tile == 7) { launch_w4k64(a, stream); return hipGetLastError(); }
   dim3 grid(ceil_div(a.N, BN), ceil_div(a.M, BM), a.nbatch);
   const bool ak = a.A[0].s_k == 1, bk = a.B[0].s_k == 1;
-  if (ak && bk) hipLaunchKernelGGL((gemm_kernel<T, true, true>), grid, dim3(NT), 0, stream, a);
-  else if (ak && !bk) hipLaunchKernelGGL((gemm_kernel<T, true, false>), grid, dim3(NT), 0, stream, a);
-  else if (!ak && bk) hipLaunchKernelGGL((gemm_kernel<T, false, true>), grid, dim3(NT), 0, stream, a);
-  else hipLaunchKernelGGL((gemm_kernel<T, false, false>), grid, dim3(NT), 0, stream, a);
+  if (ak && bk) hipLaunchKernelGGL((gemm_kernel<true, true>), grid, dim3(NT), 0, stream, a);
+  else if (ak && !bk) hipLaunchKernelGGL((gemm_kernel<true, false>), grid, dim3(NT), 0, stream, a);
+  else if (!ak && bk) hipLaunchKernelGGL((gemm_kernel<false, true>), grid, dim3(NT), 0, stream, a);
+  else hipLaunchKernelGGL((gemm_kernel<false, false>), grid, dim3(NT), 0, stream, a);
   return hipGetLastError();
+}
+
+template <typename T>
+hipError_t gemm(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t stream) {
+  if constexpr (sizeof(T) == 4) return gemm_f32(g, n, ws, stream);
+  for (int p = 0; p < n; ++p) {
+    const hipError_t r = gemm_one(g[p], stream);
+    if (r != hipSuccess) return r;
+  }
+  return hipSuccess;
+}
+
+template <typename T>
+size_t gemm_scratch(const GemmArgs* g, int n, size_t most) {
+  return sizeof(T) == 4 ? gemm_f32_scratch(g, n, most) : 0;
 }
 
 template <bool AK, bool BKM, int WN>
@@ -1446,12 +1153,14 @@ hipError_t gemm_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t stream)
       return hipGetLastError();
     }
   }
-  const hipError_t r = gemm<T>(a0, stream);
-  return r != hipSuccess ? r : gemm<T>(a1, stream);
+  const hipError_t r = gemm<T>(&a0, 1, GemmScratch{}, stream);
+  return r != hipSuccess ? r : gemm<T>(&a1, 1, GemmScratch{}, stream);
 }
 
-template hipError_t gemm<float>(const GemmArgs&, hipStream_t);
-template hipError_t gemm<bf16_t>(const GemmArgs&, hipStream_t);
+template hipError_t gemm<float>(const GemmArgs*, int, const GemmScratch&, hipStream_t);
+template hipError_t gemm<bf16_t>(const GemmArgs*, int, const GemmScratch&, hipStream_t);
+template size_t gemm_scratch<float>(const GemmArgs*, int, size_t);
+template size_t gemm_scratch<bf16_t>(const GemmArgs*, int, size_t);
 template hipError_t gemm_pair<float>(const GemmArgs&, const GemmArgs&, hipStream_t);
 template hipError_t gemm_pair<bf16_t>(const GemmArgs&, const GemmArgs&, hipStream_t);
 template const char* gemm_check<float>(const GemmArgs&);

@@ -98,6 +98,8 @@ def lib():
         "fdh_testing_gemm": (i32, [i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, i32, C.c_float, i32, vp]),
         "fdh_testing_gemm_pair": (i32, [i32, i32, i32, i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp,
                                         vp, vp, C.c_float, i32, vp]),
+        "fdh_testing_gemm_channels": (i32, [i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, C.c_float, vp,
+                                            C.c_size_t, vp]),
         "fdh_testing_unfused_attention": (i32, [vp, i32]),
         "fdh_testing_unsplit_wgrad": (i32, [vp, i32]),
         "fdh_testing_timing": (i32, [vp, i32]),
@@ -474,6 +476,15 @@ def testing_gemm(dtype: str, M, N, K, batch, a_kmajor, b_kmajor, A, B, A2, B2, C
                                 _ptr(A2), _ptr(B2), _ptr(Cout), causal, float(alpha), int(tile), _stream())
     if st != OK:
         raise FdhError(st, "fdh_testing_gemm")
+
+
+def testing_gemm_channels(dtype: str, M, N, K, batch, a_kmajor, b_kmajor, A, B, A2, B2, C2, C1, alpha=1.0, scratch=None):
+    """C2 = alpha (A B^T + A2 B2^T) and C1 = alpha A B^T (None: not formed) as an HVP launches them (testing)."""
+    st = lib().fdh_testing_gemm_channels(DTYPE[dtype], M, N, K, batch, int(a_kmajor), int(b_kmajor), _ptr(A), _ptr(B),
+                                         _ptr(A2), _ptr(B2), _ptr(C2), _ptr(C1), float(alpha), _ptr(scratch),
+                                         0 if scratch is None else scratch.numel() * scratch.element_size(), _stream())
+    if st != OK:
+        raise FdhError(st, "fdh_testing_gemm_channels")
 
 
 def testing_gemm_pair(M0, N0, K0, M1, N1, K1, a_kmajor, b_kmajor, P0, P1, alpha=1.0, tile=6, batch0=1, batch1=1):
