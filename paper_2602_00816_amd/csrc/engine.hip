@@ -123,14 +123,16 @@ Engine::Engine(const fdh_model_config& c, hipStream_t s) : cfg(c), stream(s) {
   P = off;
 }
 
-// Number of K slices for a weight-gradient GEMM (M x N output, contraction
-// over the T tokens).  A grid of fewer than 128 output tiles leaves most of
-// the 256 compute units idle; slicing the token range multiplies the
-// workgroups, up to one full wave of 256.  Larger grids are not sliced: there
-// the extra prologues, epilogues and the summation pass cost more than the
-// better balance gains (measured on the 1.3B shapes).
+// 256 x 256 output tiles of a weight-gradient GEMM.  From 128 on its contraction
+// is not cut: the parts' sums cost more than the better balance gains (measured
+// on the 1.3B shapes).
+static int64_t wgrad_tiles(int M, int N) { return (int64_t)((M + 255) / 256) * ((N + 255) / 256); }
+
+// Token slices of a weight-gradient GEMM (M x N output, contraction over the T
+// tokens) whose order of summation is fixed (f32_chain): up to one full wave of
+// 256 tiles for a grid that leaves most compute units idle.
 static int wgrad_splits(int M, int N, int T_) {
-  const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+  const int64_t tiles = wgrad_tiles(M, N);
   if (tiles >= 128) return 1;
   int best = 1;
   for (int s : {2, 3, 4, 6, 8})
@@ -154,10 +156,9 @@ static bool f32_chain(int T_) { return T_ > 4096; }
 // of its last wave of 256 tiles (the 2048-wide layer: 192 + 64 tiles).  Its
 // tiles then cost no extra time, where on their own they would be cut into
 // token slices and summed.
-static bool pair_wgrads(int Mq, int Nq, int Mo, int No, int T_) {
-  const int64_t tq = (int64_t)((Mq + 255) / 256) * ((Nq + 255) / 256);
-  const int64_t to = (int64_t)((Mo + 255) / 256) * ((No + 255) / 256);
-  return wgrad_splits(Mq, Nq, T_) == 1 && tq % 256 != 0 && tq % 256 + to <= 256;
+static bool pair_wgrads(int Mq, int Nq, int Mo, int No) {
+  const int64_t tq = wgrad_tiles(Mq, Nq), to = wgrad_tiles(Mo, No);
+  return tq >= 128 && tq % 256 != 0 && tq % 256 + to <= 256;
 }
 
 // The MLP's two weight gradients (gate/up: Ma x Na, down: Mb x Nb) in one
@@ -170,9 +171,8 @@ static bool pair_wgrads(int Mq, int Nq, int Mo, int No, int T_) {
 // at 8192 tokens: 352 + 176 tiles take 3 units in two launches, 2.25 in one
 // with the down gradient in 4 slices.
 static int mlp_wgrad_split(int Ma, int Na, int Mb, int Nb, int T_) {
-  const int64_t ta = (int64_t)((Ma + 255) / 256) * ((Na + 255) / 256);
-  const int64_t tb = (int64_t)((Mb + 255) / 256) * ((Nb + 255) / 256);
-  if (wgrad_splits(Ma, Na, T_) != 1 || wgrad_splits(Mb, Nb, T_) != 1) return 0;
+  const int64_t ta = wgrad_tiles(Ma, Na), tb = wgrad_tiles(Mb, Nb);
+  if (ta < 128 || tb < 128) return 0;
   auto makespan = [&](int s) {
     std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
     for (int i = 0; i < 256; ++i) cu.push(0.0);
@@ -228,6 +228,7 @@ size_t Engine::linear_scratch(int T_) const {
           g[p].npairs = 2 - p;
         }
         const int n = kind == 2 ? 1 : 2;
+        if (kind == 2 && bf16 && wgrad_tiles(sh[0], sh[1]) >= 128) continue;
         mx = std::max(mx, bf16 ? gemm_scratch<bf16_t>(g, n, most) : gemm_scratch<float>(g, n, most));
       }
   return mx;
@@ -307,7 +308,7 @@ size_t Engine::plan(int B, int S, int m, const fdh_lanczos_opts* o, WsLayout* ou
       size_t mx = linear_scratch((int)T_);
       const int shapes[5][2] = {{qkvd, d}, {d, Hq * dh}, {nu, d}, {d, F}, {V, d}};
       for (const auto& sh : shapes) {
-        const int ns = bf16 || f32_chain((int)T_) ? wgrad_splits(sh[0], sh[1], (int)T_) : 1;
+        const int ns = !bf16 && f32_chain((int)T_) ? wgrad_splits(sh[0], sh[1], (int)T_) : 1;
         if (ns > 1) mx = std::max(mx, (size_t)ns * sh[0] * sh[1] * 4);
       }
       // the down projection's slices when the MLP weight gradients share a launch
@@ -668,11 +669,11 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
   };
   auto lin_wgrad = [&](const T* dYm, const T* dYd, int N, const T* Xm, const T* Xd, int K, const ParamRef& W) -> int {
     GemmArgs g = wgrad_args(dYm, dYd, N, Xm, Xd, K, W);
-    // (fp32 products are cut, where that pays, inside the launch)
-    const int ns = bf16 || chain ? wgrad_splits(N, K, T_) : 1;
+    // (cut, where that pays, inside the launch; chain products into token slices here)
+    const int ns = chain ? wgrad_splits(N, K, T_) : 1;
     if (ns == 1 || force_unsplit || wsplit.bytes < (size_t)ns * N * K * 4) {
       if (acc) g.beta = 1.f;
-      return run_gemm<T>(*this, &g, 1, chain, force_unsplit);
+      return run_gemm<T>(*this, &g, 1, chain, force_unsplit || (bf16 && wgrad_tiles(N, K) >= 128));
     }
     const int kc = T_ / ns;
     g.K = kc;
@@ -895,7 +896,7 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     // (paired with the q/k/v weight gradient below: gom, god and o stay intact
     // through the fused attention backward)
     const bool pair_o = std::is_same<T, bf16_t>::value && fused && !force_unsplit && !force_unpaired &&
-                        pair_wgrads(qkvd, d, d, Hq * dh, T_);
+                        pair_wgrads(qkvd, d, d, Hq * dh);
     if (!pair_o) RC(lin_wgrad(gom, god, d, OP(s.o_m), OP(s.o_d), Hq * dh, R.wo));
     RC(lin_dgrad(gom, god, d, R.wo, Hq * dh, OP(do_m), OP(do_d), OUT_OP));
     const T* qm = OP(s.qkv_m);

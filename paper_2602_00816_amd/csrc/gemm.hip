@@ -13,7 +13,9 @@
 // always single 16-byte LDS reads.  Global loads are 16-byte vectors,
 // prefetched into registers one K tile ahead.
 #include "gemm_dev.h"
+#include "gemm_split.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace fdh {
@@ -566,45 +568,51 @@ __global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_dma(GemmArgs a) {
 }
 
 // ===========================================================================
-// bf16 GEMM, 256 x 256 block tile, four wavefronts of 128 x 128 each (one per
-// SIMD; WN = 2), on the same DMA-fed LDS ring and LDS layouts as
-// gemm_bf16_dma.  With 128 x 128 per wavefront every fragment read from LDS
-// feeds four MFMAs instead of two or three, which halves LDS read traffic per
-// FLOP.  WN = 4 runs the same schedule on eight wavefronts of 128 x 64 (two
-// per SIMD, 220 registers), which trades LDS reads for a second wavefront to
-// hide latency and a shorter prologue and epilogue per tile.  A wavefront
-// keeps two fragment register sets and its instruction order is fixed by
-// scheduling barriers: a K slice is two half slices of 16 k; while the 16
-// MFMAs of one half run, the fragments of the next half are read.  The loads
-// of a slice are spread over two half slices, one load per two MFMAs: A's
-// into the stage freed at the ring barrier (three slices ahead), B's during
-// the next half slice (then two and a half slices ahead), which keeps the
-// load queue shorter than issuing all eight at once (measured 1.5-3% faster
-// on the 1.3B layer shapes, same bits).  Loads past the last slice reload the
-// last slice into the free stage (never read), so every slice issues the same
-// number of loads and the vmcnt waits are constants.
+// bf16 GEMM on the LDS layouts and four-stage ring of gemm_bf16_dma, with the
+// instruction order of a wavefront fixed by scheduling barriers.  A wavefront
+// keeps two fragment register sets: a K slice of 32 is two half slices of 16 k,
+// and while the matrix operations of one half run, the fragments of the next
+// half are read.  The loads of a slice are spread over two half slices, one
+// load per two fragments: A's into the stage freed at the ring barrier (three
+// slices ahead), B's during the next half slice (then two and a half slices
+// ahead), which keeps the load queue shorter than issuing all at once (measured
+// 1.5-3% faster on the 1.3B layer shapes, same bits).  Loads past the last slice
+// reload the last slice into the free stage (never read), so every slice issues
+// the same number of loads and the vmcnt waits are constants.  Operands are read
+// through buffer resources at the slice origin: lanes past the contraction's end
+// read out of range and get zeros, so K needs no multiple of 32.
+//   256 x 256, WN = 2: four wavefronts of 128 x 128 (one per SIMD): every
+//     fragment read feeds four matrix operations;
+//   256 x 256, WN = 4: eight of 128 x 64 (two per SIMD): twice the reads for a
+//     second wavefront to hide latency and a shorter prologue and epilogue;
+//   128 x 128, WN = 2: four of 64 x 64, two workgroups per CU: for outputs with
+//     few tiles, and for parts of split contractions (gemm_split.h).
 // ===========================================================================
-// One 256 x 256 output tile of the product a: tile lin of a gx x gy tile grid
-// (times a.nbatch).
-template <bool AK, bool BKM, int WN>
-__device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int lin) {
-  // WN = 2: four wavefronts of 128 x 128; WN = 4: eight of 128 x 64
-  constexpr int BM_ = 256, BN_ = 256, NW = 2 * WN, IM = 4, JN = 8 / WN, WTN = BN_ / WN;
+constexpr uint32_t OOB = 0x80000000u;   // byte offset at which the buffer resources end
+
+// Tile lin (of the product's tiles, batch entries and parts) of product prod.
+template <int BM_, int BN_, int WN, bool AK, bool BKM>
+__device__ __forceinline__ void ring_tile(const GemmJob& job, int prod, int lin) {
+  const GemmArgs& a = job.g[prod];
+  constexpr int NW = 2 * WN, WTM = BM_ / 2, WTN = BN_ / WN, IM = WTM / 32, JN = WTN / 32;
   constexpr int ASZ = BM_ * KT3, BSZ = BN_ * KT3;
   constexpr int NU = BM_ * KT3 * 2 / 1024 / NW;   // 1 KB loads per operand per wavefront per slice
   constexpr int PERT = 2 * NU;                    // loads per wavefront per slice
+  static_assert(BM_ == BN_, "one load count for both operands");
   __shared__ __attribute__((aligned(1024))) bf16_t st0[ASZ + BSZ];
   __shared__ __attribute__((aligned(1024))) bf16_t st1[ASZ + BSZ];
   __shared__ __attribute__((aligned(1024))) bf16_t st2[ASZ + BSZ];
   __shared__ __attribute__((aligned(1024))) bf16_t st3[ASZ + BSZ];
 
+  const int gx = (a.N + BN_ - 1) / BN_, gy = (a.M + BM_ - 1) / BM_;
   const int tiles = gx * gy;
-  const int z = lin / tiles;
+  const int part = lin / tiles;             // part * nbatch + batch entry
+  const int sp = part / a.nbatch, z = part % a.nbatch;
   const int tl = lin % tiles;
   // tiles run down GM tile rows before the next column (with the XCD
-  // renumbering, each XCD's 32 concurrent tiles then share 4 A and 8 B
-  // operand blocks); 4 measured 0.35% faster per HVP than 8 and 16 slower
-  constexpr int GM = 4;
+  // renumbering, each XCD's concurrent tiles then share 4 A and 8 B operand
+  // blocks of 256 rows); 4 measured 0.35% faster per HVP than 8 and 16 slower
+  constexpr int GM = BM_ == 256 ? 4 : 8;
   const int gsize = GM * gx;
   const int first_m = (tl / gsize) * GM;
   const int gm_rows = min(gy - first_m, GM);
@@ -620,34 +628,40 @@ __device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int l
   int kmin = 0, kmax = a.K;
   if (a.causal == CAUSAL_K_LE_M) kmax = min(a.K, m0 + BM_);
   if (a.causal == CAUSAL_K_GE_M) kmin = (min(m0, a.K) / KT3) * KT3;
-  const int nkt = (kmax > kmin) ? (kmax - kmin) / KT3 : 0;
-  const int total = nkt * a.npairs;
+  const int nkt = (kmax > kmin) ? (kmax - kmin + KT3 - 1) / KT3 : 0;
+  // this workgroup's slices of the pair-concatenated contraction
+  const int ts = sp * job.len, total = min(nkt * a.npairs, ts + job.len);
 
-  // per-lane source offsets (elements) of this wavefront's loads, both pairs
   const bf16_t* baseA[2];
   const bf16_t* baseB[2];
-  int64_t offA[2][NU], offB[2][NU], skA[2], skB[2];
 #pragma clang loop unroll(full)
   for (int p = 0; p < 2; ++p) {
-    const int pp = p < a.npairs ? p : 0;
-    const GemmOperand& A = a.A[pp];
-    const GemmOperand& B = a.B[pp];
-    baseA[p] = reinterpret_cast<const bf16_t*>(A.ptr) + batch_off(z, a.inner_count, A.s_outer, A.s_inner, A.inner_div);
-    baseB[p] = reinterpret_cast<const bf16_t*>(B.ptr) + batch_off(z, a.inner_count, B.s_outer, B.s_inner, B.inner_div);
-    skA[p] = AK ? 1 : A.s_k;
-    skB[p] = BKM ? 1 : B.s_k;
-#pragma clang loop unroll(full)
-    for (int u = 0; u < NU; ++u) {
-      const int q = wave + u * NW;
-      // K-major: 16 rows of 64 B per load; MN-major: 2 k-rows of 512 B per load
-      const int r = q * 16 + (lane >> 2), ck = (lane & 3) ^ ((r >> 2) & 3);
-      const int k = q * 2 + (lane >> 5), cm = (lane & 31) ^ (4 * (k & 3));
-      offA[p][u] = AK ? (int64_t)min(m0 + r, a.M - 1) * A.s_row + 8 * ck
-                      : (int64_t)k * A.s_k + min(m0 + 8 * cm, a.M - 8);
-      offB[p][u] = BKM ? (int64_t)min(n0 + r, a.N - 1) * B.s_row + 8 * ck
-                       : (int64_t)k * B.s_k + min(n0 + 8 * cm, a.N - 8);
-    }
+    const GemmOperand& A = a.A[p < a.npairs ? p : 0];
+    const GemmOperand& B = a.B[p < a.npairs ? p : 0];
+    baseA[p] = reinterpret_cast<const bf16_t*>(A.ptr) + batch_off(z, a.inner_count, A.s_outer, A.s_inner, A.inner_div) +
+               (AK ? (int64_t)m0 * A.s_row : (int64_t)m0);
+    baseB[p] = reinterpret_cast<const bf16_t*>(B.ptr) + batch_off(z, a.inner_count, B.s_outer, B.s_inner, B.inner_div) +
+               (BKM ? (int64_t)n0 * B.s_row : (int64_t)n0);
   }
+  // per-lane source byte offsets from the slice origin and the k of the lane's
+  // chunk (both pairs share them: equal strides, checked on the host)
+  uint32_t voA[NU], voB[NU];
+  int kqA[NU], kqB[NU];
+#pragma clang loop unroll(full)
+  for (int u = 0; u < NU; ++u) {
+    const int q = wave + u * NW;
+    // K-major: 16 rows of 64 B per load; MN-major: whole k-rows
+    const int r = q * 16 + (lane >> 2), ck = (lane & 3) ^ ((r >> 2) & 3);
+    constexpr int CPR = BM_ / 8, RPI = 64 / CPR;
+    const int k = q * RPI + lane / CPR, cm = (lane % CPR) ^ (4 * (k & 3));
+    kqA[u] = AK ? 8 * ck : k;
+    kqB[u] = BKM ? 8 * ck : k;
+    voA[u] = 2u * (uint32_t)(AK ? (int64_t)(min(m0 + r, a.M - 1) - m0) * a.A[0].s_row + 8 * ck
+                                : (int64_t)k * a.A[0].s_k + (min(m0 + 8 * cm, a.M - 8) - m0));
+    voB[u] = 2u * (uint32_t)(BKM ? (int64_t)(min(n0 + r, a.N - 1) - n0) * a.B[0].s_row + 8 * ck
+                                 : (int64_t)k * a.B[0].s_k + (min(n0 + 8 * cm, a.N - 8) - n0));
+  }
+  const int64_t skA = AK ? 1 : a.A[0].s_k, skB = BKM ? 1 : a.B[0].s_k;
 
   auto stage = [&](auto s) -> bf16_t* {
     constexpr int S = decltype(s)::value & 3;
@@ -656,24 +670,29 @@ __device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int l
     else if constexpr (S == 2) return st2;
     else return st3;
   };
-  // load u (0..2 NU-1) of slice t (clamped to the last slice) into stage st
-  auto dma = [&](bf16_t* st, int t, int u) {
+  struct Src {
+    i32x4_t rs;
+    int left;   // k's of the contraction from the slice origin on
+  };
+  // slice t (clamped to the last) of operand A or B
+  auto src = [&](bool isA, int t) {
     t = min(t, total - 1);
     const int p = t >= nkt ? 1 : 0;
-    const int64_t k0 = kmin + (t - p * nkt) * KT3;
-    const bool isA = u < NU;
-    const int uu = isA ? u : u - NU;
-    const int q = wave + uu * NW;
-    const bf16_t* g = isA ? (p ? baseA[1] + offA[1][uu] + k0 * skA[1] : baseA[0] + offA[0][uu] + k0 * skA[0])
-                          : (p ? baseB[1] + offB[1][uu] + k0 * skB[1] : baseB[0] + offB[0][uu] + k0 * skB[0]);
+    const int k0 = kmin + (t - p * nkt) * KT3;
+    const uint64_t b = (uint64_t)(uintptr_t)(isA ? (p ? baseA[1] : baseA[0]) + k0 * skA : (p ? baseB[1] : baseB[0]) + k0 * skB);
+    return Src{i32x4_t{(int)(uint32_t)b, (int)((b >> 32) & 0xffffu), (int)OOB, 0x00020000}, kmax - k0};
+  };
+  auto dma = [&](bool isA, const Src& s, bf16_t* st, int u) {
+    const int q = wave + u * NW;
+    const uint32_t vo = (isA ? kqA[u] : kqB[u]) < s.left ? (isA ? voA[u] : voB[u]) : OOB;
     // LDS byte address: stage base (a link-time constant) + wave-uniform offset
     const uint32_t ldsaddr = (uint32_t)(uintptr_t)(lds_void_t*)st + (uint32_t)(((isA ? 0 : ASZ) + q * 512) * 2);
     asm volatile(
         "s_mov_b32 m0, %0\n\t"
         "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, off"
+        "buffer_load_dwordx4 %1, %2, 0 offen lds"
         :
-        : "s"(ldsaddr), "v"(g)
+        : "s"(ldsaddr), "v"(vo), "s"(s.rs)
         : "memory", "m0");
   };
 
@@ -687,7 +706,7 @@ __device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int l
 
   bf16x8_t f0[IM + JN], f1[IM + JN];   // fragments of half slices (k 0..15, k 16..31)
   auto rd = [&](bf16x8_t& f, const bf16_t* st, int x, int kk) {
-    if (x < IM) f = frag<BM_, AK>(st, wm * 128 + x * 32, kk, lane);
+    if (x < IM) f = frag<BM_, AK>(st, wm * WTM + x * 32, kk, lane);
     else f = frag<BN_, BKM>(st + ASZ, wn * WTN + (x - IM) * 32, kk, lane);
   };
   auto mma = [&](const bf16x8_t (&f)[IM + JN], int e) {
@@ -699,18 +718,19 @@ __device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int l
     constexpr int S = decltype(s)::value;
     const bf16_t* cur = stage(s);
     bf16_t* fill2 = stage(std::integral_constant<int, S + 2>{});
+    const Src sb = src(false, t + 2);
     // half slice 0 on f0 (read during the previous slice); read half 1 into
     // f1; issue B's loads of slice t + 2 into the stage freed at the previous
     // barrier (A's went out during the previous half slice)
 #pragma clang loop unroll(full)
     for (int x = 0; x < IM + JN; ++x) {
       rd(f1[x], cur, x, 16);
-      if ((x & 1) && x / 2 < NU) dma(fill2, t + 2, NU + x / 2);
+      if ((x & 1) && x / 2 < NU) dma(false, sb, fill2, x / 2);
 #pragma clang loop unroll(full)
       for (int e = x * IM * JN / (IM + JN); e < (x + 1) * IM * JN / (IM + JN); ++e) mma(f0, e);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // own loads of slice t + 1 done (the 8 issued since are slice t + 2's),
+    // own loads of slice t + 1 done (the PERT issued since are slice t + 2's),
     // then everyone's; stage S - 1 is free
     wait_vm<PERT>();
     __builtin_amdgcn_s_barrier();
@@ -718,10 +738,11 @@ __device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int l
     __builtin_amdgcn_sched_barrier(0);
     bf16_t* nxt_fill = stage(std::integral_constant<int, S + 3>{});
     const bf16_t* nxt = stage(std::integral_constant<int, S + 1>{});
+    const Src sa = src(true, t + 3);
     // half slice 1 on f1; A's loads of slice t + 3 into stage S - 1; read half 0 of slice t + 1 into f0
 #pragma clang loop unroll(full)
     for (int x = 0; x < IM + JN; ++x) {
-      if ((x & 1) && x / 2 < NU) dma(nxt_fill, t + 3, x / 2);
+      if ((x & 1) && x / 2 < NU) dma(true, sa, nxt_fill, x / 2);
       rd(f0[x], nxt, x, 0);
 #pragma clang loop unroll(full)
       for (int e = x * IM * JN / (IM + JN); e < (x + 1) * IM * JN / (IM + JN); ++e) mma(f1, e);
@@ -729,20 +750,24 @@ __device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int l
     }
   };
 
-  if (total > 0) {
-    // slices 0 and 1, and A's loads of slice 2 (B's go out in the first step)
+  if (ts < total) {
+    // the part's slices 0 and 1, and A's loads of slice 2 (B's go out in the first step)
+    for (int h = 0; h < 2; ++h) {
+      const Src sa = src(true, ts + h), sb = src(false, ts + h);
 #pragma clang loop unroll(full)
-    for (int u = 0; u < 2 * NU; ++u) dma(st0, 0, u);
+      for (int u = 0; u < NU; ++u) dma(true, sa, h ? st1 : st0, u);
 #pragma clang loop unroll(full)
-    for (int u = 0; u < 2 * NU; ++u) dma(st1, 1, u);
+      for (int u = 0; u < NU; ++u) dma(false, sb, h ? st1 : st0, u);
+    }
+    const Src s2 = src(true, ts + 2);
 #pragma clang loop unroll(full)
-    for (int u = 0; u < NU; ++u) dma(st2, 2, u);
+    for (int u = 0; u < NU; ++u) dma(true, s2, st2, u);
     wait_vm<PERT + NU>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma clang loop unroll(full)
     for (int x = 0; x < IM + JN; ++x) rd(f0[x], st0, x, 0);
-    for (int t0 = 0; t0 < total; t0 += NS3) {
+    for (int t0 = ts; t0 < total; t0 += NS3) {
       step(std::integral_constant<int, 0>{}, t0);
       if (t0 + 1 < total) step(std::integral_constant<int, 1>{}, t0 + 1);
       if (t0 + 2 < total) step(std::integral_constant<int, 2>{}, t0 + 2);
@@ -751,47 +776,45 @@ __device__ __forceinline__ void w4_tile(const GemmArgs& a, int gx, int gy, int l
     wait_vm<0>();   // no load may land in LDS after the workgroup ends
   }
 
+  if (job.splits[prod] > 1) {
+#pragma clang loop unroll(full)
+    for (int i = 0; i < IM; ++i)
+#pragma clang loop unroll(full)
+      for (int j = 0; j < JN; ++j)
+        store_partial(job, prod, acc[i][j], part, m0 + wm * WTM + i * 32, n0 + wn * WTN + j * 32, lane);
+    return;
+  }
   const int64_t coff = batch_off(z, a.inner_count, a.c_outer, a.c_inner, a.c_div);
   // stage the output through the ring once every wavefront is done with it:
-  // four wavefronts: wavefront w uses stage w (4 x 32 x 36 floats = 18 KB of
-  // its 32 KB); eight: wavefronts 2s and 2s + 1 share stage s, 2 blocks each
+  // four wavefronts: wavefront w uses stage w (JN x 32 x 36 floats); eight:
+  // wavefronts 2s and 2s + 1 share stage s, 2 blocks each
   __syncthreads();
-  if constexpr (WN == 2) {
-    float* stg = reinterpret_cast<float*>(wave == 0 ? st0 : wave == 1 ? st1 : wave == 2 ? st2 : st3);
-    const int cbs[4] = {n0 + wn * 128, n0 + wn * 128 + 32, n0 + wn * 128 + 64, n0 + wn * 128 + 96};
+  float* stg;
+  if constexpr (WN == 2) stg = reinterpret_cast<float*>(wave == 0 ? st0 : wave == 1 ? st1 : wave == 2 ? st2 : st3);
+  else stg = reinterpret_cast<float*>(wave < 2 ? st0 : wave < 4 ? st1 : wave < 6 ? st2 : st3) + (wave & 1) * 2 * STG_FLOATS;
+  static_assert((WN == 2 ? JN : 4) * STG_FLOATS * 4 <= (ASZ + BSZ) * 2, "staging areas exceed a ring stage");
+  int cbs[JN];
 #pragma clang loop unroll(full)
-    for (int i = 0; i < IM; ++i)
-      store_blocks_lds<bf16_t, 4>(a, acc[i], coff, m0 + wm * 128 + i * 32, cbs, lane, stg);
-  } else {
-    float* stg = reinterpret_cast<float*>(wave < 2 ? st0 : wave < 4 ? st1 : wave < 6 ? st2 : st3) +
-                 (wave & 1) * 2 * STG_FLOATS;
-    const int cbs[2] = {n0 + wn * WTN, n0 + wn * WTN + 32};
+  for (int j = 0; j < JN; ++j) cbs[j] = n0 + wn * WTN + j * 32;
 #pragma clang loop unroll(full)
-    for (int i = 0; i < IM; ++i)
-      store_blocks_lds<bf16_t, 2>(a, acc[i], coff, m0 + wm * 128 + i * 32, cbs, lane, stg);
-  }
+  for (int i = 0; i < IM; ++i)
+    store_blocks_lds<bf16_t, JN>(a, acc[i], coff, m0 + wm * WTM + i * 32, cbs, lane, stg);
 }
 
-template <bool AK, bool BKM, int WN = 2>
-__global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_w4(GemmArgs a) {
-  const int gx = gridDim.x, gy = gridDim.y;
-  w4_tile<AK, BKM, WN>(a, gx, gy, xcd_order(blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z), gx * gy * gridDim.z));
-}
-
-// Two independent products in one grid (one-dimensional, the n0 tiles of a0,
-// batch entries included, then those of a1): the tiles of a1 take the compute
-// units that a grid of a0 alone would leave idle in its last wave.  Each product is renumbered on
-// its own, so that every XCD takes an eighth of each (renumbering the joint
-// grid would give a0 to some XCDs and a1 to the others).
-template <bool AK, bool BKM, int WN = 2>
-__global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_w4_pair(GemmArgs a0, GemmArgs a1, int n0) {
+// The tiles of product 0 (all parts and batch entries), then those of product
+// 1: the second takes the compute units that the first alone would leave idle
+// in its last wave.  Each product is renumbered for the XCDs on its own, so
+// that every XCD takes an eighth of each (renumbering the joint grid would give
+// product 0 to some XCDs and product 1 to the others).
+template <int BM_, int BN_, int WN, bool AK, bool BKM>
+__global__ __launch_bounds__(128 * WN) void gemm_bf16_ring(GemmJob job) {
   const int b = blockIdx.x;
-  if (b < n0) w4_tile<AK, BKM, WN>(a0, (a0.N + 255) / 256, (a0.M + 255) / 256, xcd_order(b, n0));
-  else w4_tile<AK, BKM, WN>(a1, (a1.N + 255) / 256, (a1.M + 255) / 256, xcd_order(b - n0, gridDim.x - n0));
+  const int prod = b >= job.nblk0 ? 1 : 0;
+  ring_tile<BM_, BN_, WN, AK, BKM>(job, prod, prod ? xcd_order(b - job.nblk0, gridDim.x - job.nblk0) : xcd_order(b, job.nblk0));
 }
 
 // ===========================================================================
-// As gemm_bf16_w4 with K slices of 64 in a two-stage ring (2 x 64 KB).  A
+// As the four-wavefront ring kernel with K slices of 64 in a two-stage ring (2 x 64 KB).  A
 // K-major row of a slice is one whole 128-byte line, so each DMA load moves 8
 // full lines (half as many L1/L2 requests per byte as 64-byte row pieces),
 // and there is one barrier per 64 k.  A slice is four half slices of 16 k
@@ -989,18 +1012,23 @@ void launch_w4k64(const GemmArgs& a, hipStream_t stream) {
   else launch_w4k64_t<false, false>(a, stream);
 }
 
-template <bool AK, bool BKM, int WN>
-void launch_w4_t(const GemmArgs& a, hipStream_t stream) {
-  dim3 grid(ceil_div(a.N, 256), ceil_div(a.M, 256), a.nbatch);
-  hipLaunchKernelGGL((gemm_bf16_w4<AK, BKM, WN>), grid, dim3(128 * WN), 0, stream, a);
+template <int BM_, int WN, bool AK, bool BKM>
+void launch_ring_t(const GemmJob& j, int blocks, hipStream_t stream) {
+  hipLaunchKernelGGL((gemm_bf16_ring<BM_, BM_, WN, AK, BKM>), dim3(blocks), dim3(128 * WN), 0, stream, j);
 }
-template <int WN>
-void launch_w4(const GemmArgs& a, hipStream_t stream) {
-  const bool ak = a.A[0].s_k == 1, bk = a.B[0].s_k == 1;
-  if (ak && bk) launch_w4_t<true, true, WN>(a, stream);
-  else if (ak && !bk) launch_w4_t<true, false, WN>(a, stream);
-  else if (!ak && bk) launch_w4_t<false, true, WN>(a, stream);
-  else launch_w4_t<false, false, WN>(a, stream);
+template <int BM_, int WN>
+void launch_ring(const GemmJob& j, int blocks, hipStream_t stream) {
+  const bool ak = j.g[0].A[0].s_k == 1, bk = j.g[0].B[0].s_k == 1;
+  if (ak && bk) launch_ring_t<BM_, WN, true, true>(j, blocks, stream);
+  else if (ak && !bk) launch_ring_t<BM_, WN, true, false>(j, blocks, stream);
+  else if (!ak && bk) launch_ring_t<BM_, WN, false, true>(j, blocks, stream);
+  else launch_ring_t<BM_, WN, false, false>(j, blocks, stream);
+}
+hipError_t launch_ring(int tile, const GemmJob& j, int blocks, hipStream_t stream) {
+  if (tile == 6) launch_ring<256, 2>(j, blocks, stream);
+  else if (tile == 8) launch_ring<256, 4>(j, blocks, stream);
+  else launch_ring<128, 2>(j, blocks, stream);
+  return hipGetLastError();
 }
 
 template <int BN_, int WN>
@@ -1058,47 +1086,48 @@ const char* gemm_check(const GemmArgs& a) {
     }
   }
   if (a.causal == CAUSAL_SKIP_UPPER && a.M > a.N) return "gemm: causal skip needs M <= N";
-  if (a.tile < 0 || a.tile > 8) return "gemm: bad tile";
+  if (a.tile < 0 || a.tile > 9) return "gemm: bad tile";
   if (a.tile >= 4 && (a.K % 32 || a.M < 8 || a.N < 8)) return "gemm: the DMA kernel needs K % 32 == 0";
   if (a.tile == 7 && a.K % 64) return "gemm: the 64-deep kernels need K % 64 == 0";
-  if ((a.tile == 7 || sizeof(T) == 4) && a.npairs == 2 &&
+  if (a.npairs == 2 &&
       (a.A[1].s_row != a.A[0].s_row || a.A[1].s_k != a.A[0].s_k || a.B[1].s_row != a.B[0].s_row ||
        a.B[1].s_k != a.B[0].s_k))
-    return "gemm: this kernel needs equal operand strides in both pairs";
+    return "gemm: both pairs need equal operand strides";
   return nullptr;
 }
 
-// The bf16 kernel a product runs on (the tile values of GemmArgs::tile).
-static int bf16_tile(const GemmArgs& a) {
-  int tile = a.tile;
-  if (tile == 0 && a.M >= 256) {
-    const int64_t t256 = (int64_t)ceil_div(a.M, 256) * ceil_div(a.N, 256) * a.nbatch;
-    const int64_t t128 = (int64_t)ceil_div(a.M, 256) * ceil_div(a.N, 128) * a.nbatch;
-    const bool dma = a.K % KT3 == 0;
-    // 256 x 256 tiles once there are more than 128 of them; with fewer,
-    // 256 x 128 tiles keep more of the 256 CUs busy.  Contractions up to
-    // 4096 deep (the forward projections and the input gradients of
-    // 2048-wide layers) run on eight wavefronts of 128 x 64, two per SIMD,
-    // whose tiles spend less of their time in the prologue and the staged
-    // epilogue; longer ones (the weight gradients, the input gradients of the
-    // MLP and q/k/v) on four wavefronts of 128 x 128 (measured on the 1.3B
-    // layer shapes, one and two operand pairs).
-    if (a.N > 128 && t256 > 128) tile = dma ? (a.K <= 4096 ? 8 : 6) : 2;
-    else if (t128 >= 64) tile = dma ? 5 : 3;
-  }
-  return tile;
-}
+// Costs of the ring kernels, measured on 256 and 1024 tiles with K = 2048 to
+// 11264 (busy) and on 16 and 64 of them (alone).
+static const GemmCost RING256{256, 256, KT3, 0.83, 0.52, 15.0, 1, 0}, RING128{128, 128, KT3, 0.30, 0.26, 7.0, 2, 0};
 
-static hipError_t gemm_one(const GemmArgs& a, hipStream_t stream) {
+// The ring kernel that n products share (as tile number), with its plan.
+// 256 x 256 tiles run on eight wavefronts: four of 128 x 128 (tile 6) are 1%
+// faster on K-major A with MN-major B at K = 11264, 1-4% slower on the weight
+// gradients and 2-5% slower at K = 2048, two operand pairs.
+static int bf16_plan(const GemmArgs* g, int n, size_t scratch, GemmPlan& pl) {
+  pl = plan_splits(g, n, RING128, scratch);
+  if (g[0].M <= 128 || g[0].N <= 128) return 9;
+  const GemmPlan big = plan_splits(g, n, RING256, scratch);
+  if (pl.us < big.us) return 9;
+  pl = big;
+  return 8;
+}
+static const GemmCost& ring_cost(int tile) { return tile == 9 ? RING128 : RING256; }
+
+// the kernel that GemmArgs::tile names (tests)
+static hipError_t gemm_tile(const GemmArgs& a, hipStream_t stream) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
-  const int tile = bf16_tile(a);
+  const int tile = a.tile;
   if (tile == 2) { launch_big<256, 256, 2, 4>(a, stream); return hipGetLastError(); }
   if (tile == 3) { launch_big<256, 128, 2, 2>(a, stream); return hipGetLastError(); }
   if (tile == 4) { launch_dma<256, 4>(a, stream); return hipGetLastError(); }
   if (tile == 5) { launch_dma<128, 2>(a, stream); return hipGetLastError(); }
-  if (tile == 6) { launch_w4<2>(a, stream); return hipGetLastError(); }
-  if (tile == 8) { launch_w4<4>(a, stream); return hipGetLastError(); }
   if (tile == 7) { launch_w4k64(a, stream); return hipGetLastError(); }
+  if (tile == 6 || tile >= 8) {
+    GemmJob j;
+    const GemmCost& c = ring_cost(tile);
+    return launch_ring(tile, j, make_job(j, &a, 1, plan_splits(&a, 1, c, 0), c, nullptr), stream);
+  }
   dim3 grid(ceil_div(a.N, BN), ceil_div(a.M, BM), a.nbatch);
   const bool ak = a.A[0].s_k == 1, bk = a.B[0].s_k == 1;
   if (ak && bk) hipLaunchKernelGGL((gemm_kernel<true, true>), grid, dim3(NT), 0, stream, a);
@@ -1111,46 +1140,45 @@ static hipError_t gemm_one(const GemmArgs& a, hipStream_t stream) {
 template <typename T>
 hipError_t gemm(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t stream) {
   if constexpr (sizeof(T) == 4) return gemm_f32(g, n, ws, stream);
-  for (int p = 0; p < n; ++p) {
-    const hipError_t r = gemm_one(g[p], stream);
-    if (r != hipSuccess) return r;
+  if (g[0].tile != 0) {
+    for (int p = 0; p < n; ++p) {
+      const hipError_t r = gemm_tile(g[p], stream);
+      if (r != hipSuccess) return r;
+    }
+    return hipSuccess;
   }
-  return hipSuccess;
+  if (g[0].M == 0 || g[0].N == 0) return hipSuccess;
+  GemmPlan pl;
+  const int tile = bf16_plan(g, n, ws.bytes, pl);
+  GemmJob j;
+  const int blocks = make_job(j, g, n, pl, ring_cost(tile), ws.p);
+  const hipError_t r = launch_ring(tile, j, blocks, stream);
+  return r != hipSuccess ? r : reduce_splits<bf16_t>(j, n, stream);
 }
 
 template <typename T>
 size_t gemm_scratch(const GemmArgs* g, int n, size_t most) {
-  return sizeof(T) == 4 ? gemm_f32_scratch(g, n, most) : 0;
-}
-
-template <bool AK, bool BKM, int WN>
-static void launch_w4_pair_t(const GemmArgs& a0, const GemmArgs& a1, int n0, int n1, hipStream_t stream) {
-  hipLaunchKernelGGL((gemm_bf16_w4_pair<AK, BKM, WN>), dim3(n0 + n1), dim3(128 * WN), 0, stream, a0, a1, n0);
-}
-template <int WN>
-static void launch_w4_pair(const GemmArgs& a0, const GemmArgs& a1, int n0, int n1, hipStream_t stream) {
-  const bool ak = a0.A[0].s_k == 1, bk = a0.B[0].s_k == 1;
-  if (ak && bk) launch_w4_pair_t<true, true, WN>(a0, a1, n0, n1, stream);
-  else if (ak && !bk) launch_w4_pair_t<true, false, WN>(a0, a1, n0, n1, stream);
-  else if (!ak && bk) launch_w4_pair_t<false, true, WN>(a0, a1, n0, n1, stream);
-  else launch_w4_pair_t<false, false, WN>(a0, a1, n0, n1, stream);
+  if (sizeof(T) == 4) return gemm_f32_scratch(g, n, most);
+  GemmPlan pl;
+  bf16_plan(g, n, most, pl);
+  return pl.bytes;
 }
 
 template <typename T>
 hipError_t gemm_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t stream) {
   if constexpr (sizeof(T) == 2) {
-    GemmArgs b = a1;
-    b.tile = bf16_tile(a0);
-    const bool one = (b.tile == 6 || b.tile == 8) && a0.M > 0 && a0.N > 0 && a1.M > 0 && a1.N > 0 &&
+    GemmPlan pl;
+    const int tile = a0.tile ? a0.tile : bf16_plan(&a0, 1, 0, pl);
+    const bool one = (tile == 6 || tile == 8) && a0.M >= 8 && a0.N >= 8 && a1.M >= 8 && a1.N >= 8 &&
                      a0.causal == CAUSAL_NONE && a1.causal == CAUSAL_NONE &&
-                     (a0.A[0].s_k == 1) == (a1.A[0].s_k == 1) && (a0.B[0].s_k == 1) == (a1.B[0].s_k == 1) &&
-                     gemm_check<T>(b) == nullptr;
+                     (a0.A[0].s_k == 1) == (a1.A[0].s_k == 1) && (a0.B[0].s_k == 1) == (a1.B[0].s_k == 1);
     if (one) {
-      const int n0 = (int)(ceil_div(a0.M, 256) * ceil_div(a0.N, 256)) * a0.nbatch;
-      const int n1 = (int)(ceil_div(a1.M, 256) * ceil_div(a1.N, 256)) * a1.nbatch;
-      if (b.tile == 6) launch_w4_pair<2>(a0, b, n0, n1, stream);
-      else launch_w4_pair<4>(a0, b, n0, n1, stream);
-      return hipGetLastError();
+      GemmJob j;
+      j.g[0] = a0;
+      j.g[1] = a1;
+      j.nblk0 = (int)(ceil_div(a0.M, 256) * ceil_div(a0.N, 256)) * a0.nbatch;
+      j.len = 2 * std::max(ceil_div(a0.K, KT3), ceil_div(a1.K, KT3));
+      return launch_ring(tile, j, j.nblk0 + (int)(ceil_div(a1.M, 256) * ceil_div(a1.N, 256)) * a1.nbatch, stream);
     }
   }
   const hipError_t r = gemm<T>(&a0, 1, GemmScratch{}, stream);

@@ -1,5 +1,6 @@
 // Planning and summation of split contractions (gemm_split.h).
 #include <algorithm>
+#include <cmath>
 
 #include "gemm_dev.h"
 #include "gemm_split.h"
@@ -27,13 +28,13 @@ GemmPlan plan_splits(const GemmArgs* g, int n, const GemmCost& c, size_t scratch
     cut = cut && g[p].causal == CAUSAL_NONE && g[p].N % 4 == 0 && g[p].ldc % 4 == 0 && g[p].c_outer % 4 == 0 &&
           g[p].c_inner % 4 == 0 && (uintptr_t)g[p].C % ob == 0 && (uintptr_t)g[p].resid % 16 == 0;
   }
+  // a CU with one workgroup runs it at the lone rate, one with several (or a
+  // full chip) at the busy rate
+  const double whole_chip = 256.0 * c.per_cu;
   auto rounds_us = [&](int64_t wgs, int len) {
-    const int64_t full = wgs / 256, rest = wgs % 256;
-    // a CU with one workgroup runs it at the lone rate, one with several at the busy rate
-    double t = 0.0;
-    if (full == 0 || (full == 1 && rest == 0) || c.per_cu == 1) t = (double)(full + (rest ? 1 : 0)) * len * c.alone;
-    else t = (double)(full + (rest ? 1 : 0)) * len * c.slice;
-    return t + c.fixed * (double)((wgs + 256 * c.per_cu - 1) / (256 * c.per_cu));
+    const double busy = std::min(1.0, std::max(0.0, (double)wgs / whole_chip));
+    const double slice = c.per_cu == 1 ? c.alone + (c.slice - c.alone) * busy : wgs <= 256 ? c.alone : c.slice;
+    return (double)((wgs + 255) / 256) * len * slice + c.fixed * std::ceil((double)wgs / whole_chip);
   };
   GemmPlan best;
   best.BN = c.BN;

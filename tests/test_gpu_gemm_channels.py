@@ -14,22 +14,27 @@ pytestmark = pytest.mark.gpu
 
 # (M, N, K, batch): tile edges and remainders in every dimension, one tile, long
 # contractions over few tiles, the shapes of the small workloads
-SHAPES = [(4, 4, 4, 1), (128, 128, 32, 1), (132, 68, 36, 2), (64, 64, 200, 3), (256, 512, 1024, 1), (1200, 512, 2816, 1),
-          (520, 192, 1000, 1), (96, 4096, 1200, 1), (16, 24, 4096, 1)]
+# (fp32 operands need multiples of 4, bf16 ones of 8)
+SHAPES = [(4, 4, 4, 1), (8, 8, 8, 1), (128, 128, 32, 1), (136, 72, 40, 2), (64, 64, 200, 3), (256, 512, 1024, 1),
+          (1200, 512, 2816, 1), (520, 192, 1000, 1), (96, 4096, 1200, 1), (16, 24, 4096, 1), (2056, 2312, 264, 1)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
 @pytest.mark.parametrize("ak,bk", [(1, 1), (1, 0), (0, 0), (0, 1)])
-@pytest.mark.parametrize("dtype", ["f32"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_channel_products(dtype, ak, bk, shape):
     torch = need_gpu()
     from paper_2602_00816_amd import fdhvp as fd
     M, N, K, batch = shape
+    if dtype == "bf16" and (M % 8 or N % 8 or K % 8):
+        pytest.skip("bf16 operands come in 16-byte vectors of 8")
     say(f"gemm channels {dtype} {shape} layouts {ak}{bk}")
     rng = np.random.default_rng(M + 3 * N + 7 * K)
     # magnitudes over several decades, so that no operand's low bits are idle
     ops = [(rng.standard_normal((batch, r, K)) * 10.0 ** rng.integers(-3, 3, (batch, r, 1))).astype(np.float32)
            for r in (M, N, M, N)]
+    if dtype == "bf16":
+        ops = [torch.from_numpy(x).to(torch.bfloat16).float().numpy() for x in ops]
     A, B, A2, B2 = ops
     one = A.astype(np.float64) @ B.astype(np.float64).transpose(0, 2, 1)
     two = one + A2.astype(np.float64) @ B2.astype(np.float64).transpose(0, 2, 1)
@@ -37,7 +42,8 @@ def test_channel_products(dtype, ak, bk, shape):
     mag2 = mag1 + np.abs(A2).astype(np.float64) @ np.abs(B2).astype(np.float64).transpose(0, 2, 1)
 
     def up(x, kmajor):
-        return torch.from_numpy(np.ascontiguousarray(x if kmajor else x.transpose(0, 2, 1))).cuda()
+        return torch.from_numpy(np.ascontiguousarray(x if kmajor else x.transpose(0, 2, 1))).cuda().to(
+            torch.bfloat16 if dtype == "bf16" else torch.float32)
 
     dA, dB, dA2, dB2 = up(A, ak), up(B, bk), up(A2, ak), up(B2, bk)
     for nbytes in (0, 64 << 20):
@@ -45,7 +51,7 @@ def test_channel_products(dtype, ak, bk, shape):
         C2 = torch.full((batch, M, N), float("nan"), device="cuda")
         C1 = torch.full_like(C2, float("nan"))
         fd.testing_gemm_channels(dtype, M, N, K, batch, ak, bk, dA, dB, dA2, dB2, C2, C1, 0.5, scratch)
-        bar = 6 * (K / 16 + 2) * 2.0 ** -24
+        bar = (6 if dtype == "f32" else 1) * (K / 16 + 2) * 2.0 ** -24
         e1 = (np.abs(2 * C1.cpu().numpy().astype(np.float64) - one) / mag1).max()
         e2 = (np.abs(2 * C2.cpu().numpy().astype(np.float64) - two) / mag2).max()
         rms = np.linalg.norm(2 * C2.cpu().numpy().astype(np.float64) - two) / np.linalg.norm(two)
