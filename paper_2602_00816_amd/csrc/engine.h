@@ -69,8 +69,8 @@ struct WsLayout {
   };
   std::vector<LayerSpans> ls;
   Span xL_m, xL_d, f_m, f_d, lo, sc_m, sc_d, log_m, log_d, dlog_m, dlog_d, rowloss, losses;
-  Span dx0_m, dx0_d, dx1_m, dx1_d, dxo_m, dxo_d, dz_m, dz_d, dgu_m, dgu_d, dudf, db_m, db_d, gpart, do_m, do_d, dS_m, dS_d;
-  Span dqkv_m, dqkv_d, dqkvo_m, dqkvo_d, gqa_m, gqa_d, dl, da_m, da_d, colpart, keys, rope, cdf, gpartial, bpart, bout;
+  Span dx0_m, dx0_d, dx1_m, dx1_d, dxo_m, dxo_d, dz_m, dz_d, dgu_m, dgu_d, db_m, db_d, gpart, do_m, do_d, dS_m, dS_d;
+  Span dqkv_m, dqkv_d, dqkvo_m, dqkvo_d, gqa_m, gqa_d, dl, da_m, da_d, keys, rope, cdf, gpartial, bpart, bout;
   Span tcount;  // two int64 counters of fdh_bind_dataset
   Span nfflag;  // non-finite flags of the input direction and the product (two int32)
   Span wsplit;  // split-K partial products of the weight-gradient GEMMs
@@ -78,7 +78,7 @@ struct WsLayout {
   int64_t lz_ldq = 0;   // basis row stride (elements, multiple of 8)
   int lz_dev_rows = 0;  // basis rows held in the workspace
   // attention path: fused kernels (bf16, head dim 64 or 128, S a multiple of
-  // 128) or score/probability matrices in the workspace
+  // 8) or score/probability matrices in the workspace
   bool fused = false;
   // activation recomputation: only each layer's input pair x_in is kept; the
   // other spans of every layer alias one shared set, which the backward refills

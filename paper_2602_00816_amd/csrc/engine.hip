@@ -140,6 +140,9 @@ static int wgrad_splits(int M, int N, int T_) {
   return best;
 }
 
+// most rows of column sums that the bias kernels write for up to `rows` tokens
+static size_t bias_rows(size_t rows, int cols) { return std::min(rows, (size_t)std::max(1, 1024 / ((cols + 1023) / 1024))); }
+
 // fp32 batches of more than 4096 tokens keep the fp32 matrix instructions and
 // their order of summation.  The split products are faster there too (27.7
 // against 37.6 ms for the 23M-parameter GPT-2's product on 16 x 512 tokens) and
@@ -293,9 +296,14 @@ size_t Engine::plan(int B, int S, int m, const fdh_lanczos_opts* o, WsLayout* ou
     take(W.dxo_m, td * ob); take(W.dxo_d, td * ob);
     take(W.dz_m, tz * 4); take(W.dz_d, tz * 4);
     take(W.dgu_m, tu * ob); take(W.dgu_d, tu * ob);
-    take(W.dudf, gpt2 ? tz * 4 : 0);
     take(W.db_m, td * 4); take(W.db_d, td * 4);
-    take(W.gpart, std::max(td * 4, (size_t)2 * norm_bwd_groups((int)T_) * d * 8));
+    // column-sum rows of the norms (fewer than 2048 groups for any batch) and of the biases (at most 1024 rows)
+    {
+      const size_t rows_n = std::min<size_t>(T_, 2048), rows_b = std::min<size_t>(T_, 1024);
+      size_t by = 3 * rows_n * d * 8;
+      if (gpt2) by = std::max(by, std::max((size_t)bias_rows(rows_b, F) * F, (size_t)bias_rows(rows_b, qkvd) * qkvd) * 8);
+      take(W.gpart, by);
+    }
     take(W.do_m, ta * ob); take(W.do_d, ta * ob);
     take(W.dS_m, pp * ob); take(W.dS_d, pp * ob);
     take(W.dqkv_m, tq * 4); take(W.dqkv_d, tq * 4);
@@ -316,8 +324,6 @@ size_t Engine::plan(int B, int S, int m, const fdh_lanczos_opts* o, WsLayout* ou
       if (nm > 1) mx = std::max(mx, (size_t)nm * d * F * 4);
       take(W.wsplit, mx);
     }
-    const size_t maxc = std::max<size_t>({(size_t)qkvd, (size_t)F, (size_t)d, (size_t)1});
-    take(W.colpart, 64 * maxc * 8);
     take(W.keys, T_ * 4);
     take(W.rope, (size_t)Smax * dh * 8);
     take(W.cdf, (size_t)V * 8);
@@ -395,9 +401,9 @@ uint64_t Engine::layout_digest() const {
                           &s.o_d, &s.xmid_m, &s.xmid_d, &s.b_m, &s.b_d, &s.u_m, &s.u_d, &s.z_m, &s.z_d})
       sp(*x);
   for (const Span* x : {&xL_m, &xL_d, &f_m, &f_d, &lo, &sc_m, &sc_d, &log_m, &log_d, &dlog_m, &dlog_d, &rowloss,
-                        &losses, &dx0_m, &dx0_d, &dx1_m, &dx1_d, &dxo_m, &dxo_d, &dz_m, &dz_d, &dgu_m, &dgu_d, &dudf,
+                        &losses, &dx0_m, &dx0_d, &dx1_m, &dx1_d, &dxo_m, &dxo_d, &dz_m, &dz_d, &dgu_m, &dgu_d,
                         &db_m, &db_d, &gpart, &do_m, &do_d, &dS_m, &dS_d, &dqkv_m, &dqkv_d, &dqkvo_m, &dqkvo_d, &gqa_m,
-                        &gqa_d, &dl, &da_m, &da_d, &colpart, &keys, &rope, &cdf, &gpartial, &bpart, &bout, &tcount,
+                        &gqa_d, &dl, &da_m, &da_d, &keys, &rope, &cdf, &gpartial, &bpart, &bout, &tcount,
                         &nfflag, &wsplit, &lz_w, &lz_q, &lz_qp, &lz_basis, &lz_alpha, &lz_beta, &lz_coef, &lz_gram,
                         &lz_partial, &lz_flag, &lz_maxabs})
     sp(*x);
@@ -691,25 +697,30 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     if (timing.on) CK(timing.end(st, 0, e0, 0.0, 0.0));
     return FDH_OK;
   };
-  auto colsum_hv = [&](const float* X, int C, int64_t ld, const ParamRef& R) -> int {
-    CK(launch_colsum(hv + R.off, X, T_, C, ld, 1.0 / eps, acc, (double*)(ws + colpart.off), st));
+  bool op_ready = false;  // dxo holds the operand-type copy of the last norm backward's output
+  double* part = (double*)F32(gpart);
+  // bias gradient from the column sums that the kernel before left in part
+  auto bias_sums = [&](const ParamRef& R, int C) -> int {
+    ColSums o{{hv + R.off, nullptr, nullptr}};
+    CK(launch_colsum_part(o, part, bias_groups(T_, C), C, C, 1.0 / eps, acc, st));
     return FDH_OK;
   };
-  bool op_ready = false;  // dxo holds the operand-type copy of the last norm backward's output
   // norm backward at both points into (dym, dyd) with its operand-type copy in
-  // dxo (bf16 models), then the gain (and LayerNorm bias) gradients
+  // dxo (bf16 models), then the gain (and LayerNorm bias) gradients and that of
+  // the bias, if any, of the linear layer whose output gradient this is
   auto norm_back = [&](float* ym, float* yd, const float* rm, const float* rd, const float* xm_, const float* xd_,
-                       const float* gm_, const float* gd_, const ParamRef& gain, const ParamRef& bias) -> int {
-    const int nwg = norm_bwd_groups(T_);
-    double* gp = (double*)F32(gpart);
-    double* bp = ln ? gp + (int64_t)nwg * d : nullptr;
+                       const float* gm_, const float* gd_, const ParamRef& gain, const ParamRef& bias,
+                       const ParamRef& before) -> int {
     const PairT<T> yo = bf16 ? PairT<T>{OP(dxo_m), OP(dxo_d)} : PairT<T>{nullptr, nullptr};
+    const bool osum = before.valid();
     CK(launch_norm_bwd<T>(PairF{ym, yd}, yo, rm, rd, xm_, xd_, gm_, gd_, T_, d, ln, th + gain.off, v + gain.off, eps, neps,
-                          gp, bp, st));
+                          part, osum, st));
     op_ready = bf16;
-    double* cp = (double*)(ws + colpart.off);
-    CK(launch_colsum_f64(hv + gain.off, gp, nwg, d, 1.0 / eps, acc, cp, st));
-    if (ln) CK(launch_colsum_f64(hv + bias.off, bp, nwg, d, 1.0 / eps, acc, cp, st));
+    ColSums o{{hv + gain.off, nullptr, nullptr}};
+    int k = 1;
+    if (ln) o.out[k++] = hv + bias.off;
+    if (osum) o.out[k++] = hv + before.off;
+    CK(launch_colsum_part(o, part, norm_bwd_groups(T_, d, ln), k * d, d, 1.0 / eps, acc, st));
     return FDH_OK;
   };
   // fp32 pair -> operand pair (aliases in fp32 mode; skipped when the norm
@@ -848,7 +859,8 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
   float* dxd = F32(dx0_d);
   float* dym = F32(dx1_m);
   float* dyd = F32(dx1_d);
-  RC(norm_back(dxm, dxd, nullptr, nullptr, F32(xL_m), F32(xL_d), F32(db_m), F32(db_d), nfg, nfb));
+  RC(norm_back(dxm, dxd, nullptr, nullptr, F32(xL_m), F32(xL_d), F32(db_m), F32(db_d), nfg, nfb,
+               L > 0 ? layers[L - 1].b2 : ParamRef{}));
 
   // token slices of the down projection's weight gradient when the MLP's two
   // weight gradients share a launch (0: two launches)
@@ -866,16 +878,14 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     // ---- MLP ----  (dx = gradient w.r.t. layer output)
     T *gom, *god;
     RC(as_op(dxm, dxd, dxo_m, dxo_d, (int64_t)T_ * d, &gom, &god));
-    if (gpt2) RC(colsum_hv(dxd, d, d, R.b2));
     // (with mlp_split > 0 the down projection's weight gradient shares the
     // gate/up one's launch below: gom, god and z stay intact until then)
     if (!mlp_split) RC(lin_wgrad(gom, god, d, OP(s.z_m), OP(s.z_d), F, R.w2));
     RC(lin_dgrad(gom, god, d, R.w2, F, F32(dz_m), F32(dz_d), OUT_F32));
     const int nu = gpt2 ? F : 2 * F;
     if (gpt2) {
-      CK(launch_gelu_bwd<T>(PairT<T>{OP(dgu_m), OP(dgu_d)}, F32(dudf), OP(s.u_m), OP(s.u_d), F32(dz_m), F32(dz_d),
-                            (int64_t)T_ * F, st));
-      RC(colsum_hv(F32(dudf), F, F, R.b1));
+      CK(launch_gelu_bwd<T>(PairT<T>{OP(dgu_m), OP(dgu_d)}, OP(s.u_m), OP(s.u_d), F32(dz_m), F32(dz_d), T_, F, part, st));
+      RC(bias_sums(R.b1, F));
     } else {
       CK(launch_swiglu_bwd<T>(PairT<T>{OP(dgu_m), OP(dgu_d)}, OP(s.u_m), OP(s.u_d), F32(dz_m), F32(dz_d), T_, F, st));
     }
@@ -887,12 +897,11 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     }
     RC(lin_dgrad(OP(dgu_m), OP(dgu_d), nu, R.w1, d, F32(db_m), F32(db_d), OUT_F32));
     // norm 2 backward, residual: dy = dx + norm2'(db)
-    RC(norm_back(dym, dyd, dxm, dxd, F32(s.xmid_m), F32(s.xmid_d), F32(db_m), F32(db_d), R.n2g, R.n2b));
+    RC(norm_back(dym, dyd, dxm, dxd, F32(s.xmid_m), F32(s.xmid_d), F32(db_m), F32(db_d), R.n2g, R.n2b, R.bo));
     std::swap(dxm, dym);
     std::swap(dxd, dyd);
     // ---- attention ----  (dx = gradient w.r.t. x_mid)
     RC(as_op(dxm, dxd, dxo_m, dxo_d, (int64_t)T_ * d, &gom, &god));
-    if (gpt2) RC(colsum_hv(dxd, d, d, R.bo));
     // (paired with the q/k/v weight gradient below: gom, god and o stay intact
     // through the fused attention backward)
     const bool pair_o = std::is_same<T, bf16_t>::value && fused && !force_unsplit && !force_unpaired &&
@@ -1015,18 +1024,26 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
         }
       }
     }
-    {
-      if (gpt2) RC(colsum_hv(gd, qkvd, qkvd, R.bqkv));
-      CK(launch_qkv_bwd_post<T>(PairT<T>{OP(dqkvo_m), OP(dqkvo_d)}, gm, gd, T_, S, Hq, Hk, dh,
-                                (const double*)(ws + rope.off), llama, st));
+    // operand-type q/k/v gradients (fp32 models without RoPE: the fp32 ones as they are)
+    T *qom = OP(dqkvo_m), *qod = OP(dqkvo_d);
+    if (gpt2) {
+      CK(launch_qkv_bias<T>(bf16 ? PairT<T>{qom, qod} : PairT<T>{nullptr, nullptr}, gm, gd, T_, qkvd, part, st));
+      RC(bias_sums(R.bqkv, qkvd));
+      if (!bf16) {
+        qom = (T*)gm;
+        qod = (T*)gd;
+      }
+    } else {
+      CK(launch_qkv_bwd_post<T>(PairT<T>{qom, qod}, gm, gd, T_, S, Hq, Hk, dh, (const double*)(ws + rope.off), st));
     }
     if (pair_o)
-      RC(lin_wgrad_pair(wgrad_args(OP(dqkvo_m), OP(dqkvo_d), qkvd, OP(s.a_m), OP(s.a_d), d, R.wqkv),
+      RC(lin_wgrad_pair(wgrad_args(qom, qod, qkvd, OP(s.a_m), OP(s.a_d), d, R.wqkv),
                         wgrad_args(gom, god, d, OP(s.o_m), OP(s.o_d), Hq * dh, R.wo), 1, R.wo));
     else
-      RC(lin_wgrad(OP(dqkvo_m), OP(dqkvo_d), qkvd, OP(s.a_m), OP(s.a_d), d, R.wqkv));
-    RC(lin_dgrad(OP(dqkvo_m), OP(dqkvo_d), qkvd, R.wqkv, d, F32(da_m), F32(da_d), OUT_F32));
-    RC(norm_back(dym, dyd, dxm, dxd, F32(s.x_in_m), F32(s.x_in_d), F32(da_m), F32(da_d), R.n1g, R.n1b));
+      RC(lin_wgrad(qom, qod, qkvd, OP(s.a_m), OP(s.a_d), d, R.wqkv));
+    RC(lin_dgrad(qom, qod, qkvd, R.wqkv, d, F32(da_m), F32(da_d), OUT_F32));
+    RC(norm_back(dym, dyd, dxm, dxd, F32(s.x_in_m), F32(s.x_in_d), F32(da_m), F32(da_d), R.n1g, R.n1b,
+                 l > 0 ? layers[l - 1].b2 : ParamRef{}));
     std::swap(dxm, dym);
     std::swap(dxd, dyd);
   }
@@ -1052,7 +1069,10 @@ int Engine::check_batch(const int32_t* tok, int B, int S) {
   if ((int64_t)B * S > 16384) { err = "B*S must be <= 16384"; return FDH_ERR_UNSUPPORTED; }
   if (S > 4096) { err = "S must be <= 4096"; return FDH_ERR_UNSUPPORTED; }
   if (S % 8 || dh % 8) { err = "S and head_dim must be multiples of 8"; return FDH_ERR_UNSUPPORTED; }
-  if (fused && S % 128) { err = "this workspace uses fused attention: S must be a multiple of 128"; return FDH_ERR_UNSUPPORTED; }
+  if (fused && planS % 128 == 0 && S % 128) {
+    err = "this workspace was planned for sequences in multiples of 128: S must be one";
+    return FDH_ERR_UNSUPPORTED;
+  }
   return FDH_OK;
 }
 

@@ -124,25 +124,45 @@ template <typename T>
 hipError_t launch_norm_fwd(PairT<T> y, const float* xm, const float* xd, int rows, int dmodel, bool layernorm,
                            const T* th_g, const float* v_g, const T* th_b, const float* v_b, double eps, float norm_eps, hipStream_t s);
 // Norm backward at both points: dx_out = dx_res + d/dx, and dx_op (if dx_op.m is
-// not null) = the operand-type copy of dx_out.  Rows are taken norm_bwd_groups(rows)
-// workgroups at a time: gpart[w][j] (fp64) = the workgroup's sum over its rows
-// of the half difference of dy * xhat (gain gradient), and with bpart (LayerNorm)
-// bpart[w][j] = its sum of dy.d (bias gradient); launch_colsum_f64 finishes both.
-// dmodel * (bpart ? 2 : 1) <= 8192.
-constexpr int NORM_BWD_ROWS = 16;
-inline int norm_bwd_groups(int rows) { return (rows + NORM_BWD_ROWS - 1) / NORM_BWD_ROWS; }
+// not null) = the operand-type copy of dx_out.  Each of norm_bwd_groups
+// workgroups takes consecutive rows; row w of part (fp64) holds workgroup w's
+// column sums of the half difference of dy * xhat (gain gradient), with
+// LayerNorm of dy.d (bias gradient), and with osum of dx_out.d;
+// launch_colsum_part finishes them.  dmodel * (layernorm ? 2 : 1) <= 8192.
+// One wavefront per row from 4096 rows on (256 workgroups) for rows of 512, 1024
+// or 2048 columns; else a workgroup per row (about
+// 1024 workgroups, at most 8 rows each).
+constexpr int NORM_WAVE_ROWS = 16;
+inline bool norm_bwd_waves(int rows, int dm, bool ln) {
+  return rows >= 4096 && (dm == 512 || dm == 1024 || dm == 2048);
+}
+inline int norm_bwd_rows(int rows) { return rows < 2048 ? 1 : rows >= 8192 ? 8 : rows / 1024; }
+inline int norm_bwd_groups(int rows, int dm, bool ln) {
+  const int per = norm_bwd_waves(rows, dm, ln) ? NORM_WAVE_ROWS : norm_bwd_rows(rows);
+  return (rows + per - 1) / per;
+}
 template <typename T>
 hipError_t launch_norm_bwd(PairF dx_out, PairT<T> dx_op, const float* dres_m, const float* dres_d, const float* xm,
                            const float* xd, const float* dym, const float* dyd, int rows, int dmodel, bool layernorm,
-                           const T* th_g, const float* v_g, double eps, float norm_eps, double* gpart, double* bpart,
+                           const T* th_g, const float* v_g, double eps, float norm_eps, double* part, bool osum,
                            hipStream_t s);
 
-// out[j] = scale * sum_t X[t*ld + j] (deterministic); accumulate adds to out.  partial: [64 * C]
-hipError_t launch_colsum(float* out, const float* X, int rows, int C, int64_t ld, double scale, bool accumulate,
-                         double* partial, hipStream_t s);
-// the same for fp64 rows X [rows][C]
-hipError_t launch_colsum_f64(float* out, const double* X, int rows, int C, double scale, bool accumulate, double* partial,
-                             hipStream_t s);
+// out[s][j] = scale * sum_r part[r][s C + j] (deterministic; a null output is
+// left out); accumulate adds to the outputs.  part: [rows][ncol], ncol a multiple of C
+struct ColSums { float* out[3]; };
+hipError_t launch_colsum_part(const ColSums& o, const double* part, int rows, int ncol, int C, double scale, bool accumulate,
+                              hipStream_t s);
+// row groups of the kernels that add up a linear layer's bias gradient over
+// `rows` rows of `cols` columns (about 1024 workgroups of 1024 columns)
+inline int bias_groups(int rows, int cols) {
+  const int cb = (cols + 1023) / 1024, g = cb < 1024 ? 1024 / cb : 1;
+  const int per = (rows + g - 1) / g;
+  return (rows + per - 1) / per;
+}
+// operand-type copy of the q/k/v gradients (out.m not null) and, as rows of
+// part [bias_groups][ncols], the column sums of gd
+template <typename T>
+hipError_t launch_qkv_bias(PairT<T> out, const float* gm, const float* gd, int rows, int ncols, double* part, hipStream_t s);
 
 // RoPE (Llama) of the q and k columns, in place on both channels of the
 // operand-type projection output [T, (Hq + 2 Hk) dh]; v is left as it is
@@ -151,7 +171,7 @@ hipError_t launch_rope_inplace(PairT<T> qkv, int T_, int S, int Hq, int Hk, int 
 // backward RoPE on dq/dk columns (fp32, in place) + cast of dq,dk,dv into operand type
 template <typename T>
 hipError_t launch_qkv_bwd_post(PairT<T> out, float* gm, float* gd, int T_, int S, int Hq, int Hk, int dh,
-                               const double* rope_cs, bool rope, hipStream_t s);
+                               const double* rope_cs, hipStream_t s);
 // rope table: cs[s*dh + 2i] = cos(s * base^(-2i/dh)), cs[s*dh + 2i + 1] = sin(...)
 hipError_t launch_rope_table(double* cs, int S, int dh, double base, hipStream_t s);
 
@@ -186,7 +206,7 @@ struct FlashArgs {
   // derived from scale by the launchers: scale log2(e), scale^2 / 2, scale^3 / 6
   float c_exp, c_cosh, c_sinh;
 };
-// head dimension 64 or 128, S a multiple of 128
+// head dimension 64 or 128, S a multiple of 8
 bool flash_supported(int dh, int S);
 hipError_t launch_flash_fwd(const FlashArgs& a, int B, hipStream_t s);
 // row terms, dq (query columns of g) and dk, dv (key/value columns, summed over each group)
@@ -195,9 +215,10 @@ hipError_t launch_flash_bwd(const FlashArgs& a, int B, hipStream_t s);
 // activations at both points
 template <typename T>
 hipError_t launch_gelu_fwd(PairT<T> z, const T* um, const T* ud, int64_t n, hipStream_t s);
+// part [bias_groups(rows, F)][F]: column sums of the fp32 half difference of du
 template <typename T>
-hipError_t launch_gelu_bwd(PairT<T> du, float* dud_f32, const T* um, const T* ud, const float* dzm, const float* dzd,
-                           int64_t n, hipStream_t s);
+hipError_t launch_gelu_bwd(PairT<T> du, const T* um, const T* ud, const float* dzm, const float* dzd, int rows, int F,
+                           double* part, hipStream_t s);
 template <typename T>
 hipError_t launch_swiglu_fwd(PairT<T> z, const T* gum, const T* gud, int rows, int F, hipStream_t s);
 template <typename T>

@@ -107,98 +107,6 @@ __global__ __launch_bounds__(NT) void norm_fwd_kernel(PairT<T> y, const float* x
   }
 }
 
-// NORM_BWD_ROWS consecutive rows per workgroup.  Besides dx (and its operand-type
-// copy), each workgroup adds up the gain-gradient terms of its rows per column
-// in fp64, in row order (and dy.d for the LayerNorm bias), and writes one
-// partial row; a column sum over the workgroups finishes the gradient.  A
-// column's sum lives in LDS and is only ever touched by the thread that owns
-// the column, so no barrier guards it.
-template <typename T>
-__global__ __launch_bounds__(NT) void norm_bwd_kernel(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd,
-                                                      const float* xm, const float* xd, const float* dym,
-                                                      const float* dyd, int rows, int dm, bool ln, const T* thg,
-                                                      const float* vg, double eps, double neps, double* gpart,
-                                                      double* bpart) {
-  extern __shared__ double cacc[];  // [dm] gain partials, then [dm] bias partials
-  __shared__ double sh[NT / 64];
-  for (int j = threadIdx.x; j < dm; j += NT) {
-    cacc[j] = 0.0;
-    if (bpart) cacc[dm + j] = 0.0;
-  }
-  const int r0 = blockIdx.x * NORM_BWD_ROWS, r1 = min(rows, r0 + NORM_BWD_ROWS);
-  for (int row = r0; row < r1; ++row) {
-    const int64_t o = (int64_t)row * dm;
-    double mup = 0.0, mum = 0.0;
-    if (ln) {
-      double sp = 0.0, sm = 0.0;
-      for (int j = threadIdx.x; j < dm; j += NT) {
-        sp += (double)xm[o + j] + (double)xd[o + j];
-        sm += (double)xm[o + j] - (double)xd[o + j];
-      }
-      mup = block_sum<NT>(sp, sh) / dm;
-      mum = block_sum<NT>(sm, sh) / dm;
-    }
-    double qp = 0.0, qm = 0.0;
-    for (int j = threadIdx.x; j < dm; j += NT) {
-      const double a = (double)xm[o + j] + (double)xd[o + j] - mup;
-      const double b = (double)xm[o + j] - (double)xd[o + j] - mum;
-      qp += a * a;
-      qm += b * b;
-    }
-    const double rp = 1.0 / sqrt(block_sum<NT>(qp, sh) / dm + neps);
-    const double rmi = 1.0 / sqrt(block_sum<NT>(qm, sh) / dm + neps);
-    // means of dxhat and dxhat * xhat at both points
-    double s1p = 0.0, s1m = 0.0, s2p = 0.0, s2m = 0.0;
-    for (int j = threadIdx.x; j < dm; j += NT) {
-      const double g = ldf(thg, j), dg = eps * (double)vg[j];
-      const double xhp = ((double)xm[o + j] + (double)xd[o + j] - mup) * rp;
-      const double xhm = ((double)xm[o + j] - (double)xd[o + j] - mum) * rmi;
-      const double dhp = ((double)dym[o + j] + (double)dyd[o + j]) * (g + dg);
-      const double dhm = ((double)dym[o + j] - (double)dyd[o + j]) * (g - dg);
-      s1p += dhp;
-      s1m += dhm;
-      s2p += dhp * xhp;
-      s2m += dhm * xhm;
-    }
-    const double a1p = ln ? block_sum<NT>(s1p, sh) / dm : 0.0;
-    const double a1m = ln ? block_sum<NT>(s1m, sh) / dm : 0.0;
-    const double a2p = block_sum<NT>(s2p, sh) / dm;
-    const double a2m = block_sum<NT>(s2m, sh) / dm;
-    for (int j = threadIdx.x; j < dm; j += NT) {
-      const double g = ldf(thg, j), dg = eps * (double)vg[j];
-      const double xhp = ((double)xm[o + j] + (double)xd[o + j] - mup) * rp;
-      const double xhm = ((double)xm[o + j] - (double)xd[o + j] - mum) * rmi;
-      const double dyp = (double)dym[o + j] + (double)dyd[o + j];
-      const double dymi = (double)dym[o + j] - (double)dyd[o + j];
-      const double dhp = dyp * (g + dg), dhm = dymi * (g - dg);
-      const double dxp = rp * (dhp - a1p - xhp * a2p);
-      const double dxm = rmi * (dhm - a1m - xhm * a2m);
-      const double rm0 = dresm ? (double)dresm[o + j] : 0.0;
-      const double rd0 = dresd ? (double)dresd[o + j] : 0.0;
-      const float om = (float)(rm0 + 0.5 * (dxp + dxm)), od = (float)(rd0 + 0.5 * (dxp - dxm));
-      dx.m[o + j] = om;
-      dx.d[o + j] = od;
-      if (dxo.m) {
-        stf(dxo.m, o + j, om);
-        stf(dxo.d, o + j, od);
-      }
-      cacc[j] += 0.5 * (dyp * xhp - dymi * xhm);
-      if (bpart) cacc[dm + j] += (double)dyd[o + j];
-    }
-  }
-  for (int j = threadIdx.x; j < dm; j += NT) {
-    gpart[(int64_t)blockIdx.x * dm + j] = cacc[j];
-    if (bpart) bpart[(int64_t)blockIdx.x * dm + j] = cacc[dm + j];
-  }
-}
-
-// Same computation with one wavefront per row (rows of 256 CPL columns): lane
-// l holds the float4 chunks at columns 256 c + 4 l.  The row reductions are
-// wavefront sums (no barriers); each pass rereads its operands, which after
-// the first pass come from the caches.  Each wavefront adds the
-// gain and bias terms of its rows per column in LDS (fp32, at most
-// NORM_BWD_ROWS / 4 rows), and the four wavefronts' sums are added in fp64 in
-// wavefront order.
 template <typename T>
 __device__ inline float4 ld4f(const T* p, int64_t i) {
   if constexpr (sizeof(T) == 4) {
@@ -318,29 +226,196 @@ __global__ __launch_bounds__(NT) void norm_fwd_wave_kernel(PairT<T> y, const flo
   }
 }
 
-template <typename T, int CPL>
+// Sums of K values over the workgroup, the same for every thread (wavefront sums,
+// then the wavefronts in order).  sh: two slots of K * waves doubles used in
+// turn, so that one barrier per call is enough.
+template <int NTH, int K>
+__device__ inline void block_sums(double (&x)[K], double* sh, int& slot) {
+  constexpr int NWV = NTH / 64;
+#pragma unroll
+  for (int k = 0; k < K; ++k) x[k] = wave_sum(x[k]);
+  if constexpr (NWV > 1) {
+    double* q = sh + slot * K * NWV;
+    slot ^= 1;
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+      for (int k = 0; k < K; ++k) q[k * NWV + (threadIdx.x >> 6)] = x[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      double t = q[k * NWV];
+#pragma unroll
+      for (int w = 1; w < NWV; ++w) t += q[k * NWV + w];
+      x[k] = t;
+    }
+  }
+}
+
+// Norm backward, HBM-bound (three pairs read, one written, with its operand-type
+// copy): a workgroup takes norm_bwd_rows consecutive rows one after the other,
+// thread t the float4 chunks at columns 4 (t + c NTH).  The row of x and dy is
+// read once into registers; both row statistics come from it (RMSNorm: sum x^2
+// and sum dxhat x in one reduction, mean(dxhat xhat) = r mean(dxhat x);
+// LayerNorm: the mean first, then the variance, sum dxhat and sum dxhat (x - mu)
+// in one).  Each thread adds the gain terms of its columns, the LayerNorm bias
+// terms (dy.d) and, with osum, the outputs' half differences (the bias gradient
+// of the linear layer before this norm) over the rows in fp64 registers and
+// writes them as one row of part.  2048 x 4096: 482 -> 90 us, 512 x 64: 69 -> 6 us
+// (16 rows per workgroup, three passes over each before).
+template <typename T, int NTH, int C, bool LN>
+__global__ __launch_bounds__(NTH) void norm_bwd_kernel(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd,
+                                                       const float* xm, const float* xd, const float* dym,
+                                                       const float* dyd, int rows, int per, int dm, const T* thg,
+                                                       const float* vg, double eps, double neps, double* part, int ncol,
+                                                       bool osum) {
+  __shared__ double sh1[2 * 2 * (NTH / 64)], sh2[2 * 6 * (NTH / 64)];
+  int slot1 = 0, slot2 = 0;
+  auto ld = [](const float* p, int64_t i) { return *reinterpret_cast<const float4*>(p + i); };
+  int col[C];
+  bool on[C];
+  float4 g4[C], v4[C];
+  double sg[4 * C], sb[4 * C], so[4 * C];
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    col[c] = 4 * ((int)threadIdx.x + c * NTH);
+    on[c] = col[c] < dm;
+    g4[c] = on[c] ? ld4f(thg, col[c]) : zero;
+    v4[c] = on[c] ? ld(vg, col[c]) : zero;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sg[4 * c + e] = sb[4 * c + e] = so[4 * c + e] = 0.0;
+  }
+  const int r0 = blockIdx.x * per, r1 = min(rows, r0 + per);
+  for (int row = r0; row < r1; ++row) {
+    const int64_t o = (int64_t)row * dm;
+    float4 xa[C], xb[C], ya[C], yb[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      xa[c] = on[c] ? ld(xm, o + col[c]) : zero;
+      xb[c] = on[c] ? ld(xd, o + col[c]) : zero;
+      ya[c] = on[c] ? ld(dym, o + col[c]) : zero;
+      yb[c] = on[c] ? ld(dyd, o + col[c]) : zero;
+    }
+    double mup = 0.0, mum = 0.0, rp, rmi, a1p = 0.0, a1m = 0.0, a2p, a2m;
+    if constexpr (LN) {
+      double t[2] = {0.0, 0.0};
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          t[0] += (double)f4e(xa[c], e) + (double)f4e(xb[c], e);
+          t[1] += (double)f4e(xa[c], e) - (double)f4e(xb[c], e);
+        }
+      block_sums<NTH, 2>(t, sh1, slot1);
+      mup = t[0] / dm;
+      mum = t[1] / dm;
+    }
+    {
+      double t[LN ? 6 : 4];
+#pragma unroll
+      for (int k = 0; k < (LN ? 6 : 4); ++k) t[k] = 0.0;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        if (!on[c]) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double g = f4e(g4[c], e), dg = eps * (double)f4e(v4[c], e);
+          const double p = (double)f4e(xa[c], e) + (double)f4e(xb[c], e) - mup;
+          const double q = (double)f4e(xa[c], e) - (double)f4e(xb[c], e) - mum;
+          const double dhp = ((double)f4e(ya[c], e) + (double)f4e(yb[c], e)) * (g + dg);
+          const double dhm = ((double)f4e(ya[c], e) - (double)f4e(yb[c], e)) * (g - dg);
+          t[0] += p * p;
+          t[1] += q * q;
+          t[2] += dhp * p;
+          t[3] += dhm * q;
+          if constexpr (LN) {
+            t[4] += dhp;
+            t[5] += dhm;
+          }
+        }
+      }
+      block_sums<NTH, LN ? 6 : 4>(t, sh2, slot2);
+      rp = 1.0 / sqrt(t[0] / dm + neps);
+      rmi = 1.0 / sqrt(t[1] / dm + neps);
+      a2p = rp * (t[2] / dm);
+      a2m = rmi * (t[3] / dm);
+      if constexpr (LN) {
+        a1p = t[4] / dm;
+        a1m = t[5] / dm;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      if (!on[c]) continue;
+      const float4 ra = dresm ? ld(dresm, o + col[c]) : zero, rb = dresd ? ld(dresd, o + col[c]) : zero;
+      float om[4], od[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double g = f4e(g4[c], e), dg = eps * (double)f4e(v4[c], e);
+        const double xhp = ((double)f4e(xa[c], e) + (double)f4e(xb[c], e) - mup) * rp;
+        const double xhm = ((double)f4e(xa[c], e) - (double)f4e(xb[c], e) - mum) * rmi;
+        const double dyp = (double)f4e(ya[c], e) + (double)f4e(yb[c], e);
+        const double dyn = (double)f4e(ya[c], e) - (double)f4e(yb[c], e);
+        const double dxp = rp * (dyp * (g + dg) - a1p - xhp * a2p);
+        const double dxn = rmi * (dyn * (g - dg) - a1m - xhm * a2m);
+        om[e] = (float)((double)f4e(ra, e) + 0.5 * (dxp + dxn));
+        od[e] = (float)((double)f4e(rb, e) + 0.5 * (dxp - dxn));
+        sg[4 * c + e] += 0.5 * (dyp * xhp - dyn * xhm);
+        if constexpr (LN) sb[4 * c + e] += (double)f4e(yb[c], e);
+        so[4 * c + e] += (double)od[e];
+      }
+      *reinterpret_cast<float4*>(dx.m + o + col[c]) = make_float4(om[0], om[1], om[2], om[3]);
+      *reinterpret_cast<float4*>(dx.d + o + col[c]) = make_float4(od[0], od[1], od[2], od[3]);
+      if (dxo.m) {
+        st4f(dxo.m, o + col[c], om[0], om[1], om[2], om[3]);
+        st4f(dxo.d, o + col[c], od[0], od[1], od[2], od[3]);
+      }
+    }
+  }
+  double* p = part + (int64_t)blockIdx.x * ncol;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    if (!on[c]) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      p[col[c] + e] = sg[4 * c + e];
+      if constexpr (LN) p[dm + col[c] + e] = sb[4 * c + e];
+      if (osum) p[(LN ? 2 : 1) * dm + col[c] + e] = so[4 * c + e];
+    }
+  }
+}
+
+// The same with one wavefront per row (rows of 256 CPL columns, lane l at columns
+// 256 c + 4 l) and 4 rows per wavefront, 16 per workgroup, for many rows: no
+// barrier per row and a quarter of the reductions per element (8192 x 1024 with
+// LayerNorm: 65 us against 118, 8192 x 2048: 130 against 148).  x is kept in
+// registers, dy read again from the caches (keeping it too cost 100 and 188 us).
+// Column sums in fp32 in LDS, at most 4 rows per wavefront.
+template <typename T, int CPL, bool LN, bool OS>
 __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd,
                                                            const float* xm, const float* xd, const float* dym,
-                                                           const float* dyd, int rows, bool ln, const T* thg,
-                                                           const float* vg, double eps, double neps, double* gpart,
-                                                           double* bpart) {
+                                                           const float* dyd, int rows, const T* thg,
+                                                           const float* vg, double eps, double neps, double* part) {
   constexpr int DM = 256 * CPL;
-  // per-wavefront column sums (gain, bias); a lane only touches its own columns
-  __shared__ float cg[4][DM], cb[4][DM];
+  // per-wavefront column sums (gain, bias, outputs); a lane only touches its own columns
+  constexpr int NS = 1 + (LN ? 1 : 0) + (OS ? 1 : 0);
+  // (rows of 2048: two workgroups per CU by LDS; with more, the second read of dy
+  // misses the L2: 158 us against 130)
+  constexpr int NL = DM >= 2048 && NS < 2 ? 2 : NS;
+  __shared__ float cs[NL][4][DM];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int c = 0; c < CPL; ++c) {
-    *reinterpret_cast<float4*>(&cg[wave][256 * c + 4 * lane]) = make_float4(0.f, 0.f, 0.f, 0.f);
-    *reinterpret_cast<float4*>(&cb[wave][256 * c + 4 * lane]) = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
+  for (int n = 0; n < NS; ++n)
+    for (int c = 0; c < CPL; ++c)
+      *reinterpret_cast<float4*>(&cs[n][wave][256 * c + 4 * lane]) = make_float4(0.f, 0.f, 0.f, 0.f);
   auto ld = [](const float* p, int64_t i) { return *reinterpret_cast<const float4*>(p + i); };
-  const int r0 = blockIdx.x * NORM_BWD_ROWS;
-  for (int i = wave; i < NORM_BWD_ROWS; i += 4) {
+  const int r0 = blockIdx.x * NORM_WAVE_ROWS;
+  for (int i = wave; i < NORM_WAVE_ROWS; i += 4) {
     const int row = r0 + i;
     if (row >= rows) break;
     const int64_t o = (int64_t)row * DM + 4 * lane;
     double mup = 0.0, mum = 0.0;
     float4 xac[CPL], xbc[CPL];   // the row of x, kept in registers for the later passes
-    if (ln) {
+    if constexpr (LN) {
       double sp = 0.0, sm = 0.0;
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
@@ -357,7 +432,7 @@ __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(PairF dx, PairT<T> dx
       mum = wave_sum(sm) / DM;
     }
     double rp, rmi, a1p = 0.0, a1m = 0.0, a2p, a2m;
-    if (!ln) {
+    if constexpr (!LN) {
       // RMSNorm (no mean): sum x^2 and sum dxhat * x in one pass over x and
       // dy; mean(dxhat * xhat) = r * mean(dxhat * x)
       double qp = 0.0, qm = 0.0, tp = 0.0, tm = 0.0;
@@ -446,51 +521,49 @@ __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(PairF dx, PairT<T> dx
         st4f(dxo.m, o + 256 * c, om[0], om[1], om[2], om[3]);
         st4f(dxo.d, o + 256 * c, od[0], od[1], od[2], od[3]);
       }
-      float4* pg = reinterpret_cast<float4*>(&cg[wave][col]);
-      float4* pb = reinterpret_cast<float4*>(&cb[wave][col]);
-      const float4 g0 = *pg, b0 = *pb;
-      *pg = make_float4(g0.x + tg[0], g0.y + tg[1], g0.z + tg[2], g0.w + tg[3]);
-      *pb = make_float4(b0.x + yb.x, b0.y + yb.y, b0.z + yb.z, b0.w + yb.w);
+      auto add = [&](int n, float a, float b, float c, float e) {
+        float4* p = reinterpret_cast<float4*>(&cs[n][wave][col]);
+        const float4 v = *p;
+        *p = make_float4(v.x + a, v.y + b, v.z + c, v.w + e);
+      };
+      add(0, tg[0], tg[1], tg[2], tg[3]);
+      if constexpr (LN) add(1, yb.x, yb.y, yb.z, yb.w);
+      if constexpr (OS) add(NS - 1, od[0], od[1], od[2], od[3]);
     }
   }
   // the four wavefronts' column sums, added in fp64 in wavefront order
   __syncthreads();
-  for (int j = threadIdx.x; j < DM; j += NT) {
-    gpart[(int64_t)blockIdx.x * DM + j] = (double)cg[0][j] + (double)cg[1][j] + (double)cg[2][j] + (double)cg[3][j];
-    if (bpart)
-      bpart[(int64_t)blockIdx.x * DM + j] = (double)cb[0][j] + (double)cb[1][j] + (double)cb[2][j] + (double)cb[3][j];
-  }
+  double* p = part + (int64_t)blockIdx.x * NS * DM;
+  for (int j = threadIdx.x; j < DM; j += NT)
+#pragma unroll
+    for (int n = 0; n < NS; ++n)
+      p[n * DM + j] = (double)cs[n][0][j] + (double)cs[n][1][j] + (double)cs[n][2][j] + (double)cs[n][3][j];
 }
 
 // ---- column sums ---------------------------------------------------------------
-constexpr int COLSUM_CHUNKS = 64;
-__global__ void colsum_stage1(double* partial, const float* X, int rows, int C, int64_t ld) {
-  const int j = blockIdx.x * NT + threadIdx.x;
-  if (j >= C) return;
-  const int c = blockIdx.y;
-  const int per = (rows + COLSUM_CHUNKS - 1) / COLSUM_CHUNKS;
-  const int r0 = c * per, r1 = min(rows, r0 + per);
+// out[s][j] (+)= scale * sum_r part[r][s C + j] for the sums s that have an
+// output.  16 columns and 64 row groups per workgroup: a thread adds every 64th
+// row, lanes and then wavefronts are added in a fixed order.
+__global__ __launch_bounds__(1024) void colsum_part_kernel(ColSums o, const double* part, int rows, int ncol, int C,
+                                                           double scale, bool acc) {
+  __shared__ double sh[16][16];
+  const int cl = threadIdx.x & 15, j = blockIdx.x * 16 + cl;
   double s = 0.0;
-  for (int r = r0; r < r1; ++r) s += (double)X[(int64_t)r * ld + j];
-  partial[(int64_t)c * C + j] = s;
-}
-__global__ void colsum64_stage1(double* partial, const double* X, int rows, int C) {
-  const int j = blockIdx.x * NT + threadIdx.x;
-  if (j >= C) return;
-  const int c = blockIdx.y;
-  const int per = (rows + COLSUM_CHUNKS - 1) / COLSUM_CHUNKS;
-  const int r0 = c * per, r1 = min(rows, r0 + per);
-  double s = 0.0;
-  for (int r = r0; r < r1; ++r) s += X[(int64_t)r * C + j];
-  partial[(int64_t)c * C + j] = s;
-}
-__global__ void colsum_stage2(float* out, const double* partial, int C, double scale, bool acc) {
-  const int j = blockIdx.x * NT + threadIdx.x;
-  if (j >= C) return;
-  double s = 0.0;
-  for (int c = 0; c < COLSUM_CHUNKS; ++c) s += partial[(int64_t)c * C + j];
+  if (j < ncol)
+    for (int r = threadIdx.x >> 4; r < rows; r += 64) s += part[(int64_t)r * ncol + j];
+  s += __shfl_xor(s, 16, 64);
+  s += __shfl_xor(s, 32, 64);
+  if ((threadIdx.x & 63) < 16) sh[threadIdx.x >> 6][cl] = s;
+  __syncthreads();
+  if (threadIdx.x >= 16 || j >= ncol) return;
+  s = 0.0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) s += sh[w][cl];
   s *= scale;
-  out[j] = acc ? (float)((double)out[j] + s) : (float)s;
+  float* out = o.out[j / C];
+  if (!out) return;
+  out += j % C;
+  *out = acc ? (float)((double)*out + s) : (float)s;
 }
 
 // ---- RoPE ----------------------------------------------------------------------
@@ -508,15 +581,15 @@ __global__ void rope_table_kernel(double* cs, int S, int dh, double base) {
 // Both channels in one pass.  A thread takes 4 consecutive columns f0..f0+3
 // of the first half of a q or k head together with their rotate-half
 // partners f0+dh/2.., reads each once and writes both rotated quadruples
-// (packed); v columns (and q/k without RoPE) are cast 4 at a time.
+// (packed); v columns are cast 4 at a time.
 template <typename T, typename TI>
 __global__ void qkv_rope_kernel(PairT<T> out, const TI* inm, const TI* ind, int S, int ncols, int nqk, int dh,
-                                const double* cs, bool rope, bool inverse, bool copy_v) {
+                                const double* cs, bool inverse, bool copy_v) {
   const int t = blockIdx.y;
   const int u = blockIdx.x * blockDim.x + threadIdx.x;
   const int half = dh / 2, qpu = half / 4;      // units per q/k head
-  const int qu = rope ? nqk * qpu : 0;          // rotated units
-  const int vu = copy_v ? (ncols - (rope ? nqk * dh : 0)) / 4 : 0;
+  const int qu = nqk * qpu;                     // rotated units
+  const int vu = copy_v ? (ncols - nqk * dh) / 4 : 0;
   const int64_t o = (int64_t)t * ncols;
   if (u < qu) {
     const int head = u / qpu, f0 = 4 * (u % qpu);
@@ -546,11 +619,35 @@ __global__ void qkv_rope_kernel(PairT<T> out, const TI* inm, const TI* ind, int 
       st4f(outs[ch], o + c + half, hi[0], hi[1], hi[2], hi[3]);
     }
   } else if (u < qu + vu) {
-    const int c = (rope ? nqk * dh : 0) + 4 * (u - qu);
+    const int c = nqk * dh + 4 * (u - qu);
     const float4 a = ld4f(inm, o + c), b = ld4f(ind, o + c);
     st4f(out.m, o + c, a.x, a.y, a.z, a.w);
     st4f(out.d, o + c, b.x, b.y, b.z, b.w);
   }
+}
+
+// Without RoPE: the operand-type copy of both channels (out.m not null) and the
+// q/k/v bias gradient: a thread takes 4 columns of `per` rows and writes the sums
+// of their half differences as its workgroup row of part.
+template <typename T>
+__global__ __launch_bounds__(NT) void qkv_bias_kernel(PairT<T> out, const float* gm, const float* gd, int rows, int per,
+                                                      int ncols, double* part) {
+  const int c = 4 * (blockIdx.x * NT + threadIdx.x);
+  if (c >= ncols) return;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  const int r0 = blockIdx.y * per, r1 = min(rows, r0 + per);
+  for (int r = r0; r < r1; ++r) {
+    const int64_t i = (int64_t)r * ncols + c;
+    const float4 b = *reinterpret_cast<const float4*>(gd + i);
+    if (out.m) {
+      const float4 a = *reinterpret_cast<const float4*>(gm + i);
+      st4f(out.m, i, a.x, a.y, a.z, a.w);
+      st4f(out.d, i, b.x, b.y, b.z, b.w);
+    }
+    s[0] += b.x; s[1] += b.y; s[2] += b.z; s[3] += b.w;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[(int64_t)blockIdx.y * ncols + c + e] = s[e];
 }
 
 // ---- causal softmax and its backward, both points ---------------------------------------
@@ -743,16 +840,48 @@ __global__ void group_sum_kernel(float* out, int64_t out_ld, const float* in, in
 }
 
 // ---- activations ------------------------------------------------------------------
-__device__ inline double gelu_t(double u) {
-  const double k = 0.7978845608028654, a = 0.044715;
-  return 0.5 * u * (1.0 + tanh(k * (u + a * u * u * u)));
+// GELU (tanh form) is u sigmoid(y), y = 2 k (u + a u^3): tanh t = 2 sigmoid(2t) - 1.
+// Both points' sigmoids in fp64 from one exponential and one division:
+// e^-y+- = e^-ym e^-+h for ym and h the half sum and half difference of y+-, and
+// 1 / (1 + e^-y+) = B / (A B), 1 / (1 + e^-y-) = A / (A B).  (e^-ym is held
+// below 1e150, where u sigmoid is already far below the smallest fp32 number.)
+__device__ inline void exp_pm(double b, double& ep, double& en);
+__device__ inline void sigmoid_pair(double yp, double yn, double& sp, double& sn) {
+  const double ym = 0.5 * (yp + yn), h = 0.5 * (yp - yn);
+  double ep, en;
+  if (fabs(h) < 0.0625) {
+    const double E = fmin(exp(-ym), 1e150);
+    exp_pm(h, ep, en);
+    ep *= E;   // e^-yn
+    en *= E;   // e^-yp
+  } else {
+    en = fmin(exp(-yp), 1e150);
+    ep = fmin(exp(-yn), 1e150);
+  }
+  const double A = 1.0 + en, B = 1.0 + ep;
+  const double inv = 1.0 / (A * B);
+  sp = B * inv;
+  sn = A * inv;
 }
-__device__ inline double gelu_t_grad(double u) {
-  const double k = 0.7978845608028654, a = 0.044715;
-  const double t = tanh(k * (u + a * u * u * u));
-  return 0.5 * (1.0 + t) + 0.5 * u * (1.0 - t * t) * k * (1.0 + 3.0 * a * u * u);
+constexpr double GELU_K = 2.0 * 0.7978845608028654, GELU_A = 0.044715;
+__device__ inline void gelu_pair(double a, double b, float& om, float& od) {
+  const double up = a + b, un = a - b;
+  double sp, sn;
+  sigmoid_pair(GELU_K * (up + GELU_A * up * up * up), GELU_K * (un + GELU_A * un * un * un), sp, sn);
+  const double p = up * sp, n = un * sn;
+  om = (float)(0.5 * (p + n));
+  od = (float)(0.5 * (p - n));
 }
-__device__ inline double sigm(double x) { return 1.0 / (1.0 + exp(-x)); }
+// gradient s + u s (1 - s) y'(u) at both points times the upstream gradient
+__device__ inline void gelu_bwd_pair(double a, double b, double zm, double zd, float& om, float& od) {
+  const double up = a + b, un = a - b;
+  double sp, sn;
+  sigmoid_pair(GELU_K * (up + GELU_A * up * up * up), GELU_K * (un + GELU_A * un * un * un), sp, sn);
+  const double gp = (zm + zd) * (sp + up * sp * (1.0 - sp) * (GELU_K * (1.0 + 3.0 * GELU_A * up * up)));
+  const double gn = (zm - zd) * (sn + un * sn * (1.0 - sn) * (GELU_K * (1.0 + 3.0 * GELU_A * un * un)));
+  om = (float)(0.5 * (gp + gn));
+  od = (float)(0.5 * (gp - gn));
+}
 
 // SwiGLU output at both points, (s(a) v_a, s(b) v_b) with s(x) = x sigmoid(x),
 // gate a, b = gm +- gd and up u = um +- ud, returned as its half sum om and half
@@ -803,25 +932,42 @@ __device__ inline void swiglu_bwd_pair(float gm, float gd, float um, float ud, f
   bd = zm * D0 + zd * S0;
 }
 
+// four consecutive elements per thread (n is a multiple of 4)
 template <typename T>
-__global__ void gelu_fwd_kernel(PairT<T> z, const T* um, const T* ud, int64_t n) {
-  GRID_LOOP(i, n) {
-    const double a = ldf(um, i), b = ldf(ud, i);
-    const double up = a + b, un = a - b;
-    put_pair(z, i, gelu_t(up), gelu_t(un));
+__global__ __launch_bounds__(NT) void gelu_fwd_kernel(PairT<T> z, const T* um, const T* ud, int64_t n4) {
+  GRID_LOOP(i, n4) {
+    const float4 a = ld4f(um, 4 * i), b = ld4f(ud, 4 * i);
+    float om[4], od[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) gelu_pair(f4e(a, e), f4e(b, e), om[e], od[e]);
+    st4f(z.m, 4 * i, om[0], om[1], om[2], om[3]);
+    st4f(z.d, 4 * i, od[0], od[1], od[2], od[3]);
   }
 }
+// A thread takes 4 columns of `per` rows; the sums of the half differences (the
+// bias gradient of the MLP input layer, from the fp32 values) go to part.
 template <typename T>
-__global__ void gelu_bwd_kernel(PairT<T> du, float* dudf, const T* um, const T* ud, const float* dzm,
-                                const float* dzd, int64_t n) {
-  GRID_LOOP(i, n) {
-    const double a = ldf(um, i), b = ldf(ud, i);
-    const double up = a + b, un = a - b;
-    const double gp = ((double)dzm[i] + (double)dzd[i]) * gelu_t_grad(up);
-    const double gn = ((double)dzm[i] - (double)dzd[i]) * gelu_t_grad(un);
-    put_pair(du, i, gp, gn);
-    if (dudf) dudf[i] = (float)(0.5 * (gp - gn));
+__global__ __launch_bounds__(NT) void gelu_bwd_kernel(PairT<T> du, const T* um, const T* ud, const float* dzm,
+                                                      const float* dzd, int rows, int per, int F, double* part) {
+  const int c = 4 * (blockIdx.x * NT + threadIdx.x);
+  if (c >= F) return;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  const int r0 = blockIdx.y * per, r1 = min(rows, r0 + per);
+  for (int r = r0; r < r1; ++r) {
+    const int64_t i = (int64_t)r * F + c;
+    const float4 a = ld4f(um, i), b = ld4f(ud, i);
+    const float4 zm = *reinterpret_cast<const float4*>(dzm + i), zd = *reinterpret_cast<const float4*>(dzd + i);
+    float om[4], od[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      gelu_bwd_pair(f4e(a, e), f4e(b, e), f4e(zm, e), f4e(zd, e), om[e], od[e]);
+      s[e] += (double)od[e];
+    }
+    st4f(du.m, i, om[0], om[1], om[2], om[3]);
+    st4f(du.d, i, od[0], od[1], od[2], od[3]);
   }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[(int64_t)blockIdx.y * F + c + e] = s[e];
 }
 // Vectorised forms: grid.y = row, each thread 4 consecutive columns of the
 // F gate (and F up) columns; F % 4 == 0.  Same arithmetic as the scalar forms.
@@ -907,71 +1053,82 @@ __device__ inline void exp_pm(double b, double& ep, double& en) {
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(NT) void ce_kernel(PairT<T> dl, double* rowloss, const float* lm, const float* ld,
-                                                const int32_t* tok, const int32_t* lab, int T_, int S, int V,
-                                                double inv_n) {
-  __shared__ double sh[NT / 64];
+// One workgroup per row, four consecutive logits per thread and step, two passes.
+// Large workgroups keep few rows in flight, so that the second pass over a row
+// finds it in the last-level cache (256 KB per row of 32000 logits: 512 rows in
+// flight are 128 MB, the 2048 rows of 256-thread workgroups do not fit).
+// 8192 x 32000: 1250 -> 1020 us.
+template <typename T, int NTH>
+__global__ __launch_bounds__(NTH) void ce_kernel(PairT<T> dl, double* rowloss, const float* lm, const float* ld,
+                                                 const int32_t* tok, const int32_t* lab, int T_, int S, int V,
+                                                 double inv_n) {
+  __shared__ double sh[NTH / 64];
   const int64_t t = blockIdx.x;
   const int64_t o = t * (int64_t)V;
+  const int n4 = V / 4;   // V is a multiple of 8
   const bool last = (t % S) == (S - 1);
   const int raw = last ? IGNORE_LABEL : (lab ? lab[t + 1] : tok[t + 1]);
   if (raw == IGNORE_LABEL) {
-    for (int j = threadIdx.x; j < V; j += NT) put_pair(dl, o + j, 0.0, 0.0);
+    for (int j = threadIdx.x; j < n4; j += NTH) {
+      st4f(dl.m, o + 4 * j, 0.f, 0.f, 0.f, 0.f);
+      st4f(dl.d, o + 4 * j, 0.f, 0.f, 0.f, 0.f);
+    }
     if (threadIdx.x == 0) { rowloss[t] = 0.0; rowloss[T_ + t] = 0.0; }
     return;
   }
   const int y = clamp_tok(raw, V);
-  // exp(a +- b) = E e^+-b with E = exp(a) shared by both points.  For bf16
-  // models E is taken in fp32 (a common factor of the two channels, so its
-  // rounding never cancels in their half difference) and e^+-b from exp_pm;
-  // fp32 models keep both exponentials in fp64.
-  auto both = [&](double a, double b, double& xp, double& xn) {
-    if constexpr (sizeof(T) == 2) {
-      const double E = (double)__expf((float)a);
-      double ep, en;
-      exp_pm(b, ep, en);
-      xp = E * ep;
-      xn = E * en;
-    } else {
-      xp = exp(a + b);
-      xn = exp(a - b);
-    }
+  auto ld4 = [](const float* p, int64_t i) { return *reinterpret_cast<const float4*>(p + i); };
+  // exp(a +- b) = E e^+-b with E = exp(a) shared by both points and e^+-b from
+  // exp_pm.  For bf16 models E is taken in fp32 (a common factor of the two
+  // channels, so its rounding never cancels in their half difference).
+  auto expa = [&](double a) {
+    if constexpr (sizeof(T) == 2) return (double)__expf((float)a);
+    else return exp(a);
   };
   // one pass for the row maximum and the sums: each thread keeps its sums
   // relative to its own running maximum mt, rescaled by exp(old mt - new mt)
   // when mt rises, then relative to the row maximum mx.  The rescale factors
-  // are common to both points (taken in fp32 for bf16 models, like E).
-  auto rescale = [&](double d) {
-    if constexpr (sizeof(T) == 2) return (double)__expf((float)d);
-    else return exp(d);
-  };
+  // are common to both points.
   double mt = -1e300, zp = 0.0, zm = 0.0;
-  for (int j = threadIdx.x; j < V; j += NT) {
-    const double av = (double)lm[o + j], b = (double)ld[o + j];
-    if (av > mt) {
-      const double f = mt > -1e300 ? rescale(mt - av) : 0.0;
+  for (int j = threadIdx.x; j < n4; j += NTH) {
+    const float4 a = ld4(lm, o + 4 * j), b = ld4(ld, o + 4 * j);
+    const double top = (double)fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w));
+    if (top > mt) {
+      const double f = mt > -1e300 ? expa(mt - top) : 0.0;
       zp *= f;
       zm *= f;
-      mt = av;
+      mt = top;
     }
-    double xp, xn;
-    both(av - mt, b, xp, xn);
-    zp += xp;
-    zm += xn;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double E = expa((double)f4e(a, e) - mt);
+      double ep, en;
+      exp_pm((double)f4e(b, e), ep, en);
+      zp += E * ep;
+      zm += E * en;
+    }
   }
-  const double mx = block_max<NT>(mt, sh);
-  const double fr = mt > -1e300 ? rescale(mt - mx) : 0.0;
-  zp = block_sum<NT>(zp * fr, sh);
-  zm = block_sum<NT>(zm * fr, sh);
-  const double izp = 1.0 / zp, izm = 1.0 / zm;
-  for (int j = threadIdx.x; j < V; j += NT) {
-    const double a = (double)lm[o + j] - mx, b = (double)ld[o + j];
-    double xp, xn;
-    both(a, b, xp, xn);
-    double pp = xp * izp, pn = xn * izm;
-    if (j == y) { pp -= 1.0; pn -= 1.0; }
-    put_pair(dl, o + j, pp * inv_n, pn * inv_n);
+  const double mx = block_max<NTH>(mt, sh);
+  const double fr = mt > -1e300 ? expa(mt - mx) : 0.0;
+  zp = block_sum<NTH>(zp * fr, sh);
+  zm = block_sum<NTH>(zm * fr, sh);
+  const double izp = inv_n / zp, izm = inv_n / zm;
+  // (last logits first: they are still in the L2)
+  for (int j = ((n4 - 1) / NTH) * NTH + threadIdx.x; j >= 0; j -= NTH) {
+    if (j >= n4) continue;
+    const float4 a = ld4(lm, o + 4 * j), b = ld4(ld, o + 4 * j);
+    float om[4], od[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double E = expa((double)f4e(a, e) - mx);
+      double ep, en;
+      exp_pm((double)f4e(b, e), ep, en);
+      const double pp = E * ep * izp, pn = E * en * izm;
+      om[e] = (float)(0.5 * (pp + pn) - (4 * j + e == y ? inv_n : 0.0));
+      od[e] = (float)(0.5 * (pp - pn));
+    }
+    st4f(dl.m, o + 4 * j, om[0], om[1], om[2], om[3]);
+    st4f(dl.d, o + 4 * j, od[0], od[1], od[2], od[3]);
   }
   if (threadIdx.x == 0) {
     const double a = (double)lm[o + y] - mx, b = (double)ld[o + y];
@@ -984,7 +1141,17 @@ __global__ void loss_sum_kernel(double* out2, const double* rowloss, int T_, boo
   __shared__ double sh[NT / 64];
   double a = 0.0, b = 0.0;
   // fixed assignment of rows to threads, fixed reduction tree
-  for (int t = threadIdx.x; t < T_; t += NT) { a += rowloss[t]; b += rowloss[T_ + t]; }
+  for (int t0 = threadIdx.x; t0 < T_; t0 += 8 * NT) {
+    double x[8], y[8];   // sixteen loads in flight
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int t = t0 + u * NT;
+      x[u] = t < T_ ? rowloss[t] : 0.0;
+      y[u] = t < T_ ? rowloss[T_ + t] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { a += x[u]; b += y[u]; }
+  }
   a = block_sum<NT>(a, sh);
   b = block_sum<NT>(b, sh);
   if (threadIdx.x == 0) {
@@ -1023,35 +1190,45 @@ __global__ void count_targets_kernel(int64_t* out, const int32_t* tok, const int
 }
 
 // ---- embedding backward --------------------------------------------------------------
-constexpr int SORT_N = 16384;  // keys = token << 14 | position, positions < 2^14
-__global__ __launch_bounds__(1024) void token_sort_kernel(uint32_t* keys, const int32_t* tok, int T_, int V) {
-  __shared__ uint32_t k[SORT_N];
-  int n2 = 1;
-  while (n2 < T_) n2 <<= 1;
-  for (int i = threadIdx.x; i < n2; i += 1024)
-    k[i] = (i < T_) ? (((uint32_t)clamp_tok(tok[i], V) << 14) | (uint32_t)i) : 0xFFFFFFFFu;
-  __syncthreads();
-  for (int size = 2; size <= n2; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = threadIdx.x; i < n2; i += 1024) {
-        const int p = i ^ stride;
-        if (p > i) {
-          const bool up = (i & size) == 0;
-          const uint32_t a = k[i], b = k[p];
-          if ((a > b) == up) { k[i] = b; k[p] = a; }
-        }
-      }
-      __syncthreads();
+// Sorted keys by rank: keys = token << 14 | position (positions < 2^14) are
+// distinct, so the rank of a key is the number of smaller ones.  A workgroup
+// holds all keys in LDS and ranks 32 of them, 8 lanes each (T^2 / 8 comparisons
+// per lane group over the whole chip; one workgroup's bitonic sort of 8192 keys
+// took 100 us, this 26).
+constexpr int SORT_N = 16384;
+__global__ __launch_bounds__(NT) void token_sort_kernel(uint32_t* keys, const int32_t* tok, int T_, int V) {
+  extern __shared__ uint32_t k[];   // [round_up(T, 4)]
+  const int n4 = (T_ + 3) / 4;
+  for (int i0 = threadIdx.x; i0 < 4 * n4; i0 += 8 * NT) {
+    int t[8];   // eight loads in flight
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = tok[min(i0 + u * NT, T_ - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + u * NT;
+      if (i < 4 * n4) k[i] = i < T_ ? (((uint32_t)clamp_tok(t[u], V) << 14) | (uint32_t)i) : 0xFFFFFFFFu;
     }
   }
-  for (int i = threadIdx.x; i < T_; i += 1024) keys[i] = k[i];
+  __syncthreads();
+  const int i = blockIdx.x * (NT / 8) + (threadIdx.x >> 3);
+  const uint32_t own = k[min(i, T_ - 1)];
+  int rank = 0;
+  for (int q = threadIdx.x & 7; q < n4; q += 8) {
+    const uint4 x = *reinterpret_cast<const uint4*>(k + 4 * q);
+    rank += (int)(x.x < own) + (int)(x.y < own) + (int)(x.z < own) + (int)(x.w < own);
+  }
+  rank += __shfl_xor(rank, 1, 64);
+  rank += __shfl_xor(rank, 2, 64);
+  rank += __shfl_xor(rank, 4, 64);
+  if ((threadIdx.x & 7) == 0 && i < T_) keys[rank] = own;
 }
 
 // One workgroup per (sorted position, NT-column chunk); only segment starts
-// work.  The segment end is found by binary search in the sorted keys, and
-// the segment's rows are summed with 8 partial sums (row q of the segment
-// into partial q % 8, combined in a fixed order), so that frequent tokens
-// (hundreds of rows under a Zipf distribution) keep 8 loads in flight.
+// work.  The segment end is found by binary search in the sorted keys, and the
+// segment's rows are summed with 16 partial sums (row q of the segment into
+// partial q % 16, combined in a fixed order), the next rows' keys loaded ahead:
+// a frequent token (hundreds of rows under a Zipf distribution) is a chain of
+// loads, which bounds the kernel.  8192 x 512: 81 -> 70 us (8 rows in flight).
 __global__ void embed_bwd_kernel(float* hv, const uint32_t* keys, const float* dxd, int T_, int dm, double inv_eps,
                                  bool acc) {
   const int j = blockIdx.x;
@@ -1066,16 +1243,33 @@ __global__ void embed_bwd_kernel(float* hv, const uint32_t* keys, const float* d
   const int e = lo;
   const int c = blockIdx.y * NT + threadIdx.x;
   if (c >= dm) return;
-  double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  int q = j;
-  for (; q + 8 <= e; q += 8) {
+  constexpr int U = 16;
+  double s[U];
+  uint32_t pos[U];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s[u] += (double)dxd[(int64_t)(keys[q + u] & 0x3FFFu) * dm + c];
+  for (int u = 0; u < U; ++u) {
+    s[u] = 0.0;
+    pos[u] = keys[min(j + u, T_ - 1)] & 0x3FFFu;
   }
-  for (int u = 0; q < e; ++q, ++u) s[u] += (double)dxd[(int64_t)(keys[q] & 0x3FFFu) * dm + c];
-  const double t = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+  int q = j;
+  for (; q + U <= e; q += U) {
+    float x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = dxd[(int64_t)pos[u] * dm + c];
+#pragma unroll
+    for (int u = 0; u < U; ++u) pos[u] = keys[min(q + U + u, T_ - 1)] & 0x3FFFu;
+#pragma unroll
+    for (int u = 0; u < U; ++u) s[u] += (double)x[u];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (q + u < e) s[u] += (double)dxd[(int64_t)pos[u] * dm + c];
+#pragma unroll
+  for (int w = U / 2; w > 0; w /= 2)
+#pragma unroll
+    for (int u = 0; u < w; ++u) s[u] += s[u + w];
   const int64_t idx = (int64_t)tk * dm + c;
-  hv[idx] = acc ? (float)((double)hv[idx] + t * inv_eps) : (float)(t * inv_eps);
+  hv[idx] = acc ? (float)((double)hv[idx] + s[0] * inv_eps) : (float)(s[0] * inv_eps);
 }
 
 __global__ void pos_bwd_kernel(float* hv, const float* dxd, int B, int S, int dm, double inv_eps, bool acc) {
@@ -1123,35 +1317,59 @@ hipError_t launch_norm_fwd(PairT<T> y, const float* xm, const float* xd, int row
 template <typename T>
 hipError_t launch_norm_bwd(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd, const float* xm, const float* xd,
                            const float* dym, const float* dyd, int rows, int dm, bool ln, const T* thg,
-                           const float* vg, double eps, float neps, double* gpart, double* bpart, hipStream_t s) {
-  const dim3 g(norm_bwd_groups(rows));
-  // one wavefront per row where the row is 512, 1024 or 2048 columns
-#define NBW(C) hipLaunchKernelGGL((norm_bwd_wave_kernel<T, C>), g, dim3(NT), 0, s, dx, dxo, dresm, dresd, xm, xd, dym, dyd, \
-                                  rows, ln, thg, vg, eps, (double)neps, gpart, bpart)
-  if (dm == 512) NBW(2);
-  else if (dm == 1024) NBW(4);
-  else if (dm == 2048) NBW(8);
-  else {
-    const size_t lds = (size_t)dm * (bpart ? 2 : 1) * sizeof(double);
-    if (lds > 64 * 1024) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(norm_bwd_kernel<T>, g, dim3(NT), lds, s, dx, dxo, dresm, dresd, xm, xd, dym, dyd, rows, dm, ln, thg,
-                       vg, eps, (double)neps, gpart, bpart);
+                           const float* vg, double eps, float neps, double* part, bool osum, hipStream_t s) {
+  // (wider rows were never supported)
+  if ((size_t)dm * (ln ? 2 : 1) > 8192) return hipErrorInvalidValue;
+  if (norm_bwd_waves(rows, dm, ln)) {
+    const dim3 g(norm_bwd_groups(rows, dm, ln));
+#define NW(C, L, O)                                                                                                    \
+  hipLaunchKernelGGL((norm_bwd_wave_kernel<T, C, L, O>), g, dim3(NT), 0, s, dx, dxo, dresm, dresd, xm, xd, dym, dyd,    \
+                     rows, thg, vg, eps, (double)neps, part)
+#define NWD(C)                    \
+  do {                            \
+    if (ln && osum) NW(C, true, true);  \
+    else if (ln) NW(C, true, false);    \
+    else if (osum) NW(C, false, true);  \
+    else NW(C, false, false);     \
+  } while (0)
+    if (dm == 512) NWD(2);
+    else if (dm == 1024) NWD(4);
+    else NWD(8);
+#undef NWD
+#undef NW
+    return hipGetLastError();
   }
-#undef NBW
+  const int per = norm_bwd_rows(rows), ncol = dm * (1 + (ln ? 1 : 0) + (osum ? 1 : 0));
+  const dim3 g(norm_bwd_groups(rows, dm, ln));
+#define NB(N, C)                                                                                                        \
+  do {                                                                                                                  \
+    if (ln) hipLaunchKernelGGL((norm_bwd_kernel<T, N, C, true>), g, dim3(N), 0, s, dx, dxo, dresm, dresd, xm, xd, dym,  \
+                               dyd, rows, per, dm, thg, vg, eps, (double)neps, part, ncol, osum);                       \
+    else hipLaunchKernelGGL((norm_bwd_kernel<T, N, C, false>), g, dim3(N), 0, s, dx, dxo, dresm, dresd, xm, xd, dym,    \
+                            dyd, rows, per, dm, thg, vg, eps, (double)neps, part, ncol, osum);                          \
+  } while (0)
+  // as few chunks per thread as the registers of the column sums allow
+  if (dm <= 256) NB(64, 1);
+  else if (dm <= 512) NB(128, 1);
+  else if (dm <= 1024) NB(256, 1);
+  else if (dm <= 2048) NB(256, 2);
+  else if (dm <= 4096) NB(512, 2);
+  else NB(1024, 2);
+#undef NB
   return hipGetLastError();
 }
 
-hipError_t launch_colsum(float* out, const float* X, int rows, int C, int64_t ld, double scale, bool acc, double* partial,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(colsum_stage1, dim3(ceil_div(C, NT), COLSUM_CHUNKS), dim3(NT), 0, s, partial, X, rows, C, ld);
-  hipLaunchKernelGGL(colsum_stage2, dim3(ceil_div(C, NT)), dim3(NT), 0, s, out, (const double*)partial, C, scale, acc);
+hipError_t launch_colsum_part(const ColSums& o, const double* part, int rows, int ncol, int C, double scale, bool acc,
+                              hipStream_t s) {
+  hipLaunchKernelGGL(colsum_part_kernel, dim3(ceil_div(ncol, 16)), dim3(1024), 0, s, o, part, rows, ncol, C, scale, acc);
   return hipGetLastError();
 }
 
-hipError_t launch_colsum_f64(float* out, const double* X, int rows, int C, double scale, bool acc, double* partial,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(colsum64_stage1, dim3(ceil_div(C, NT), COLSUM_CHUNKS), dim3(NT), 0, s, partial, X, rows, C);
-  hipLaunchKernelGGL(colsum_stage2, dim3(ceil_div(C, NT)), dim3(NT), 0, s, out, (const double*)partial, C, scale, acc);
+template <typename T>
+hipError_t launch_qkv_bias(PairT<T> out, const float* gm, const float* gd, int rows, int ncols, double* part, hipStream_t s) {
+  const int groups = bias_groups(rows, ncols), per = (rows + groups - 1) / groups;
+  hipLaunchKernelGGL(qkv_bias_kernel<T>, dim3(ceil_div(ncols / 4, NT), groups), dim3(NT), 0, s, out, gm, gd, rows, per,
+                     ncols, part);
   return hipGetLastError();
 }
 
@@ -1166,18 +1384,18 @@ hipError_t launch_rope_inplace(PairT<T> qkv, int T_, int S, int Hq, int Hk, int 
   const int units = (Hq + Hk) * dh / 8;
   const dim3 g(ceil_div(units, NT), T_);
   hipLaunchKernelGGL((qkv_rope_kernel<T, T>), g, dim3(NT), 0, s, qkv, (const T*)qkv.m, (const T*)qkv.d, S, ncols, Hq + Hk, dh,
-                     cs, true, false, false);
+                     cs, false, false);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_qkv_bwd_post(PairT<T> out, float* gm, float* gd, int T_, int S, int Hq, int Hk, int dh,
-                               const double* cs, bool rope, hipStream_t s) {
+                               const double* cs, hipStream_t s) {
   const int ncols = (Hq + 2 * Hk) * dh;
-  const int units = (rope ? (Hq + Hk) * dh / 8 : 0) + (ncols - (rope ? (Hq + Hk) * dh : 0)) / 4;
+  const int units = (Hq + Hk) * dh / 8 + (ncols - (Hq + Hk) * dh) / 4;
   const dim3 g(ceil_div(units, NT), T_);
   hipLaunchKernelGGL((qkv_rope_kernel<T, float>), g, dim3(NT), 0, s, out, (const float*)gm, (const float*)gd, S, ncols,
-                     Hq + Hk, dh, cs, rope, true, true);
+                     Hq + Hk, dh, cs, true, true);
   return hipGetLastError();
 }
 
@@ -1211,13 +1429,15 @@ hipError_t launch_group_sum(float* out, int64_t out_ld, const float* in, int T_,
 
 template <typename T>
 hipError_t launch_gelu_fwd(PairT<T> z, const T* um, const T* ud, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(gelu_fwd_kernel<T>, dim3(grid_for(n)), dim3(NT), 0, s, z, um, ud, n);
+  hipLaunchKernelGGL(gelu_fwd_kernel<T>, dim3(grid_for(n / 4)), dim3(NT), 0, s, z, um, ud, n / 4);
   return hipGetLastError();
 }
 template <typename T>
-hipError_t launch_gelu_bwd(PairT<T> du, float* dudf, const T* um, const T* ud, const float* dzm, const float* dzd,
-                           int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(gelu_bwd_kernel<T>, dim3(grid_for(n)), dim3(NT), 0, s, du, dudf, um, ud, dzm, dzd, n);
+hipError_t launch_gelu_bwd(PairT<T> du, const T* um, const T* ud, const float* dzm, const float* dzd, int rows, int F,
+                           double* part, hipStream_t s) {
+  const int groups = bias_groups(rows, F), per = (rows + groups - 1) / groups;
+  hipLaunchKernelGGL(gelu_bwd_kernel<T>, dim3(ceil_div(F / 4, NT), groups), dim3(NT), 0, s, du, um, ud, dzm, dzd, rows, per,
+                     F, part);
   return hipGetLastError();
 }
 template <typename T>
@@ -1247,7 +1467,9 @@ hipError_t launch_swiglu_bwd(PairT<T> dgu, const T* gum, const T* gud, const flo
 template <typename T>
 hipError_t launch_ce(PairT<T> dl, double* rowloss, const float* lm, const float* ld, const int32_t* tok,
                      const int32_t* lab, int T_, int S, int V, double inv_n, hipStream_t s) {
-  hipLaunchKernelGGL(ce_kernel<T>, dim3(T_), dim3(NT), 0, s, dl, rowloss, lm, ld, tok, lab, T_, S, V, inv_n);
+  // one step of the row loop over the whole workgroup is 4 NTH logits
+  if (V >= 8192) hipLaunchKernelGGL((ce_kernel<T, 1024>), dim3(T_), dim3(1024), 0, s, dl, rowloss, lm, ld, tok, lab, T_, S, V, inv_n);
+  else hipLaunchKernelGGL((ce_kernel<T, NT>), dim3(T_), dim3(NT), 0, s, dl, rowloss, lm, ld, tok, lab, T_, S, V, inv_n);
   return hipGetLastError();
 }
 hipError_t launch_loss_sum(double* out2, const double* rowloss, int T_, bool acc, hipStream_t s) {
@@ -1261,7 +1483,7 @@ hipError_t launch_count_targets(int64_t* out3, const int32_t* tok, const int32_t
 
 hipError_t launch_token_sort(uint32_t* keys, const int32_t* tok, int T_, int V, hipStream_t s) {
   if (T_ > SORT_N) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(token_sort_kernel, dim3(1), dim3(1024), 0, s, keys, tok, T_, V);
+  hipLaunchKernelGGL(token_sort_kernel, dim3(ceil_div(T_, NT / 8)), dim3(NT), (size_t)(T_ + 3) / 4 * 16, s, keys, tok, T_, V);
   return hipGetLastError();
 }
 hipError_t launch_embed_bwd(float* hv, const uint32_t* keys, const float* dxd, int T_, int dm, double inv_eps, bool acc,
@@ -1283,16 +1505,17 @@ hipError_t launch_pos_bwd(float* hv, const float* dxd, int B, int S, int dm, dou
                                          const T*, const float*, double, float, hipStream_t);                          \
   template hipError_t launch_norm_bwd<T>(PairF, PairT<T>, const float*, const float*, const float*, const float*,      \
                                          const float*, const float*, int, int, bool, const T*, const float*, double,    \
-                                         float, double*, double*, hipStream_t);                                        \
+                                         float, double*, bool, hipStream_t);                                           \
+  template hipError_t launch_qkv_bias<T>(PairT<T>, const float*, const float*, int, int, double*, hipStream_t);        \
   template hipError_t launch_rope_inplace<T>(PairT<T>, int, int, int, int, int, const double*, hipStream_t);          \
-  template hipError_t launch_qkv_bwd_post<T>(PairT<T>, float*, float*, int, int, int, int, int, const double*, bool,   \
+  template hipError_t launch_qkv_bwd_post<T>(PairT<T>, float*, float*, int, int, int, int, int, const double*,         \
                                              hipStream_t);                                                             \
   template hipError_t launch_attn_softmax<T>(PairT<T>, const float*, const float*, int, int, hipStream_t);             \
   template hipError_t launch_attn_dsoftmax<T>(PairT<T>, const T*, const T*, const float*, const float*, int, int,      \
                                               hipStream_t);                                                            \
   template hipError_t launch_gelu_fwd<T>(PairT<T>, const T*, const T*, int64_t, hipStream_t);                          \
-  template hipError_t launch_gelu_bwd<T>(PairT<T>, float*, const T*, const T*, const float*, const float*,             \
-                                         int64_t, hipStream_t);                                                        \
+  template hipError_t launch_gelu_bwd<T>(PairT<T>, const T*, const T*, const float*, const float*, int, int, double*,  \
+                                         hipStream_t);                                                                 \
   template hipError_t launch_swiglu_fwd<T>(PairT<T>, const T*, const T*, int, int, hipStream_t);                       \
   template hipError_t launch_swiglu_bwd<T>(PairT<T>, const T*, const T*, const float*, const float*, int, int,         \
                                            hipStream_t);                                                               \
