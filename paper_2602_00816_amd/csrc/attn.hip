@@ -178,18 +178,19 @@ __device__ inline void coshsinh(float b, float& c, float& s) {
 // dst + i * R * D.  Each load moves 1 KB: 64 lanes x 16 bytes, lane l at
 // +16 l in LDS, so each lane fetches the logical chunk that the swizzle puts
 // at that position.  Completion is waited for with vmcnt before the barrier
-// that publishes the tiles.
+// that publishes the tiles.  `rows` of the tile lie inside the sequence; where
+// that is fewer than R the rest read the last of them (finite values that the
+// causal mask, or the mask of the queries past the end, keeps out).
 template <int D, int R, int NTILE, int SW = 0, int NWV = 4>
-__device__ inline void dma_tiles(bf16_t* dst, const bf16_t* const (&src)[NTILE], int64_t ld, int wave, int lane) {
+__device__ inline void dma_tiles(bf16_t* dst, const bf16_t* const (&src)[NTILE], int64_t ld, int wave, int lane, int rows) {
   constexpr int CPR = D / 8, RPI = 64 / CPR, IPT = R / RPI, NI = NTILE * IPT;
   static_assert(IPT % NWV == 0, "each tile's loads must split evenly over the wavefronts");
-#pragma unroll
-  for (int u = 0; u < NI / NWV; ++u) {
+  auto load = [&](int u, auto whole) {
     const int tile = NWV * u / IPT;         // compile-time: wave < NWV never crosses a tile
     const int q = NWV * u % IPT + wave;
     const int row = q * RPI + lane / CPR, pch = lane % CPR;
     const int lch = (tswz<D, SW>(row, pch) - row * D) >> 3;   // the swizzle is an involution on chunks
-    const bf16_t* g = src[tile] + (int64_t)row * ld + 8 * lch;
+    const bf16_t* g = src[tile] + (int64_t)(decltype(whole)::value ? row : min(row, rows - 1)) * ld + 8 * lch;
     const uint32_t la = (uint32_t)(uintptr_t)(lds_void_t*)(dst + tile * R * D + q * 512);
     asm volatile(
         "s_mov_b32 m0, %0\n\t"
@@ -198,6 +199,13 @@ __device__ inline void dma_tiles(bf16_t* dst, const bf16_t* const (&src)[NTILE],
         :
         : "s"(__builtin_amdgcn_readfirstlane(la)), "v"(g)
         : "memory", "m0");
+  };
+  if (rows >= R) {
+#pragma unroll
+    for (int u = 0; u < NI / NWV; ++u) load(u, std::true_type{});
+  } else {
+#pragma unroll
+    for (int u = 0; u < NI / NWV; ++u) load(u, std::false_type{});
   }
 }
 
@@ -244,11 +252,12 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
   const int q0 = qb * 128, qw = q0 + 32 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 31);
+  const int qc = min(qi, a.S - 1);   // (a query past the end computes the last one again and stores nothing)
 
   // Q fragments (B operand of S^T = K Q^T), both points' halves
   bf16x8_t qm[KS], qd[KS];
   {
-    const int64_t off = (row0 + qi) * a.ld + (int64_t)h * D + 8 * (lane >> 5);
+    const int64_t off = (row0 + qc) * a.ld + (int64_t)h * D + 8 * (lane >> 5);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       qm[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + off + 16 * s);
@@ -267,21 +276,23 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
     for (int r = 0; r < 16; ++r) Ac[t][r] = X[t][r] = 0.f;
   float zc = 0.f, zs = 0.f;
 
-  const int nkb = (q0 + 128) / KB;
+  const int nkb = min((q0 + 128) / KB, (a.S + KB - 1) / KB);
   const int lastw = qw / KB;   // this wavefront's diagonal block
   constexpr float LOG2E = 1.4426950408889634f;
   // block j of K (or V) into stage j % R; past the last block the last block
   // is loaded again (never read), so every iteration issues the same number
   // of loads and the vmcnt waits are constants
   auto issue_k = [&](int j) {
-    const int64_t r = row0 + (int64_t)min(j, nkb - 1) * KB;
+    const int jb = min(j, nkb - 1);
+    const int64_t r = row0 + (int64_t)jb * KB;
     const bf16_t* src[2] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D};
-    dma_tiles<D, KB, 2>(kring[j % R], src, a.ld, wave, lane);
+    dma_tiles<D, KB, 2>(kring[j % R], src, a.ld, wave, lane, a.S - jb * KB);
   };
   auto issue_v = [&](int j) {
-    const int64_t r = row0 + (int64_t)min(j, nkb - 1) * KB;
+    const int jb = min(j, nkb - 1);
+    const int64_t r = row0 + (int64_t)jb * KB;
     const bf16_t* src[2] = {a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 2>(vring[j % R], src, a.ld, wave, lane);
+    dma_tiles<D, KB, 2>(vring[j % R], src, a.ld, wave, lane, a.S - jb * KB);
   };
   // raw scores of the block in kring[st]: sm = K.m q.m, sd = K.m q.d + K.d q.m
   auto scores = [&](int st, f32x16_t& sm, f32x16_t& sd) {
@@ -457,6 +468,7 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
   zs += __shfl_xor(zs, 32, 64);
   const float den = (zc - zs) * (zc + zs);
   const float u = zc / den, w = zs / den;
+  if (qi >= a.S) return;
   const int64_t orow = (row0 + qi) * a.ldo + (int64_t)h * D + 4 * (lane >> 5);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -502,10 +514,11 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   const int q0 = qb * QS, qw = q0 + 16 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 15);
+  const int qc = min(qi, a.S - 1);   // (a query past the end computes the last one again and stores nothing)
 
   bf16x8_t qm[KS], qd[KS];   // B operands of S^T = K Q^T
   {
-    const int64_t off = (row0 + qi) * a.ld + (int64_t)h * D + 8 * (lane >> 4);
+    const int64_t off = (row0 + qc) * a.ld + (int64_t)h * D + 8 * (lane >> 4);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       qm[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + off + 32 * s);
@@ -522,13 +535,13 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   constexpr float LOG2E = 1.4426950408889634f;
   float mrun = NEG;   // reference maximum of the scaled logits, moved lazily (see flash_fwd_kernel)
 
-  const int nkb = (q0 + QS) / KB;
+  const int nkb = min((q0 + QS) / KB, (a.S + KB - 1) / KB);
   const int lastw = (qw + 15) / KB;   // this wavefront's last key block
   auto issue = [&](int kb) {
     const int64_t r = row0 + (int64_t)kb * KB;
     const bf16_t* src[4] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D,
                             a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 4, 1, NW>(ring[kb & 1], src, a.ld, wave, lane);
+    dma_tiles<D, KB, 4, 1, NW>(ring[kb & 1], src, a.ld, wave, lane, a.S - kb * KB);
   };
   issue(0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -634,6 +647,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   zs += __shfl_xor(zs, 32, 64);
   const float den = (zc - zs) * (zc + zs);
   const float u = zc / den, w = zs / den;
+  if (qi >= a.S) return;
   const int64_t orow = (row0 + qi) * a.ldo + (int64_t)h * D + 4 * (lane >> 4);
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -699,11 +713,12 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
   const int q0 = qb * 128, qw = q0 + 32 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 31);
+  const int qc = min(qi, a.S - 1);   // (a query past the end computes the last one again and stores nothing)
 
   bf16x8_t qm[KS], qd[KS], gm[KS], gd[KS];   // Q and dO fragments (B operands)
   {
-    const int64_t off = (row0 + qi) * a.ld + (int64_t)h * D + 8 * (lane >> 5);
-    const int64_t offo = (row0 + qi) * a.ldo + (int64_t)h * D + 8 * (lane >> 5);
+    const int64_t off = (row0 + qc) * a.ld + (int64_t)h * D + 8 * (lane >> 5);
+    const int64_t offo = (row0 + qc) * a.ldo + (int64_t)h * D + 8 * (lane >> 5);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       qm[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + off + 16 * s);
@@ -712,21 +727,21 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
       gd[s] = *reinterpret_cast<const bf16x8_t*>(a.do_d + offo + 16 * s);
     }
   }
-  const float4 st = a.stats[(int64_t)bh * a.S + qi];
-  const float2 dl = a.delta[(int64_t)bh * a.S + qi];
+  const float4 st = a.stats[(int64_t)bh * a.S + qc];
+  const float2 dl = a.delta[(int64_t)bh * a.S + qc];
   f32x16_t Qm[NT], Qd[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) Qm[t][r] = Qd[t][r] = 0.f;
 
-  const int nkb = (q0 + 128) / KB;
+  const int nkb = min((q0 + 128) / KB, (a.S + KB - 1) / KB);
   const int lastw = qw / KB;
   auto issue = [&](int kb) {
     const int64_t r = row0 + (int64_t)kb * KB;
     const bf16_t* src[4] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D,
                             a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 4>(ring[kb & 1], src, a.ld, wave, lane);
+    dma_tiles<D, KB, 4>(ring[kb & 1], src, a.ld, wave, lane, a.S - kb * KB);
   };
   issue(0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -798,6 +813,7 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
     __syncthreads();
   }
 
+  if (qi >= a.S) return;
   const int64_t grow = (row0 + qi) * a.ldg + (int64_t)h * D + 4 * (lane >> 5);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -838,11 +854,12 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
   const int q0 = qb * QS, qw = q0 + 16 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 15);
+  const int qc = min(qi, a.S - 1);   // (a query past the end computes the last one again and stores nothing)
 
   bf16x8_t qm[KS], qd[KS], gm[KS], gd[KS];   // B operands of S^T = K Q^T, dP^T = V dO^T
   {
-    const int64_t off = (row0 + qi) * a.ld + (int64_t)h * D + 8 * (lane >> 4);
-    const int64_t offo = (row0 + qi) * a.ldo + (int64_t)h * D + 8 * (lane >> 4);
+    const int64_t off = (row0 + qc) * a.ld + (int64_t)h * D + 8 * (lane >> 4);
+    const int64_t offo = (row0 + qc) * a.ldo + (int64_t)h * D + 8 * (lane >> 4);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       qm[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + off + 32 * s);
@@ -851,8 +868,8 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
       gd[s] = *reinterpret_cast<const bf16x8_t*>(a.do_d + offo + 32 * s);
     }
   }
-  const float4 st = a.stats[(int64_t)bh * a.S + qi];
-  const float2 dl = a.delta[(int64_t)bh * a.S + qi];
+  const float4 st = a.stats[(int64_t)bh * a.S + qc];
+  const float2 dl = a.delta[(int64_t)bh * a.S + qc];
   // accumulators t: queries qw + 4 (lane / 16) + r, columns 16 t + lane % 16
   f32x4_t Qm[NT], Qd[NT];
 #pragma unroll
@@ -860,13 +877,13 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
 #pragma unroll
     for (int r = 0; r < 4; ++r) Qm[t][r] = Qd[t][r] = 0.f;
 
-  const int nkb = (q0 + QS) / KB;
+  const int nkb = min((q0 + QS) / KB, (a.S + KB - 1) / KB);
   const int lastw = (qw + 15) / KB;   // this wavefront's last key block
   auto issue = [&](int kb) {
     const int64_t r = row0 + (int64_t)kb * KB;
     const bf16_t* src[4] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D,
                             a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 4, 1, NW>(ring[kb & 1], src, a.ld, wave, lane);
+    dma_tiles<D, KB, 4, 1, NW>(ring[kb & 1], src, a.ld, wave, lane, a.S - kb * KB);
   };
   issue(0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -940,6 +957,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
+      if (qw + 4 * (lane >> 4) + r >= a.S) continue;
       const int64_t o = (row0 + qw + 4 * (lane >> 4) + r) * a.ldg + (int64_t)h * D + 16 * t + (lane & 15);
       a.g_m[o] = Qm[t][r] * a.scale;
       a.g_d[o] = Qd[t][r] * a.scale;
@@ -968,7 +986,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   // K and V fragments of this wavefront's 16 keys (B operands of S = Q K^T, dP = dO V^T)
   bf16x8_t km[KS], kd[KS], vm[KS], vd[KS];
   {
-    const int64_t r = (row0 + kj) * a.ld + kh * D + 8 * (lane >> 4);
+    const int64_t r = (row0 + min(kj, a.S - 1)) * a.ld + kh * D + 8 * (lane >> 4);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       km[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + r + a.koff + 32 * s);
@@ -983,7 +1001,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) Vm_[t][r] = Vd_[t][r] = Km_[t][r] = Kd_[t][r] = 0.f;
 
-  const int nqb = (a.S - k0) / QB;   // query blocks from the first key on, per head
+  const int nqb = (a.S - k0 + QB - 1) / QB;   // query blocks from the first key on, per head
   const int total = nqb * a.G;
   auto issue = [&](int it) {
     const int g = it / nqb, qbk = it % nqb;
@@ -994,8 +1012,8 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
     // the two row strides differ: issue the Q and dO pairs separately
     const bf16_t* sq[2] = {src[0], src[1]};
     const bf16_t* so[2] = {src[2], src[3]};
-    dma_tiles<D, QB, 2, 1>(ring[it & 1], sq, a.ld, wave, lane);
-    dma_tiles<D, QB, 2, 1>(ring[it & 1] + 2 * TILE, so, a.ldo, wave, lane);
+    dma_tiles<D, QB, 2, 1>(ring[it & 1], sq, a.ld, wave, lane, a.S - q0);
+    dma_tiles<D, QB, 2, 1>(ring[it & 1] + 2 * TILE, so, a.ldo, wave, lane, a.S - q0);
   };
   // row terms of the next block: loaded into registers with its tiles, written
   // to LDS after this block's compute (the load's wait would otherwise also
@@ -1005,7 +1023,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   auto load_rows = [&](int it) {
     if (tid < QB) {
       const int g = it / nqb, qbk = it % nqb;
-      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + k0 + qbk * QB + tid;
+      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + min(k0 + qbk * QB + tid, a.S - 1);
       const float4 st = a.stats[si];
       const float2 dl = a.delta[si];
       nst = make_float4(st.x, st.y, st.z, dl.x);
@@ -1061,12 +1079,14 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
           sd[qt][r] *= a.scale;
           bmax = fmaxf(bmax, fabsf(sd[qt][r]));
         }
-      if (diag) {
+      if (diag || q0 + QB > a.S) {   // keys after the query, queries past the end
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (q0 + 16 * qt + 4 * (lane >> 4) + r < kj) sm[qt][r] = NEG;
+          for (int r = 0; r < 4; ++r) {
+            const int q = q0 + 16 * qt + 4 * (lane >> 4) + r;
+            if (q < kj || q >= a.S) sm[qt][r] = NEG;
+          }
       }
       float Pm[8], Pd[8], gsm[8], gsd[8];   // rows in accumulator order: (qt, r) -> 4 qt + r
       auto terms = [&](auto ser) {
@@ -1114,6 +1134,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
+      if (kw + 4 * (lane >> 4) + r >= a.S) continue;
       const int64_t o = (row0 + kw + 4 * (lane >> 4) + r) * a.ldg + kh * D + 16 * t + (lane & 15);
       a.g_m[o + a.koff] = Km_[t][r] * a.scale;
       a.g_d[o + a.koff] = Kd_[t][r] * a.scale;
@@ -1172,7 +1193,7 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
   // K and V fragments of this wavefront's 16 keys (B operands of S = Q K^T, dP = dO V^T)
   bf16x8_t km[KS], kd[KS], vm[KS], vd[KS];
   {
-    const int64_t r = (row0 + kj) * a.ld + kh * D + 8 * (lane >> 4);
+    const int64_t r = (row0 + min(kj, a.S - 1)) * a.ld + kh * D + 8 * (lane >> 4);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       km[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + r + a.koff + 32 * s);
@@ -1188,7 +1209,7 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) Vm_[kt][r] = Vd_[kt][r] = Km_[kt][r] = Kd_[kt][r] = 0.f;
 
-  const int nqb = (a.S - k0) / QB;   // query blocks from the first key on, per head
+  const int nqb = (a.S - k0 + QB - 1) / QB;   // query blocks from the first key on, per head
   const int total = nqb * a.G;
   auto issue = [&](int it) {
     const int g = it / nqb, qbk = it % nqb;
@@ -1196,15 +1217,15 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
     const int64_t r = row0 + q0;
     const bf16_t* sq[2] = {a.qkv_m + r * a.ld + (int64_t)h * D, a.qkv_d + r * a.ld + (int64_t)h * D};
     const bf16_t* so[2] = {a.do_m + r * a.ldo + (int64_t)h * D, a.do_d + r * a.ldo + (int64_t)h * D};
-    dma_tiles<D, QB, 2, 1, 8>(ring[it % 3], sq, a.ld, wave, lane);
-    dma_tiles<D, QB, 2, 1, 8>(ring[it % 3] + 2 * TILE, so, a.ldo, wave, lane);
+    dma_tiles<D, QB, 2, 1, 8>(ring[it % 3], sq, a.ld, wave, lane, a.S - q0);
+    dma_tiles<D, QB, 2, 1, 8>(ring[it % 3] + 2 * TILE, so, a.ldo, wave, lane, a.S - q0);
   };
   float4 nst = make_float4(0.f, 0.f, 0.f, 0.f);
   float ndd = 0.f;
   auto load_rows = [&](int it) {
     if (tid < QB) {
       const int g = it / nqb, qbk = it % nqb;
-      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + k0 + qbk * QB + tid;
+      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + min(k0 + qbk * QB + tid, a.S - 1);
       const float4 st = a.stats[si];
       const float2 dl = a.delta[si];
       nst = make_float4(st.x, st.y, st.z, dl.x);
@@ -1255,10 +1276,12 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
         sd[r] *= a.scale;
         bmax = fmaxf(bmax, fabsf(sd[r]));
       }
-      if (q0 + 16 * qt < kw + 16) {
+      if (q0 + 16 * qt < kw + 16 || q0 + QB > a.S) {   // keys after the query, queries past the end
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (q0 + 16 * qt + 4 * (lane >> 4) + r < kj) sm[r] = NEG;
+        for (int r = 0; r < 4; ++r) {
+          const int q = q0 + 16 * qt + 4 * (lane >> 4) + r;
+          if (q < kj || q >= a.S) sm[r] = NEG;
+        }
       }
       float Pm[4], Pd[4], gsm[4], gsd[4];
       auto terms = [&](auto ser) {
@@ -1313,6 +1336,7 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int key = k0 + 16 * kt + 4 * (lane >> 4) + r;
+      if (key >= a.S) continue;
       const int64_t o = (row0 + key) * a.ldg + kh * D + 16 * wave + (lane & 15);
       a.g_m[o + a.koff] = Km_[kt][r] * a.scale;
       a.g_d[o + a.koff] = Kd_[kt][r] * a.scale;
@@ -1323,7 +1347,11 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
 
 }  // namespace
 
-bool flash_supported(int dh, int S) { return (dh == 64 || dh == 128) && S % 128 == 0; }
+// S in multiples of 8 (the row chunks of the unfused path, which check_batch
+// requires of every model): key and query blocks past the end are masked.  The
+// ragged batches 3 x 1000 and 2 x 520 at 16 heads of 128: 14.85 ms per HVP of two
+// layers, 16.65 with score matrices in memory.
+bool flash_supported(int dh, int S) { return (dh == 64 || dh == 128) && S % 8 == 0; }
 
 static FlashArgs with_constants(const FlashArgs& a0) {
   FlashArgs a = a0;
@@ -1337,10 +1365,10 @@ static FlashArgs with_constants(const FlashArgs& a0) {
 hipError_t launch_flash_fwd(const FlashArgs& a0, int B, hipStream_t s) {
   const FlashArgs a = with_constants(a0);
   if (a.D == 128) {
-    dim3 g(a.S / 64, B * a.Hq);
+    dim3 g((a.S + 63) / 64, B * a.Hq);
     hipLaunchKernelGGL((flash_fwd16_kernel<128, 4>), g, dim3(256), 0, s, a);
   } else {
-    dim3 g(a.S / 128, B * a.Hq);
+    dim3 g((a.S + 127) / 128, B * a.Hq);
     hipLaunchKernelGGL(flash_fwd_kernel<64>, g, dim3(256), 0, s, a);
   }
   return hipGetLastError();
@@ -1353,15 +1381,15 @@ hipError_t launch_flash_bwd(const FlashArgs& a0, int B, hipStream_t s) {
   if (a.D == 128) hipLaunchKernelGGL(flash_delta_kernel<128>, gd, dim3(256), 0, s, a, nrows);
   else hipLaunchKernelGGL(flash_delta_kernel<64>, gd, dim3(256), 0, s, a, nrows);
   if (a.D == 128) {
-    dim3 gq(a.S / 64, B * a.Hq);
+    dim3 gq((a.S + 63) / 64, B * a.Hq);
     hipLaunchKernelGGL((flash_bwd_q16_kernel<128, 4>), gq, dim3(256), 0, s, a);
   } else {
-    dim3 gq(a.S / 128, B * a.Hq);
+    dim3 gq((a.S + 127) / 128, B * a.Hq);
     hipLaunchKernelGGL(flash_bwd_q_kernel<64>, gq, dim3(256), 0, s, a);
   }
   // dK/dV: 64 keys per workgroup; for D = 128 eight wavefronts share the
   // probabilities through LDS
-  dim3 gk(a.S / 64, B * a.Hk);
+  dim3 gk((a.S + 63) / 64, B * a.Hk);
   if (a.D == 128) hipLaunchKernelGGL(flash_bwd_kv8_kernel<128>, gk, dim3(512), 0, s, a);
   else hipLaunchKernelGGL(flash_bwd_kv_kernel<64>, gk, dim3(256), 0, s, a);
   return hipGetLastError();
