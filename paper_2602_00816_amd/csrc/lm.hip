@@ -390,7 +390,9 @@ __global__ __launch_bounds__(NTH) void norm_bwd_kernel(PairF dx, PairT<T> dxo, c
 // barrier per row and a quarter of the reductions per element (8192 x 1024 with
 // LayerNorm: 65 us against 118, 8192 x 2048: 130 against 148).  x is kept in
 // registers, dy read again from the caches (keeping it too cost 100 and 188 us).
-// Column sums in fp32 in LDS, at most 4 rows per wavefront.
+// Column sums in LDS, at most 4 rows per wavefront: gain and bias terms in fp32,
+// the outputs' half differences in fp64 (as the pass over the stored outputs,
+// which they replace, added them).
 template <typename T, int CPL, bool LN, bool OS>
 __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd,
                                                            const float* xm, const float* xd, const float* dym,
@@ -398,15 +400,20 @@ __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(PairF dx, PairT<T> dx
                                                            const float* vg, double eps, double neps, double* part) {
   constexpr int DM = 256 * CPL;
   // per-wavefront column sums (gain, bias, outputs); a lane only touches its own columns
-  constexpr int NS = 1 + (LN ? 1 : 0) + (OS ? 1 : 0);
+  constexpr int NF = 1 + (LN ? 1 : 0), NS = NF + (OS ? 1 : 0);
   // (rows of 2048: two workgroups per CU by LDS; with more, the second read of dy
   // misses the L2: 158 us against 130)
-  constexpr int NL = DM >= 2048 && NS < 2 ? 2 : NS;
+  constexpr int NL = DM >= 2048 && NS < 2 ? 2 : NF;
   __shared__ float cs[NL][4][DM];
+  __shared__ __attribute__((aligned(16))) double so[OS ? 4 : 1][OS ? DM : 2];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int n = 0; n < NS; ++n)
+  for (int n = 0; n < NF; ++n)
     for (int c = 0; c < CPL; ++c)
       *reinterpret_cast<float4*>(&cs[n][wave][256 * c + 4 * lane]) = make_float4(0.f, 0.f, 0.f, 0.f);
+  if constexpr (OS)
+    for (int c = 0; c < CPL; ++c)
+      for (int e = 0; e < 4; e += 2)
+        *reinterpret_cast<double2*>(&so[wave][256 * c + 4 * lane + e]) = make_double2(0.0, 0.0);
   auto ld = [](const float* p, int64_t i) { return *reinterpret_cast<const float4*>(p + i); };
   const int r0 = blockIdx.x * NORM_WAVE_ROWS;
   for (int i = wave; i < NORM_WAVE_ROWS; i += 4) {
@@ -528,16 +535,24 @@ __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(PairF dx, PairT<T> dx
       };
       add(0, tg[0], tg[1], tg[2], tg[3]);
       if constexpr (LN) add(1, yb.x, yb.y, yb.z, yb.w);
-      if constexpr (OS) add(NS - 1, od[0], od[1], od[2], od[3]);
+      if constexpr (OS)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          double2* q = reinterpret_cast<double2*>(&so[wave][col + e]);
+          const double2 v = *q;
+          *q = make_double2(v.x + (double)od[e], v.y + (double)od[e + 1]);
+        }
     }
   }
   // the four wavefronts' column sums, added in fp64 in wavefront order
   __syncthreads();
   double* p = part + (int64_t)blockIdx.x * NS * DM;
-  for (int j = threadIdx.x; j < DM; j += NT)
+  for (int j = threadIdx.x; j < DM; j += NT) {
 #pragma unroll
-    for (int n = 0; n < NS; ++n)
+    for (int n = 0; n < NF; ++n)
       p[n * DM + j] = (double)cs[n][0][j] + (double)cs[n][1][j] + (double)cs[n][2][j] + (double)cs[n][3][j];
+    if constexpr (OS) p[NF * DM + j] = so[0][j] + so[1][j] + so[2][j] + so[3][j];
+  }
 }
 
 // ---- column sums ---------------------------------------------------------------
