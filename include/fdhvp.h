@@ -195,8 +195,8 @@ fdh_status fdh_bind(fdh_ctx* ctx, const void* params_dev, const int32_t* tokens_
  * the result is the HVP of the token-weighted mean loss
  * sum_b w_b L_b / sum_b w_b (L_b the mean over batch b's targets), and with
  * FDH_REDUCE_SUM that of the summed loss.  Batches may differ in B and S,
- * each within the workspace plan (and S a multiple of 128 where the plan uses
- * fused attention and the planned S is one).  Padding is taken to sit after the real tokens (right
+ * each within the workspace plan (a plan with fused attention for S a multiple
+ * of 128 takes no other lengths).  Padding is taken to sit after the real tokens (right
  * padding) with label -100: causal attention then keeps it out of every kept
  * target's context, so no attention mask is needed.  The batch array is
  * copied, the device pointers are kept (not copied) and must stay valid.

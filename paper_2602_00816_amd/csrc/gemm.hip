@@ -1,10 +1,12 @@
 // Batched bf16 MFMA GEMM for gfx950:  C[z] = alpha * sum_p A_p[z] B_p[z]^T (+ epilogue).
 // (fp32 operands: gemm_f32.hip.)
 //
-// Two register-staged kernels, and below them the ones fed by direct loads to LDS:
+// Products run on the ring kernels (gemm_bf16_ring, fed by direct loads to LDS).
+// The others are reached by their tile number alone (GemmArgs::tile) and are what
+// the tests compare the ring kernels with, two of them register-staged:
 //  * gemm_kernel  - 128x128 workgroup tile, 4 wavefronts of 64x64 (2x2 blocks
-//    of 32x32 MFMA accumulators, v_mfma_f32_32x32x16_bf16); used for small problems.
-//  * gemm_bf16_big - bf16 only, 256x256 (8 wavefronts) or 256x128 (4
+//    of 32x32 MFMA accumulators, v_mfma_f32_32x32x16_bf16).
+//  * gemm_bf16_big - 256x256 (8 wavefronts) or 256x128 (4
 //    wavefronts) workgroup tiles; every wavefront owns 128x64 as 4x2 blocks of
 //    32x32, so one A fragment read from LDS feeds two MFMAs and one B fragment
 //    four.  K tile 64, LDS double-buffered, one barrier per K tile.
