@@ -393,8 +393,10 @@ __global__ __launch_bounds__(NTH) void norm_bwd_kernel(PairF dx, PairT<T> dxo, c
 // Column sums in LDS, at most 4 rows per wavefront: gain and bias terms in fp32,
 // the outputs' half differences in fp64 (as the pass over the stored outputs,
 // which they replace, added them).
+// Two wavefronts per SIMD asked for (at 2048 columns the compiler otherwise takes
+// more registers than leave room for the second: 168 us against 134).
 template <typename T, int CPL, bool LN, bool OS>
-__global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd,
+__global__ __launch_bounds__(NT, 2) void norm_bwd_wave_kernel(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd,
                                                            const float* xm, const float* xd, const float* dym,
                                                            const float* dyd, int rows, const T* thg,
                                                            const float* vg, double eps, double neps, double* part) {
