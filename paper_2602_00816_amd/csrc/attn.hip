@@ -232,7 +232,7 @@ __device__ inline void work_item(int nhead, int& blk, int& head) {
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, bool RG>
 __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
   constexpr int KB = 32, KS = D / 16, NT = D / 32, TILE = KB * D;
   // K is one block ahead of V: iteration kb forms the scores of block kb + 1
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
   const int q0 = qb * 128, qw = q0 + 32 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 31);
-  const int qc = min(qi, a.S - 1);   // (a query past the end computes the last one again and stores nothing)
+  const int qc = RG ? min(qi, a.S - 1) : qi;   // (a query past the end computes the last one again and stores nothing)
 
   // Q fragments (B operand of S^T = K Q^T), both points' halves
   bf16x8_t qm[KS], qd[KS];
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
     for (int r = 0; r < 16; ++r) Ac[t][r] = X[t][r] = 0.f;
   float zc = 0.f, zs = 0.f;
 
-  const int nkb = min((q0 + 128) / KB, (a.S + KB - 1) / KB);
+  const int nkb = RG ? min((q0 + 128) / KB, (a.S + KB - 1) / KB) : (q0 + 128) / KB;
   const int lastw = qw / KB;   // this wavefront's diagonal block
   constexpr float LOG2E = 1.4426950408889634f;
   // block j of K (or V) into stage j % R; past the last block the last block
@@ -286,13 +286,13 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
     const int jb = min(j, nkb - 1);
     const int64_t r = row0 + (int64_t)jb * KB;
     const bf16_t* src[2] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D};
-    dma_tiles<D, KB, 2>(kring[j % R], src, a.ld, wave, lane, a.S - jb * KB);
+    dma_tiles<D, KB, 2>(kring[j % R], src, a.ld, wave, lane, RG ? a.S - jb * KB : KB);
   };
   auto issue_v = [&](int j) {
     const int jb = min(j, nkb - 1);
     const int64_t r = row0 + (int64_t)jb * KB;
     const bf16_t* src[2] = {a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 2>(vring[j % R], src, a.ld, wave, lane, a.S - jb * KB);
+    dma_tiles<D, KB, 2>(vring[j % R], src, a.ld, wave, lane, RG ? a.S - jb * KB : KB);
   };
   // raw scores of the block in kring[st]: sm = K.m q.m, sd = K.m q.d + K.d q.m
   auto scores = [&](int st, f32x16_t& sm, f32x16_t& sd) {
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
   zs += __shfl_xor(zs, 32, 64);
   const float den = (zc - zs) * (zc + zs);
   const float u = zc / den, w = zs / den;
-  if (qi >= a.S) return;
+  if (RG && qi >= a.S) return;
   const int64_t orow = (row0 + qi) * a.ldo + (int64_t)h * D + 4 * (lane >> 5);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
 // sums are combined over the four lanes of a query with two shuffles.  Key
 // blocks wholly above a wavefront's queries are skipped.  At under 256
 // registers and 64 KB of LDS two workgroups share a CU.
-template <int D, int NW>
+template <int D, int NW, bool RG>
 __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   static_assert(D == 128, "16-query forward is for head dimension 128");
   constexpr int KB = 32, KS = D / 32, TILE = KB * D, QS = 16 * NW, NT = D / 16;
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   const int q0 = qb * QS, qw = q0 + 16 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 15);
-  const int qc = min(qi, a.S - 1);   // (a query past the end computes the last one again and stores nothing)
+  const int qc = RG ? min(qi, a.S - 1) : qi;   // (a query past the end computes the last one again and stores nothing)
 
   bf16x8_t qm[KS], qd[KS];   // B operands of S^T = K Q^T
   {
@@ -535,13 +535,13 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   constexpr float LOG2E = 1.4426950408889634f;
   float mrun = NEG;   // reference maximum of the scaled logits, moved lazily (see flash_fwd_kernel)
 
-  const int nkb = min((q0 + QS) / KB, (a.S + KB - 1) / KB);
+  const int nkb = RG ? min((q0 + QS) / KB, (a.S + KB - 1) / KB) : (q0 + QS) / KB;
   const int lastw = (qw + 15) / KB;   // this wavefront's last key block
   auto issue = [&](int kb) {
     const int64_t r = row0 + (int64_t)kb * KB;
     const bf16_t* src[4] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D,
                             a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 4, 1, NW>(ring[kb & 1], src, a.ld, wave, lane, a.S - kb * KB);
+    dma_tiles<D, KB, 4, 1, NW>(ring[kb & 1], src, a.ld, wave, lane, RG ? a.S - kb * KB : KB);
   };
   issue(0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -647,7 +647,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   zs += __shfl_xor(zs, 32, 64);
   const float den = (zc - zs) * (zc + zs);
   const float u = zc / den, w = zs / den;
-  if (qi >= a.S) return;
+  if (RG && qi >= a.S) return;
   const int64_t orow = (row0 + qi) * a.ldo + (int64_t)h * D + 4 * (lane >> 4);
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
@@ -699,7 +699,7 @@ __global__ __launch_bounds__(256) void flash_delta_kernel(FlashArgs a, int nrows
 // ---------------------------------------------------------------------------
 // backward: dQ
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, bool RG>
 __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
   constexpr int KB = 32, KS = D / 16, NT = D / 32, TILE = KB * D;
   __shared__ __attribute__((aligned(1024))) bf16_t ring[2][4 * TILE];   // K.m K.d V.m V.d
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
   const int q0 = qb * 128, qw = q0 + 32 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 31);
-  const int qc = min(qi, a.S - 1);   // (a query past the end computes the last one again and stores nothing)
+  const int qc = RG ? min(qi, a.S - 1) : qi;   // (a query past the end computes the last one again and stores nothing)
 
   bf16x8_t qm[KS], qd[KS], gm[KS], gd[KS];   // Q and dO fragments (B operands)
   {
@@ -735,13 +735,13 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) Qm[t][r] = Qd[t][r] = 0.f;
 
-  const int nkb = min((q0 + 128) / KB, (a.S + KB - 1) / KB);
+  const int nkb = RG ? min((q0 + 128) / KB, (a.S + KB - 1) / KB) : (q0 + 128) / KB;
   const int lastw = qw / KB;
   auto issue = [&](int kb) {
     const int64_t r = row0 + (int64_t)kb * KB;
     const bf16_t* src[4] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D,
                             a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 4>(ring[kb & 1], src, a.ld, wave, lane, a.S - kb * KB);
+    dma_tiles<D, KB, 4>(ring[kb & 1], src, a.ld, wave, lane, RG ? a.S - kb * KB : KB);
   };
   issue(0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -813,7 +813,7 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
     __syncthreads();
   }
 
-  if (qi >= a.S) return;
+  if (RG && qi >= a.S) return;
   const int64_t grow = (row0 + qi) * a.ldg + (int64_t)h * D + 4 * (lane >> 5);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -839,7 +839,7 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
 // So no exchange through LDS and one barrier per block.  Key blocks wholly
 // above a wavefront's queries are skipped.  About 220 registers: with four
 // wavefronts, two workgroups share a CU and their barriers are independent.
-template <int D, int NW>
+template <int D, int NW, bool RG>
 __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) {
   static_assert(D == 128, "16-query dQ is for head dimension 128");
   constexpr int KB = 32, KS = D / 32, TILE = KB * D, QS = 16 * NW, NT = D / 16;
@@ -854,7 +854,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
   const int q0 = qb * QS, qw = q0 + 16 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 15);
-  const int qc = min(qi, a.S - 1);   // (a query past the end computes the last one again and stores nothing)
+  const int qc = RG ? min(qi, a.S - 1) : qi;   // (a query past the end computes the last one again and stores nothing)
 
   bf16x8_t qm[KS], qd[KS], gm[KS], gd[KS];   // B operands of S^T = K Q^T, dP^T = V dO^T
   {
@@ -877,13 +877,13 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
 #pragma unroll
     for (int r = 0; r < 4; ++r) Qm[t][r] = Qd[t][r] = 0.f;
 
-  const int nkb = min((q0 + QS) / KB, (a.S + KB - 1) / KB);
+  const int nkb = RG ? min((q0 + QS) / KB, (a.S + KB - 1) / KB) : (q0 + QS) / KB;
   const int lastw = (qw + 15) / KB;   // this wavefront's last key block
   auto issue = [&](int kb) {
     const int64_t r = row0 + (int64_t)kb * KB;
     const bf16_t* src[4] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D,
                             a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 4, 1, NW>(ring[kb & 1], src, a.ld, wave, lane, a.S - kb * KB);
+    dma_tiles<D, KB, 4, 1, NW>(ring[kb & 1], src, a.ld, wave, lane, RG ? a.S - kb * KB : KB);
   };
   issue(0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -957,7 +957,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      if (qw + 4 * (lane >> 4) + r >= a.S) continue;
+      if (RG && qw + 4 * (lane >> 4) + r >= a.S) continue;
       const int64_t o = (row0 + qw + 4 * (lane >> 4) + r) * a.ldg + (int64_t)h * D + 16 * t + (lane & 15);
       a.g_m[o] = Qm[t][r] * a.scale;
       a.g_d[o] = Qd[t][r] * a.scale;
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
 // ---------------------------------------------------------------------------
 // backward: dK, dV (summed over the query heads that share the key/value head)
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, bool RG>
 __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   constexpr int QB = 32, KS = D / 32, NT = D / 16, TILE = QB * D;
   __shared__ __attribute__((aligned(1024))) bf16_t ring[2][4 * TILE];   // Q.m Q.d dO.m dO.d
@@ -986,7 +986,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   // K and V fragments of this wavefront's 16 keys (B operands of S = Q K^T, dP = dO V^T)
   bf16x8_t km[KS], kd[KS], vm[KS], vd[KS];
   {
-    const int64_t r = (row0 + min(kj, a.S - 1)) * a.ld + kh * D + 8 * (lane >> 4);
+    const int64_t r = (row0 + (RG ? min(kj, a.S - 1) : kj)) * a.ld + kh * D + 8 * (lane >> 4);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       km[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + r + a.koff + 32 * s);
@@ -1001,7 +1001,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) Vm_[t][r] = Vd_[t][r] = Km_[t][r] = Kd_[t][r] = 0.f;
 
-  const int nqb = (a.S - k0 + QB - 1) / QB;   // query blocks from the first key on, per head
+  const int nqb = (a.S - k0 + (RG ? QB - 1 : 0)) / QB;   // query blocks from the first key on, per head
   const int total = nqb * a.G;
   auto issue = [&](int it) {
     const int g = it / nqb, qbk = it % nqb;
@@ -1012,8 +1012,8 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
     // the two row strides differ: issue the Q and dO pairs separately
     const bf16_t* sq[2] = {src[0], src[1]};
     const bf16_t* so[2] = {src[2], src[3]};
-    dma_tiles<D, QB, 2, 1>(ring[it & 1], sq, a.ld, wave, lane, a.S - q0);
-    dma_tiles<D, QB, 2, 1>(ring[it & 1] + 2 * TILE, so, a.ldo, wave, lane, a.S - q0);
+    dma_tiles<D, QB, 2, 1>(ring[it & 1], sq, a.ld, wave, lane, RG ? a.S - q0 : QB);
+    dma_tiles<D, QB, 2, 1>(ring[it & 1] + 2 * TILE, so, a.ldo, wave, lane, RG ? a.S - q0 : QB);
   };
   // row terms of the next block: loaded into registers with its tiles, written
   // to LDS after this block's compute (the load's wait would otherwise also
@@ -1023,7 +1023,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   auto load_rows = [&](int it) {
     if (tid < QB) {
       const int g = it / nqb, qbk = it % nqb;
-      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + min(k0 + qbk * QB + tid, a.S - 1);
+      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + (RG ? min(k0 + qbk * QB + tid, a.S - 1) : k0 + qbk * QB + tid);
       const float4 st = a.stats[si];
       const float2 dl = a.delta[si];
       nst = make_float4(st.x, st.y, st.z, dl.x);
@@ -1079,13 +1079,13 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
           sd[qt][r] *= a.scale;
           bmax = fmaxf(bmax, fabsf(sd[qt][r]));
         }
-      if (diag || q0 + QB > a.S) {   // keys after the query, queries past the end
+      if (diag || (RG && q0 + QB > a.S)) {   // keys after the query, queries past the end
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int q = q0 + 16 * qt + 4 * (lane >> 4) + r;
-            if (q < kj || q >= a.S) sm[qt][r] = NEG;
+            if (q < kj || (RG && q >= a.S)) sm[qt][r] = NEG;
           }
       }
       float Pm[8], Pd[8], gsm[8], gsd[8];   // rows in accumulator order: (qt, r) -> 4 qt + r
@@ -1134,7 +1134,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      if (kw + 4 * (lane >> 4) + r >= a.S) continue;
+      if (RG && kw + 4 * (lane >> 4) + r >= a.S) continue;
       const int64_t o = (row0 + kw + 4 * (lane >> 4) + r) * a.ldg + kh * D + 16 * t + (lane & 15);
       a.g_m[o + a.koff] = Km_[t][r] * a.scale;
       a.g_d[o + a.koff] = Kd_[t][r] * a.scale;
@@ -1171,7 +1171,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
 // fixed per wavefront the writes of 32 lanes met only half of the banks, and
 // a quarter of the LDS cycles went to bank conflicts.
 
-template <int D>
+template <int D, bool RG>
 __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
   static_assert(D == 128, "eight-wavefront dK/dV is for head dimension 128");
   constexpr int QB = 32, KS = D / 32, TILE = QB * D, KEYS = 64;
@@ -1193,7 +1193,7 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
   // K and V fragments of this wavefront's 16 keys (B operands of S = Q K^T, dP = dO V^T)
   bf16x8_t km[KS], kd[KS], vm[KS], vd[KS];
   {
-    const int64_t r = (row0 + min(kj, a.S - 1)) * a.ld + kh * D + 8 * (lane >> 4);
+    const int64_t r = (row0 + (RG ? min(kj, a.S - 1) : kj)) * a.ld + kh * D + 8 * (lane >> 4);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       km[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + r + a.koff + 32 * s);
@@ -1209,7 +1209,7 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) Vm_[kt][r] = Vd_[kt][r] = Km_[kt][r] = Kd_[kt][r] = 0.f;
 
-  const int nqb = (a.S - k0 + QB - 1) / QB;   // query blocks from the first key on, per head
+  const int nqb = (a.S - k0 + (RG ? QB - 1 : 0)) / QB;   // query blocks from the first key on, per head
   const int total = nqb * a.G;
   auto issue = [&](int it) {
     const int g = it / nqb, qbk = it % nqb;
@@ -1217,15 +1217,15 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
     const int64_t r = row0 + q0;
     const bf16_t* sq[2] = {a.qkv_m + r * a.ld + (int64_t)h * D, a.qkv_d + r * a.ld + (int64_t)h * D};
     const bf16_t* so[2] = {a.do_m + r * a.ldo + (int64_t)h * D, a.do_d + r * a.ldo + (int64_t)h * D};
-    dma_tiles<D, QB, 2, 1, 8>(ring[it % 3], sq, a.ld, wave, lane, a.S - q0);
-    dma_tiles<D, QB, 2, 1, 8>(ring[it % 3] + 2 * TILE, so, a.ldo, wave, lane, a.S - q0);
+    dma_tiles<D, QB, 2, 1, 8>(ring[it % 3], sq, a.ld, wave, lane, RG ? a.S - q0 : QB);
+    dma_tiles<D, QB, 2, 1, 8>(ring[it % 3] + 2 * TILE, so, a.ldo, wave, lane, RG ? a.S - q0 : QB);
   };
   float4 nst = make_float4(0.f, 0.f, 0.f, 0.f);
   float ndd = 0.f;
   auto load_rows = [&](int it) {
     if (tid < QB) {
       const int g = it / nqb, qbk = it % nqb;
-      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + min(k0 + qbk * QB + tid, a.S - 1);
+      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + (RG ? min(k0 + qbk * QB + tid, a.S - 1) : k0 + qbk * QB + tid);
       const float4 st = a.stats[si];
       const float2 dl = a.delta[si];
       nst = make_float4(st.x, st.y, st.z, dl.x);
@@ -1276,11 +1276,11 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
         sd[r] *= a.scale;
         bmax = fmaxf(bmax, fabsf(sd[r]));
       }
-      if (q0 + 16 * qt < kw + 16 || q0 + QB > a.S) {   // keys after the query, queries past the end
+      if (q0 + 16 * qt < kw + 16 || (RG && q0 + QB > a.S)) {   // keys after the query, queries past the end
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int q = q0 + 16 * qt + 4 * (lane >> 4) + r;
-          if (q < kj || q >= a.S) sm[r] = NEG;
+          if (q < kj || (RG && q >= a.S)) sm[r] = NEG;
         }
       }
       float Pm[4], Pd[4], gsm[4], gsd[4];
@@ -1336,7 +1336,7 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int key = k0 + 16 * kt + 4 * (lane >> 4) + r;
-      if (key >= a.S) continue;
+      if (RG && key >= a.S) continue;
       const int64_t o = (row0 + key) * a.ldg + kh * D + 16 * wave + (lane & 15);
       a.g_m[o + a.koff] = Km_[kt][r] * a.scale;
       a.g_d[o + a.koff] = Kd_[kt][r] * a.scale;
@@ -1362,14 +1362,22 @@ static FlashArgs with_constants(const FlashArgs& a0) {
   return a;
 }
 
+// RG: the length is no multiple of the blocks.  Kernels of their own, because
+// the clamps and masks slow the aligned ones down.
+#define LAUNCH_RG(kernel, grid, block, lds, stream, args, ...)                                                        \
+  do {                                                                                                                \
+    if (args.S % 128) hipLaunchKernelGGL((kernel<__VA_ARGS__, true>), grid, block, lds, stream, args);               \
+    else hipLaunchKernelGGL((kernel<__VA_ARGS__, false>), grid, block, lds, stream, args);                           \
+  } while (0)
+
 hipError_t launch_flash_fwd(const FlashArgs& a0, int B, hipStream_t s) {
   const FlashArgs a = with_constants(a0);
   if (a.D == 128) {
     dim3 g((a.S + 63) / 64, B * a.Hq);
-    hipLaunchKernelGGL((flash_fwd16_kernel<128, 4>), g, dim3(256), 0, s, a);
+    LAUNCH_RG(flash_fwd16_kernel, g, dim3(256), 0, s, a, 128, 4);
   } else {
     dim3 g((a.S + 127) / 128, B * a.Hq);
-    hipLaunchKernelGGL(flash_fwd_kernel<64>, g, dim3(256), 0, s, a);
+    LAUNCH_RG(flash_fwd_kernel, g, dim3(256), 0, s, a, 64);
   }
   return hipGetLastError();
 }
@@ -1382,16 +1390,16 @@ hipError_t launch_flash_bwd(const FlashArgs& a0, int B, hipStream_t s) {
   else hipLaunchKernelGGL(flash_delta_kernel<64>, gd, dim3(256), 0, s, a, nrows);
   if (a.D == 128) {
     dim3 gq((a.S + 63) / 64, B * a.Hq);
-    hipLaunchKernelGGL((flash_bwd_q16_kernel<128, 4>), gq, dim3(256), 0, s, a);
+    LAUNCH_RG(flash_bwd_q16_kernel, gq, dim3(256), 0, s, a, 128, 4);
   } else {
     dim3 gq((a.S + 127) / 128, B * a.Hq);
-    hipLaunchKernelGGL(flash_bwd_q_kernel<64>, gq, dim3(256), 0, s, a);
+    LAUNCH_RG(flash_bwd_q_kernel, gq, dim3(256), 0, s, a, 64);
   }
   // dK/dV: 64 keys per workgroup; for D = 128 eight wavefronts share the
   // probabilities through LDS
   dim3 gk((a.S + 63) / 64, B * a.Hk);
-  if (a.D == 128) hipLaunchKernelGGL(flash_bwd_kv8_kernel<128>, gk, dim3(512), 0, s, a);
-  else hipLaunchKernelGGL(flash_bwd_kv_kernel<64>, gk, dim3(256), 0, s, a);
+  if (a.D == 128) LAUNCH_RG(flash_bwd_kv8_kernel, gk, dim3(512), 0, s, a, 128);
+  else LAUNCH_RG(flash_bwd_kv_kernel, gk, dim3(256), 0, s, a, 64);
   return hipGetLastError();
 }
 
