@@ -394,7 +394,8 @@ __global__ __launch_bounds__(NTH) void norm_bwd_kernel(PairF dx, PairT<T> dxo, c
 // the outputs' half differences in fp64 (as the pass over the stored outputs,
 // which they replace, added them).
 // Two wavefronts per SIMD asked for (at 2048 columns the compiler otherwise takes
-// more registers than leave room for the second: 168 us against 134).
+// more registers than leave room for the second: 168 us per call at 8192 x 2048
+// without LayerNorm, 126 with two).
 template <typename T, int CPL, bool LN, bool OS>
 __global__ __launch_bounds__(NT, 2) void norm_bwd_wave_kernel(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd,
                                                            const float* xm, const float* xd, const float* dym,
