@@ -60,9 +60,9 @@ fdh_status fdh_testing_gemm_channels(int32_t dtype, int32_t M, int32_t N, int32_
 
 /* on != 0 makes the next fdh_set_workspace plan the unfused attention path
  * (score, probability and score-gradient matrices in the workspace, MFMA
- * GEMMs and row kernels) even where the fused kernels apply (bf16 operands,
- * head dimension 64 or 128), so that the two paths can
- * be compared on one model. */
+ * GEMMs and row kernels) even where the fused kernels apply (bf16 operands;
+ * head dimension 128, or 64 with S a multiple of 128), so that the two paths
+ * can be compared on one model. */
 fdh_status fdh_testing_unfused_attention(fdh_ctx* ctx, int32_t on);
 
 /* Weight-gradient launch forms, so that they can be compared.  By default

@@ -160,17 +160,34 @@ __device__ inline f32x4_t mma16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
 // two-term series is exact to fp32 rounding (dropped terms b^4/120 and b^4/24
 // relative, below 4e-8), otherwise the exponential form is used.
 constexpr float SERIES_MAX = 1.f / 32.f;
-template <bool SERIES>
+template <bool SERIES, bool RG = false>
 __device__ inline void coshsinh(float b, float& c, float& s) {
   if constexpr (SERIES) {
     const float b2 = b * b;
     s = fmaf(b * b2, 1.f / 6.f, b);
     c = fmaf(b2, 0.5f, 1.f);
+  } else if constexpr (RG) {
+    s = sinhf(b);
+    c = coshf(b);
   } else {
     const float e = __expf(b), ie = __expf(-b);
     s = 0.5f * (e - ie);
     c = 0.5f * (e + ie);
   }
+}
+
+// The kernels of workspaces for lengths that are no multiple of 128 (RG, for any
+// length in multiples of 8) stand in for score matrices whose row sums and softmax gradient are formed in fp64, from the
+// library's exponentials: they form them in the same way (15.0 ms against 14.9
+// for the two-layer product below).  Their error against float64 is that of the
+// score matrices: 1.000 +- 0.001 of it over 69 products of random shapes, 0.998
+// +- 0.003 in the q and k gradients.
+template <bool RG>
+using Sum = std::conditional_t<RG, double, float>;
+template <bool RG>
+__device__ inline float exp_f(float x) {
+  if constexpr (RG) return expf(x);
+  else return __expf(x);
 }
 
 // Issue this wavefront's direct global-to-LDS loads of NTILE tiles of R rows
@@ -232,7 +249,7 @@ __device__ inline void work_item(int nhead, int& blk, int& head) {
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-template <int D, bool RG>
+template <int D>
 __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
   constexpr int KB = 32, KS = D / 16, NT = D / 32, TILE = KB * D;
   // K is one block ahead of V: iteration kb forms the scores of block kb + 1
@@ -252,12 +269,11 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
   const int q0 = qb * 128, qw = q0 + 32 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 31);
-  const int qc = RG ? min(qi, a.S - 1) : qi;   // (a query past the end computes the last one again and stores nothing)
 
   // Q fragments (B operand of S^T = K Q^T), both points' halves
   bf16x8_t qm[KS], qd[KS];
   {
-    const int64_t off = (row0 + qc) * a.ld + (int64_t)h * D + 8 * (lane >> 5);
+    const int64_t off = (row0 + qi) * a.ld + (int64_t)h * D + 8 * (lane >> 5);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       qm[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + off + 16 * s);
@@ -276,23 +292,21 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
     for (int r = 0; r < 16; ++r) Ac[t][r] = X[t][r] = 0.f;
   float zc = 0.f, zs = 0.f;
 
-  const int nkb = RG ? min((q0 + 128) / KB, (a.S + KB - 1) / KB) : (q0 + 128) / KB;
+  const int nkb = (q0 + 128) / KB;
   const int lastw = qw / KB;   // this wavefront's diagonal block
   constexpr float LOG2E = 1.4426950408889634f;
   // block j of K (or V) into stage j % R; past the last block the last block
   // is loaded again (never read), so every iteration issues the same number
   // of loads and the vmcnt waits are constants
   auto issue_k = [&](int j) {
-    const int jb = min(j, nkb - 1);
-    const int64_t r = row0 + (int64_t)jb * KB;
+    const int64_t r = row0 + (int64_t)min(j, nkb - 1) * KB;
     const bf16_t* src[2] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D};
-    dma_tiles<D, KB, 2>(kring[j % R], src, a.ld, wave, lane, RG ? a.S - jb * KB : KB);
+    dma_tiles<D, KB, 2>(kring[j % R], src, a.ld, wave, lane, KB);
   };
   auto issue_v = [&](int j) {
-    const int jb = min(j, nkb - 1);
-    const int64_t r = row0 + (int64_t)jb * KB;
+    const int64_t r = row0 + (int64_t)min(j, nkb - 1) * KB;
     const bf16_t* src[2] = {a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 2>(vring[j % R], src, a.ld, wave, lane, RG ? a.S - jb * KB : KB);
+    dma_tiles<D, KB, 2>(vring[j % R], src, a.ld, wave, lane, KB);
   };
   // raw scores of the block in kring[st]: sm = K.m q.m, sd = K.m q.d + K.d q.m
   auto scores = [&](int st, f32x16_t& sm, f32x16_t& sd) {
@@ -468,7 +482,6 @@ __global__ __launch_bounds__(256) void flash_fwd_kernel(FlashArgs a) {
   zs += __shfl_xor(zs, 32, 64);
   const float den = (zc - zs) * (zc + zs);
   const float u = zc / den, w = zs / den;
-  if (RG && qi >= a.S) return;
   const int64_t orow = (row0 + qi) * a.ldo + (int64_t)h * D + 4 * (lane >> 5);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -531,7 +544,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) Ac[t][r] = X[t][r] = 0.f;
-  float zc = 0.f, zs = 0.f;
+  Sum<RG> zc = 0, zs = 0;
   constexpr float LOG2E = 1.4426950408889634f;
   float mrun = NEG;   // reference maximum of the scaled logits, moved lazily (see flash_fwd_kernel)
 
@@ -585,7 +598,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
       amax = fmaxf(amax, __shfl_xor(amax, 32, 64));
       if (__any(amax > mrun + 8.f)) {
         const float mnew = fmaxf(mrun, amax);
-        const float alpha = __expf(mrun - mnew);
+        const float alpha = exp_f<RG>(mrun - mnew);
         mrun = mnew;
         zc *= alpha;
         zs *= alpha;
@@ -604,7 +617,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
         for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const float e = __builtin_amdgcn_exp2f(fmaf(sm[hf][r], a.c_exp, moff));
+            const float e = RG ? expf(fmaf(sm[hf][r], a.scale, -mrun)) : __builtin_amdgcn_exp2f(fmaf(sm[hf][r], a.c_exp, moff));
             const float q2 = sd[hf][r] * sd[hf][r];
             pc[hf][r] = e * fmaf(q2, a.c_cosh, 1.f);                  // e^a cosh b
             ps[hf][r] = e * (sd[hf][r] * fmaf(q2, a.c_sinh, a.scale));  // e^a sinh b
@@ -614,9 +627,9 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
         for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const float e = __builtin_amdgcn_exp2f(fmaf(sm[hf][r], a.c_exp, moff));
+            const float e = RG ? expf(fmaf(sm[hf][r], a.scale, -mrun)) : __builtin_amdgcn_exp2f(fmaf(sm[hf][r], a.c_exp, moff));
             float c, sn;
-            coshsinh<false>(sd[hf][r] * a.scale, c, sn);
+            coshsinh<false, RG>(sd[hf][r] * a.scale, c, sn);
             pc[hf][r] = e * c;
             ps[hf][r] = e * sn;
           }
@@ -645,8 +658,8 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
   zs += __shfl_xor(zs, 16, 64);
   zc += __shfl_xor(zc, 32, 64);
   zs += __shfl_xor(zs, 32, 64);
-  const float den = (zc - zs) * (zc + zs);
-  const float u = zc / den, w = zs / den;
+  const Sum<RG> den = (zc - zs) * (zc + zs);
+  const Sum<RG> u = zc / den, w = zs / den;
   if (RG && qi >= a.S) return;
   const int64_t orow = (row0 + qi) * a.ldo + (int64_t)h * D + 4 * (lane >> 4);
 #pragma unroll
@@ -654,20 +667,20 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_fwd16_kernel(FlashArgs a) {
     uint16_t om[4], od[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      om[r] = f32_to_bf16(u * Ac[t][r]);
-      od[r] = f32_to_bf16(u * X[t][r] - w * Ac[t][r]);
+      om[r] = f32_to_bf16((float)(u * Ac[t][r]));
+      od[r] = f32_to_bf16((float)(u * X[t][r] - w * Ac[t][r]));
     }
     const int64_t o = orow + 16 * t;
     *reinterpret_cast<uint2*>(a.o_m + o) = make_uint2(om[0] | ((uint32_t)om[1] << 16), om[2] | ((uint32_t)om[3] << 16));
     *reinterpret_cast<uint2*>(a.o_d + o) = make_uint2(od[0] | ((uint32_t)od[1] << 16), od[2] | ((uint32_t)od[3] << 16));
   }
-  if (lane < 16) a.stats[(int64_t)bh * a.S + qi] = make_float4(mrun, u, w, 0.f);
+  if (lane < 16) a.stats[(int64_t)bh * a.S + qi] = make_float4(mrun, (float)u, (float)w, 0.f);
 }
 
 // ---------------------------------------------------------------------------
 // backward: row terms D.m, D.d
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, bool RG>
 __global__ __launch_bounds__(256) void flash_delta_kernel(FlashArgs a, int nrows) {
   // 16 lanes per (token, head) row; D / 16 elements per lane
   constexpr int E = D / 16;
@@ -677,11 +690,11 @@ __global__ __launch_bounds__(256) void flash_delta_kernel(FlashArgs a, int nrows
   const int64_t t = row / a.Hq;
   const int h = (int)(row % a.Hq);
   const int64_t off = t * a.ldo + (int64_t)h * D + sub * E;
-  float dm = 0.f, dd = 0.f;
+  Sum<RG> dm = 0, dd = 0;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const float om = bf16_to_f32(a.o_m[off + e]), od = bf16_to_f32(a.o_d[off + e]);
-    const float gm = bf16_to_f32(a.do_m[off + e]), gd = bf16_to_f32(a.do_d[off + e]);
+    const Sum<RG> om = bf16_to_f32(a.o_m[off + e]), od = bf16_to_f32(a.o_d[off + e]);
+    const Sum<RG> gm = bf16_to_f32(a.do_m[off + e]), gd = bf16_to_f32(a.do_d[off + e]);
     dm += gm * om + gd * od;
     dd += gm * od + gd * om;
   }
@@ -692,14 +705,14 @@ __global__ __launch_bounds__(256) void flash_delta_kernel(FlashArgs a, int nrows
   }
   if (sub == 0) {
     const int b = (int)(t / a.S), i = (int)(t % a.S);
-    a.delta[((int64_t)b * a.Hq + h) * a.S + i] = make_float2(dm, dd);
+    a.delta[((int64_t)b * a.Hq + h) * a.S + i] = make_float2((float)dm, (float)dd);
   }
 }
 
 // ---------------------------------------------------------------------------
 // backward: dQ
 // ---------------------------------------------------------------------------
-template <int D, bool RG>
+template <int D>
 __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
   constexpr int KB = 32, KS = D / 16, NT = D / 32, TILE = KB * D;
   __shared__ __attribute__((aligned(1024))) bf16_t ring[2][4 * TILE];   // K.m K.d V.m V.d
@@ -713,12 +726,11 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
   const int q0 = qb * 128, qw = q0 + 32 * wave;
   const int64_t row0 = (int64_t)b * a.S;
   const int qi = qw + (lane & 31);
-  const int qc = RG ? min(qi, a.S - 1) : qi;   // (a query past the end computes the last one again and stores nothing)
 
   bf16x8_t qm[KS], qd[KS], gm[KS], gd[KS];   // Q and dO fragments (B operands)
   {
-    const int64_t off = (row0 + qc) * a.ld + (int64_t)h * D + 8 * (lane >> 5);
-    const int64_t offo = (row0 + qc) * a.ldo + (int64_t)h * D + 8 * (lane >> 5);
+    const int64_t off = (row0 + qi) * a.ld + (int64_t)h * D + 8 * (lane >> 5);
+    const int64_t offo = (row0 + qi) * a.ldo + (int64_t)h * D + 8 * (lane >> 5);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       qm[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + off + 16 * s);
@@ -727,21 +739,21 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
       gd[s] = *reinterpret_cast<const bf16x8_t*>(a.do_d + offo + 16 * s);
     }
   }
-  const float4 st = a.stats[(int64_t)bh * a.S + qc];
-  const float2 dl = a.delta[(int64_t)bh * a.S + qc];
+  const float4 st = a.stats[(int64_t)bh * a.S + qi];
+  const float2 dl = a.delta[(int64_t)bh * a.S + qi];
   f32x16_t Qm[NT], Qd[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) Qm[t][r] = Qd[t][r] = 0.f;
 
-  const int nkb = RG ? min((q0 + 128) / KB, (a.S + KB - 1) / KB) : (q0 + 128) / KB;
+  const int nkb = (q0 + 128) / KB;
   const int lastw = qw / KB;
   auto issue = [&](int kb) {
     const int64_t r = row0 + (int64_t)kb * KB;
     const bf16_t* src[4] = {a.qkv_m + r * a.ld + a.koff + kh * D, a.qkv_d + r * a.ld + a.koff + kh * D,
                             a.qkv_m + r * a.ld + a.voff + kh * D, a.qkv_d + r * a.ld + a.voff + kh * D};
-    dma_tiles<D, KB, 4>(ring[kb & 1], src, a.ld, wave, lane, RG ? a.S - kb * KB : KB);
+    dma_tiles<D, KB, 4>(ring[kb & 1], src, a.ld, wave, lane, KB);
   };
   issue(0);
   __builtin_amdgcn_s_waitcnt(0);
@@ -813,7 +825,6 @@ __global__ __launch_bounds__(256) void flash_bwd_q_kernel(FlashArgs a) {
     __syncthreads();
   }
 
-  if (RG && qi >= a.S) return;
   const int64_t grow = (row0 + qi) * a.ldg + (int64_t)h * D + 4 * (lane >> 5);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -928,13 +939,13 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
         auto terms = [&](auto ser) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const float e = __expf(sm[r] - st.x);
+            const Sum<RG> e = exp_f<RG>(sm[r] - st.x), u = st.y, w = st.z;
             float c, sn;
-            coshsinh<decltype(ser)::value>(sd[r], c, sn);
-            const float Pm = e * (c * st.y - sn * st.z), Pd = e * (sn * st.y - c * st.z);
-            const float xm = pm[r] - dl.x, xd = pd[r] - dl.y;
-            gsm[hf][r] = Pm * xm + Pd * xd;
-            gsd[hf][r] = Pm * xd + Pd * xm;
+            coshsinh<decltype(ser)::value, RG>(sd[r], c, sn);
+            const Sum<RG> Pm = e * (c * u - sn * w), Pd = e * (sn * u - c * w);
+            const Sum<RG> xm = pm[r] - (Sum<RG>)dl.x, xd = pd[r] - (Sum<RG>)dl.y;
+            gsm[hf][r] = (float)(Pm * xm + Pd * xd);
+            gsd[hf][r] = (float)(Pm * xd + Pd * xm);
           }
         };
         if (!__any(bmax >= SERIES_MAX)) terms(std::true_type{});
@@ -967,7 +978,7 @@ __global__ __launch_bounds__(64 * NW, 2) void flash_bwd_q16_kernel(FlashArgs a) 
 // ---------------------------------------------------------------------------
 // backward: dK, dV (summed over the query heads that share the key/value head)
 // ---------------------------------------------------------------------------
-template <int D, bool RG>
+template <int D>
 __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   constexpr int QB = 32, KS = D / 32, NT = D / 16, TILE = QB * D;
   __shared__ __attribute__((aligned(1024))) bf16_t ring[2][4 * TILE];   // Q.m Q.d dO.m dO.d
@@ -986,7 +997,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   // K and V fragments of this wavefront's 16 keys (B operands of S = Q K^T, dP = dO V^T)
   bf16x8_t km[KS], kd[KS], vm[KS], vd[KS];
   {
-    const int64_t r = (row0 + (RG ? min(kj, a.S - 1) : kj)) * a.ld + kh * D + 8 * (lane >> 4);
+    const int64_t r = (row0 + kj) * a.ld + kh * D + 8 * (lane >> 4);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       km[s] = *reinterpret_cast<const bf16x8_t*>(a.qkv_m + r + a.koff + 32 * s);
@@ -1001,7 +1012,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) Vm_[t][r] = Vd_[t][r] = Km_[t][r] = Kd_[t][r] = 0.f;
 
-  const int nqb = (a.S - k0 + (RG ? QB - 1 : 0)) / QB;   // query blocks from the first key on, per head
+  const int nqb = (a.S - k0) / QB;   // query blocks from the first key on, per head
   const int total = nqb * a.G;
   auto issue = [&](int it) {
     const int g = it / nqb, qbk = it % nqb;
@@ -1012,8 +1023,8 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
     // the two row strides differ: issue the Q and dO pairs separately
     const bf16_t* sq[2] = {src[0], src[1]};
     const bf16_t* so[2] = {src[2], src[3]};
-    dma_tiles<D, QB, 2, 1>(ring[it & 1], sq, a.ld, wave, lane, RG ? a.S - q0 : QB);
-    dma_tiles<D, QB, 2, 1>(ring[it & 1] + 2 * TILE, so, a.ldo, wave, lane, RG ? a.S - q0 : QB);
+    dma_tiles<D, QB, 2, 1>(ring[it & 1], sq, a.ld, wave, lane, QB);
+    dma_tiles<D, QB, 2, 1>(ring[it & 1] + 2 * TILE, so, a.ldo, wave, lane, QB);
   };
   // row terms of the next block: loaded into registers with its tiles, written
   // to LDS after this block's compute (the load's wait would otherwise also
@@ -1023,7 +1034,7 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   auto load_rows = [&](int it) {
     if (tid < QB) {
       const int g = it / nqb, qbk = it % nqb;
-      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + (RG ? min(k0 + qbk * QB + tid, a.S - 1) : k0 + qbk * QB + tid);
+      const int64_t si = ((int64_t)b * a.Hq + kh * a.G + g) * a.S + k0 + qbk * QB + tid;
       const float4 st = a.stats[si];
       const float2 dl = a.delta[si];
       nst = make_float4(st.x, st.y, st.z, dl.x);
@@ -1079,14 +1090,12 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
           sd[qt][r] *= a.scale;
           bmax = fmaxf(bmax, fabsf(sd[qt][r]));
         }
-      if (diag || (RG && q0 + QB > a.S)) {   // keys after the query, queries past the end
+      if (diag) {
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int q = q0 + 16 * qt + 4 * (lane >> 4) + r;
-            if (q < kj || (RG && q >= a.S)) sm[qt][r] = NEG;
-          }
+          for (int r = 0; r < 4; ++r)
+            if (q0 + 16 * qt + 4 * (lane >> 4) + r < kj) sm[qt][r] = NEG;
       }
       float Pm[8], Pd[8], gsm[8], gsd[8];   // rows in accumulator order: (qt, r) -> 4 qt + r
       auto terms = [&](auto ser) {
@@ -1134,7 +1143,6 @@ __global__ __launch_bounds__(256) void flash_bwd_kv_kernel(FlashArgs a) {
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      if (RG && kw + 4 * (lane >> 4) + r >= a.S) continue;
       const int64_t o = (row0 + kw + 4 * (lane >> 4) + r) * a.ldg + kh * D + 16 * t + (lane & 15);
       a.g_m[o + a.koff] = Km_[t][r] * a.scale;
       a.g_d[o + a.koff] = Kd_[t][r] * a.scale;
@@ -1290,15 +1298,15 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
         for (int r = 0; r < 4; ++r) {
           const float4 st = sst[it & 1][16 * qt + 4 * (lane >> 4) + r];
           const float dd = r == 0 ? ddv.x : (r == 1 ? ddv.y : (r == 2 ? ddv.z : ddv.w));
-          const float e = __expf(sm[r] - st.x);
+          const Sum<RG> e = exp_f<RG>(sm[r] - st.x), u = st.y, w = st.z;
           float c, sn;
-          coshsinh<decltype(ser)::value>(sd[r], c, sn);
-          const float P_m = e * (c * st.y - sn * st.z), P_d = e * (sn * st.y - c * st.z);
-          const float xm = pm[r] - st.w, xd = pd[r] - dd;
-          Pm[r] = P_m;
-          Pd[r] = P_d;
-          gsm[r] = P_m * xm + P_d * xd;
-          gsd[r] = P_m * xd + P_d * xm;
+          coshsinh<decltype(ser)::value, RG>(sd[r], c, sn);
+          const Sum<RG> P_m = e * (c * u - sn * w), P_d = e * (sn * u - c * w);
+          const Sum<RG> xm = pm[r] - (Sum<RG>)st.w, xd = pd[r] - (Sum<RG>)dd;
+          Pm[r] = (float)P_m;
+          Pd[r] = (float)P_d;
+          gsm[r] = (float)(P_m * xm + P_d * xd);
+          gsd[r] = (float)(P_m * xd + P_d * xm);
         }
       };
       if (!__any(bmax >= SERIES_MAX)) terms(std::true_type{});
@@ -1347,11 +1355,14 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_kv8_kernel(FlashArgs a) {
 
 }  // namespace
 
-// S in multiples of 8 (the row chunks of the unfused path, which check_batch
-// requires of every model): key and query blocks past the end are masked.  The
-// ragged batches 3 x 1000 and 2 x 520 at 16 heads of 128: 14.85 ms per HVP of two
-// layers, 16.65 with score matrices in memory.
-bool flash_supported(int dh, int S) { return (dh == 64 || dh == 128) && S % 8 == 0; }
+// 128-wide heads: S in multiples of 8 (the row chunks of the unfused path, which
+// check_batch requires of every model); key and query blocks past the end are
+// masked.  The ragged batches 3 x 1000 and 2 x 520 at 16 heads, two layers: 15.0 ms
+// per product, 16.7 with score matrices in memory.
+// 64-wide heads: S in multiples of 128.  Their kernels with masked ends had 1.01
+// (+- 0.002) of the score matrices' error in the q and k gradients of 86 GPT-2
+// products, so other lengths keep the score matrices.
+bool flash_supported(int dh, int S) { return dh == 128 ? S % 8 == 0 : dh == 64 && S % 128 == 0; }
 
 static FlashArgs with_constants(const FlashArgs& a0) {
   FlashArgs a = a0;
@@ -1362,44 +1373,48 @@ static FlashArgs with_constants(const FlashArgs& a0) {
   return a;
 }
 
-// RG: the length is no multiple of the blocks.  Kernels of their own, because
-// the clamps and masks slow the aligned ones down.
+// RG: clamps, masks and fp64 sums.  Kernels of their own, because the clamps and
+// masks alone slow the others down (forward 289 -> 294, dQ 391 ->
+// 399, dK/dV 611 -> 634 us at 4 x 2048 x 16 heads).
 #define LAUNCH_RG(kernel, grid, block, lds, stream, args, ...)                                                        \
   do {                                                                                                                \
-    if (args.S % 128) hipLaunchKernelGGL((kernel<__VA_ARGS__, true>), grid, block, lds, stream, args);               \
+    if (args.ragged) hipLaunchKernelGGL((kernel<__VA_ARGS__, true>), grid, block, lds, stream, args);               \
     else hipLaunchKernelGGL((kernel<__VA_ARGS__, false>), grid, block, lds, stream, args);                           \
   } while (0)
 
 hipError_t launch_flash_fwd(const FlashArgs& a0, int B, hipStream_t s) {
+  if (!flash_supported(a0.D, a0.S) || (a0.S % 128 && !a0.ragged)) return hipErrorInvalidValue;
   const FlashArgs a = with_constants(a0);
   if (a.D == 128) {
     dim3 g((a.S + 63) / 64, B * a.Hq);
     LAUNCH_RG(flash_fwd16_kernel, g, dim3(256), 0, s, a, 128, 4);
   } else {
-    dim3 g((a.S + 127) / 128, B * a.Hq);
-    LAUNCH_RG(flash_fwd_kernel, g, dim3(256), 0, s, a, 64);
+    dim3 g(a.S / 128, B * a.Hq);
+    hipLaunchKernelGGL(flash_fwd_kernel<64>, g, dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_flash_bwd(const FlashArgs& a0, int B, hipStream_t s) {
+  if (!flash_supported(a0.D, a0.S) || (a0.S % 128 && !a0.ragged)) return hipErrorInvalidValue;
   const FlashArgs a = with_constants(a0);
   const int nrows = B * a.S * a.Hq;
   dim3 gd((nrows + 15) / 16);
-  if (a.D == 128) hipLaunchKernelGGL(flash_delta_kernel<128>, gd, dim3(256), 0, s, a, nrows);
-  else hipLaunchKernelGGL(flash_delta_kernel<64>, gd, dim3(256), 0, s, a, nrows);
+  if (a.D == 64) hipLaunchKernelGGL((flash_delta_kernel<64, false>), gd, dim3(256), 0, s, a, nrows);
+  else if (a.ragged) hipLaunchKernelGGL((flash_delta_kernel<128, true>), gd, dim3(256), 0, s, a, nrows);
+  else hipLaunchKernelGGL((flash_delta_kernel<128, false>), gd, dim3(256), 0, s, a, nrows);
   if (a.D == 128) {
     dim3 gq((a.S + 63) / 64, B * a.Hq);
     LAUNCH_RG(flash_bwd_q16_kernel, gq, dim3(256), 0, s, a, 128, 4);
   } else {
-    dim3 gq((a.S + 127) / 128, B * a.Hq);
-    LAUNCH_RG(flash_bwd_q_kernel, gq, dim3(256), 0, s, a, 64);
+    dim3 gq(a.S / 128, B * a.Hq);
+    hipLaunchKernelGGL(flash_bwd_q_kernel<64>, gq, dim3(256), 0, s, a);
   }
   // dK/dV: 64 keys per workgroup; for D = 128 eight wavefronts share the
   // probabilities through LDS
   dim3 gk((a.S + 63) / 64, B * a.Hk);
   if (a.D == 128) LAUNCH_RG(flash_bwd_kv8_kernel, gk, dim3(512), 0, s, a, 128);
-  else LAUNCH_RG(flash_bwd_kv_kernel, gk, dim3(256), 0, s, a, 64);
+  else hipLaunchKernelGGL(flash_bwd_kv_kernel<64>, gk, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

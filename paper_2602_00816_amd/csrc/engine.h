@@ -77,8 +77,8 @@ struct WsLayout {
   Span lz_w, lz_q, lz_qp, lz_basis, lz_alpha, lz_beta, lz_coef, lz_gram, lz_partial, lz_flag, lz_maxabs;
   int64_t lz_ldq = 0;   // basis row stride (elements, multiple of 8)
   int lz_dev_rows = 0;  // basis rows held in the workspace
-  // attention path: fused kernels (bf16, head dim 64 or 128, S a multiple of
-  // 8) or score/probability matrices in the workspace
+  // attention path: fused kernels (bf16; head dim 128 and S a multiple of
+  // 8, or 64 and a multiple of 128) or score/probability matrices in the workspace
   bool fused = false;
   // activation recomputation: only each layer's input pair x_in is kept; the
   // other spans of every layer alias one shared set, which the backward refills

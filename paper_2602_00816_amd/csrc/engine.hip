@@ -582,6 +582,7 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     fa.S = S; fa.Hq = Hq; fa.Hk = Hk; fa.G = G; fa.D = dh;
     fa.koff = Hq * dh; fa.voff = (Hq + Hk) * dh;
     fa.scale = scale;
+    fa.ragged = planS % 128 != 0;
     fa.ldo = (int64_t)Hq * dh;
     return fa;
   };

@@ -193,6 +193,7 @@ struct FlashArgs {
   int S, Hq, Hk, G, D;   // G = Hq / Hk query heads per key/value head
   int koff, voff;
   float scale;           // 1 / sqrt(D)
+  bool ragged;           // a workspace for lengths that are no multiple of 128 (required for such an S)
   bf16_t* o_m;           // [T][ldo] attention output (forward), input of the backward
   bf16_t* o_d;
   int64_t ldo;
@@ -206,7 +207,7 @@ struct FlashArgs {
   // derived from scale by the launchers: scale log2(e), scale^2 / 2, scale^3 / 6
   float c_exp, c_cosh, c_sinh;
 };
-// head dimension 64 or 128, S a multiple of 8
+// head dimension 128 and S a multiple of 8, or 64 and S a multiple of 128
 bool flash_supported(int dh, int S);
 hipError_t launch_flash_fwd(const FlashArgs& a, int B, hipStream_t s);
 // row terms, dq (query columns of g) and dk, dv (key/value columns, summed over each group)
