@@ -58,6 +58,12 @@ fdh_status fdh_testing_gemm_channels(int32_t dtype, int32_t M, int32_t N, int32_
                                      float* C, float* C1, float alpha, void* scratch, size_t scratch_bytes,
                                      void* hip_stream);
 
+/* How fdh_testing_gemm_channels with both outputs would launch that product
+ * (host arithmetic only): out4 = output tile width, slices of 32 k per part of
+ * the contraction, parts of the two-pair and of the one-pair product. */
+fdh_status fdh_testing_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t batch, size_t scratch_bytes,
+                                 int32_t* out4);
+
 /* on != 0 makes the next fdh_set_workspace plan the unfused attention path
  * (score, probability and score-gradient matrices in the workspace, MFMA
  * GEMMs and row kernels) even where the fused kernels apply (bf16 operands;

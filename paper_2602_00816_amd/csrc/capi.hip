@@ -1,5 +1,6 @@
 // C ABI (include/fdhvp.h): argument validation and dispatch to the engine.
 // No exception crosses this boundary.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -430,6 +431,23 @@ extern "C" fdh_status fdh_testing_gemm_channels(int32_t dtype, int32_t M, int32_
   else if (dtype == FDH_F32) r = fdh::gemm<float>(g, n, sc, (hipStream_t)hip_stream);
   else return FDH_ERR_INVALID_ARG;
   return r == hipSuccess ? FDH_OK : FDH_ERR_HIP;
+}
+
+extern "C" fdh_status fdh_testing_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t batch,
+                                            size_t scratch_bytes, int32_t* out4) {
+  if (!out4 || M < 1 || N < 1 || K < 1 || batch < 1) return FDH_ERR_INVALID_ARG;
+  fdh::GemmArgs g[2];
+  for (int q = 0; q < 2; ++q) {
+    g[q].M = M; g[q].N = N; g[q].K = K; g[q].nbatch = batch;
+    g[q].ldc = N; g[q].c_outer = (int64_t)M * N;
+    g[q].npairs = 2 - q;
+  }
+  int32_t out[4];
+  if (dtype == FDH_BF16) fdh::gemm_plan<fdh::bf16_t>(g, 2, scratch_bytes, out);
+  else if (dtype == FDH_F32) fdh::gemm_plan<float>(g, 2, scratch_bytes, out);
+  else return FDH_ERR_INVALID_ARG;
+  std::copy(out, out + 4, out4);
+  return FDH_OK;
 }
 
 extern "C" fdh_status fdh_testing_unfused_attention(fdh_ctx* ctx, int32_t on) {

@@ -61,6 +61,12 @@ hipError_t gemm(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t str
 template <typename T>
 size_t gemm_scratch(const GemmArgs* g, int n, size_t most);
 
+// The plan of that launch on the host: tile width, slices of 32 k per part and
+// the parts of each product (tests).
+template <typename T>
+void gemm_plan(const GemmArgs* g, int n, size_t scratch, int32_t (&out)[4]);
+void gemm_f32_plan(const GemmArgs* g, int n, size_t scratch, int32_t (&out)[4]);
+
 hipError_t gemm_f32(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t stream);
 size_t gemm_f32_scratch(const GemmArgs* g, int n, size_t most);
 

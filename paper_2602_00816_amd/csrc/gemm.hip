@@ -1167,6 +1167,16 @@ size_t gemm_scratch(const GemmArgs* g, int n, size_t most) {
 }
 
 template <typename T>
+void gemm_plan(const GemmArgs* g, int n, size_t scratch, int32_t (&out)[4]) {
+  if constexpr (sizeof(T) == 4) return gemm_f32_plan(g, n, scratch, out);
+  GemmPlan pl;
+  out[0] = ring_cost(bf16_plan(g, n, scratch, pl)).BN;
+  out[1] = pl.len;
+  out[2] = pl.splits[0];
+  out[3] = pl.splits[1];
+}
+
+template <typename T>
 hipError_t gemm_pair(const GemmArgs& a0, const GemmArgs& a1, hipStream_t stream) {
   if constexpr (sizeof(T) == 2) {
     GemmPlan pl;
@@ -1191,6 +1201,8 @@ template hipError_t gemm<float>(const GemmArgs*, int, const GemmScratch&, hipStr
 template hipError_t gemm<bf16_t>(const GemmArgs*, int, const GemmScratch&, hipStream_t);
 template size_t gemm_scratch<float>(const GemmArgs*, int, size_t);
 template size_t gemm_scratch<bf16_t>(const GemmArgs*, int, size_t);
+template void gemm_plan<float>(const GemmArgs*, int, size_t, int32_t (&)[4]);
+template void gemm_plan<bf16_t>(const GemmArgs*, int, size_t, int32_t (&)[4]);
 template hipError_t gemm_pair<float>(const GemmArgs&, const GemmArgs&, hipStream_t);
 template hipError_t gemm_pair<bf16_t>(const GemmArgs&, const GemmArgs&, hipStream_t);
 template const char* gemm_check<float>(const GemmArgs&);

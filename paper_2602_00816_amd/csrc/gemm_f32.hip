@@ -403,6 +403,14 @@ size_t gemm_f32_scratch(const GemmArgs* g, int n, size_t most) {
   return pl.bytes;
 }
 
+void gemm_f32_plan(const GemmArgs* g, int n, size_t scratch, int32_t (&out)[4]) {
+  GemmPlan pl;
+  out[0] = pick(g, n, scratch, pl).BN;
+  out[1] = pl.len;
+  out[2] = pl.splits[0];
+  out[3] = pl.splits[1];
+}
+
 hipError_t gemm_f32(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t stream) {
   if (g[0].M == 0 || g[0].N == 0) return hipSuccess;
   GemmJob j;

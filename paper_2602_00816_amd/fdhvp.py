@@ -100,6 +100,7 @@ def lib():
                                         vp, vp, C.c_float, i32, vp]),
         "fdh_testing_gemm_channels": (i32, [i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, C.c_float, vp,
                                             C.c_size_t, vp]),
+        "fdh_testing_gemm_plan": (i32, [i32, i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]),
         "fdh_testing_unfused_attention": (i32, [vp, i32]),
         "fdh_testing_unsplit_wgrad": (i32, [vp, i32]),
         "fdh_testing_timing": (i32, [vp, i32]),
@@ -485,6 +486,15 @@ def testing_gemm_channels(dtype: str, M, N, K, batch, a_kmajor, b_kmajor, A, B, 
                                          0 if scratch is None else scratch.numel() * scratch.element_size(), _stream())
     if st != OK:
         raise FdhError(st, "fdh_testing_gemm_channels")
+
+
+def testing_gemm_plan(dtype: str, M, N, K, batch=1, scratch_bytes=0):
+    """(tile width, slices of 32 k per part, parts of the two-pair and the one-pair product) of a launch (testing)."""
+    out = (C.c_int32 * 4)()
+    st = lib().fdh_testing_gemm_plan(DTYPE[dtype], M, N, K, batch, scratch_bytes, out)
+    if st != OK:
+        raise FdhError(st, "fdh_testing_gemm_plan")
+    return tuple(out)
 
 
 def testing_gemm_pair(M0, N0, K0, M1, N1, K1, a_kmajor, b_kmajor, P0, P1, alpha=1.0, tile=6, batch0=1, batch1=1):
