@@ -425,7 +425,7 @@ extern "C" fdh_status fdh_testing_gemm_channels(int32_t dtype, int32_t M, int32_
   const int n = C1 ? 2 : 1;
   for (int q = 0; q < n; ++q)
     if (dtype == FDH_BF16 ? fdh::gemm_check<fdh::bf16_t>(g[q]) : fdh::gemm_check<float>(g[q])) return FDH_ERR_UNSUPPORTED;
-  const fdh::GemmScratch sc{(float*)scratch, scratch_bytes};
+  const fdh::GemmScratch sc{(float*)scratch, scratch_bytes, scratch_bytes};
   hipError_t r;
   if (dtype == FDH_BF16) r = fdh::gemm<fdh::bf16_t>(g, n, sc, (hipStream_t)hip_stream);
   else if (dtype == FDH_F32) r = fdh::gemm<float>(g, n, sc, (hipStream_t)hip_stream);

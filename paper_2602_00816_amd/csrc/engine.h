@@ -1,6 +1,7 @@
 // Host-side engine: parameter layout, workspace plan, the lockstep HVP and the
 // Lanczos / SLQ drivers.
 #pragma once
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -151,6 +152,9 @@ class Engine : public WsLayout {
 
  private:
   size_t linear_scratch(int T_) const;
+  mutable std::mutex linear_mu;      // linear_scratch(linear_tokens) = linear_bytes
+  mutable int linear_tokens = -1;
+  mutable size_t linear_bytes = 0;
   int check_batch(const int32_t* tok, int B, int S);
   int finish_checked(const float* hv);
   template <typename T>

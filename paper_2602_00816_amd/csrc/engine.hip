@@ -151,7 +151,8 @@ static size_t bias_rows(size_t rows, int cols) { return std::min(rows, (size_t)s
 // cancel: in one of eight seeds a single element carries 2.6e-4 of fp32
 // rounding, and moves by that much with any other order of summation (up to
 // 4096 tokens, 1.2e-4 at most over 96 products).
-static bool f32_chain(int T_) { return T_ > 4096; }
+constexpr int F32_CHAIN = 4096;
+static bool f32_chain(int T_) { return T_ > F32_CHAIN; }
 
 // The weight gradient of the attention output projection (Mo x No) runs in
 // the same launch as the q/k/v one (Mq x Nq) when the q/k/v grid is not cut
@@ -211,29 +212,49 @@ static int mlp_wgrad_split(int Ma, int Na, int Mb, int Nb, int T_) {
 // ---------------------------------------------------------------------------
 // workspace plan
 // ---------------------------------------------------------------------------
-// Scratch for split contractions (at most 512 MB): the most that any linear
-// product of a batch of T_ tokens, or of T_/2, T_/4, .. (the smaller batches
-// of a dataset have fewer output tiles and are cut more), would use.
+// Scratch that the plan of a split contraction may take.  The same for every
+// workspace, so that a product is cut in the same way (and gives the same bits) in
+// each of them; the workspace holds what the plans of its batches take.
+constexpr size_t SPLIT_SCRATCH = (size_t)512 << 20;
+
+// Scratch for split contractions: the most that any linear product of a batch of
+// up to T_ tokens would use.  Forward and input gradient products have one plan
+// for all token counts of as many 128-row tiles, weight gradients for all of as
+// many slices of 32.
+// (0.4 ms of arithmetic for 8192 tokens; kept for the next plan of as many, as
+// fdh_workspace_bytes and fdh_set_workspace ask in turn.)
 size_t Engine::linear_scratch(int T_) const {
-  const size_t most = (size_t)512 << 20;
+  std::lock_guard<std::mutex> lk(linear_mu);
+  if (T_ == linear_tokens) return linear_bytes;
   const int nu = gpt2 ? F : 2 * F;
   const int shapes[5][2] = {{qkvd, d}, {d, Hq * dh}, {nu, d}, {d, F}, {V, d}};   // [out, in]
   size_t mx = 0;
-  for (int t = T_; t >= 16; t /= 2)
-    for (const auto& sh : shapes)
-      for (int kind = 0; kind < 3; ++kind) {   // forward, input gradient, weight gradient
-        GemmArgs g[2];
-        for (int p = 0; p < 2; ++p) {
-          g[p].M = kind == 2 ? sh[0] : t;
-          g[p].N = kind == 0 ? sh[0] : sh[1];
-          g[p].K = kind == 0 ? sh[1] : kind == 1 ? sh[0] : t;
-          g[p].ldc = g[p].N;
-          g[p].npairs = 2 - p;
-        }
-        const int n = kind == 2 ? 1 : 2;
-        if (kind == 2 && bf16 && wgrad_tiles(sh[0], sh[1]) >= 128) continue;
-        mx = std::max(mx, bf16 ? gemm_scratch<bf16_t>(g, n, most) : gemm_scratch<float>(g, n, most));
-      }
+  GemmArgs g[2];
+  auto reserve = [&](int M, int N, int K, int n) {
+    // (49 parts of outputs this small change nothing: 32 of the two-pair
+    // product, 17 of the other; fp32 contractions of more than 65536 take more)
+    if ((size_t)ceil_div(M, 128) * 128 * N * 4 * 49 <= mx && K <= 65536) return;
+    for (int p = 0; p < 2; ++p) {
+      g[p].M = M;
+      g[p].N = N;
+      g[p].K = K;
+      g[p].ldc = N;
+      g[p].npairs = 2 - p;
+    }
+    mx = std::max(mx, bf16 ? gemm_scratch<bf16_t>(g, n, SPLIT_SCRATCH) : gemm_scratch<float>(g, n, SPLIT_SCRATCH));
+  };
+  // (products of longer fp32 batches are not cut in their launches)
+  const int top = bf16 ? T_ : std::min(T_, F32_CHAIN);
+  for (const auto& sh : shapes) {
+    for (int t = (top + 127) / 128 * 128; t > 0; t -= 128) {
+      reserve(t, sh[0], sh[1], 2);
+      reserve(t, sh[1], sh[0], 2);
+    }
+    if (bf16 && wgrad_tiles(sh[0], sh[1]) >= 128) continue;
+    for (int t = (top + 31) / 32 * 32; t > 0; t -= 32) reserve(sh[0], sh[1], t, 1);
+  }
+  linear_tokens = T_;
+  linear_bytes = mx;
   return mx;
 }
 
@@ -504,7 +525,8 @@ static int run_gemm(Engine& e, GemmArgs* g, int n, bool chain, bool no_split = f
   GemmScratch sc;
   if (!no_split) {
     sc.p = (float*)(e.ws + e.wsplit.off);
-    sc.bytes = e.wsplit.bytes;
+    sc.bytes = SPLIT_SCRATCH;
+    sc.held = e.wsplit.bytes;
   }
   int e0 = 0;
   if (e.timing.on) {

@@ -45,10 +45,12 @@ struct GemmArgs {
   int tile = 0;
 };
 
-// Device memory for the parts of split contractions (gemm_split.h); none: no product is cut.
+// Device memory for the parts of split contractions (gemm_split.h).  Plans are
+// made for `bytes` of it (0: no product is cut), whatever is there; a plan that
+// takes more than `held` is refused.
 struct GemmScratch {
   float* p = nullptr;
-  size_t bytes = 0;
+  size_t bytes = 0, held = 0;
 };
 
 // One product (n = 1), or two of the same M, N, K, batch and layouts (the two

@@ -1152,6 +1152,7 @@ hipError_t gemm(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t str
   if (g[0].M == 0 || g[0].N == 0) return hipSuccess;
   GemmPlan pl;
   const int tile = bf16_plan(g, n, ws.bytes, pl);
+  if (pl.bytes > ws.held) return hipErrorInvalidValue;
   GemmJob j;
   const int blocks = make_job(j, g, n, pl, ring_cost(tile), ws.p);
   const hipError_t r = launch_ring(tile, j, blocks, stream);

@@ -416,6 +416,7 @@ hipError_t gemm_f32(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t
   GemmJob j;
   GemmPlan pl;
   const GemmCost& c = pick(g, n, g[0].f32_chain ? 0 : ws.bytes, pl);
+  if (pl.bytes > ws.held) return hipErrorInvalidValue;
   const int blocks = make_job(j, g, n, pl, c, ws.p);
   if (c.BN == 64) launch_bn<64>(j, blocks, stream);
   else launch_bn<128>(j, blocks, stream);

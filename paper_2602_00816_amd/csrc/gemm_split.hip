@@ -21,7 +21,8 @@ namespace fdh {
 GemmPlan plan_splits(const GemmArgs* g, int n, const GemmCost& c, size_t scratch) {
   const int64_t tiles = (int64_t)ceil_div(g[0].M, c.BM) * ceil_div(g[0].N, c.BN) * g[0].nbatch;
   const int nkt = (g[0].K + c.KT - 1) / c.KT;
-  const size_t out = (size_t)g[0].M * g[0].N * g[0].nbatch * 4;
+  // (rows in whole tiles of 128: one plan for every M of a tile count)
+  const size_t out = (size_t)ceil_div(g[0].M, 128) * 128 * g[0].N * g[0].nbatch * 4;
   int tot[2] = {0, 0}, top = 0;
   bool cut = scratch > 0;
   for (int p = 0; p < n; ++p) {
@@ -39,6 +40,9 @@ GemmPlan plan_splits(const GemmArgs* g, int n, const GemmCost& c, size_t scratch
     const double slice = c.per_cu == 1 ? c.alone + (c.slice - c.alone) * busy : wgs <= 256 ? c.alone : c.slice;
     return (double)((wgs + 255) / 256) * len * slice + c.fixed * std::ceil((double)wgs / whole_chip);
   };
+  // no cut takes less than all slices at the better rate, spread evenly
+  double least = 0.0;
+  for (int q = 0; q < n; ++q) least += (double)tiles * tot[q] / 256.0 * std::min(c.alone, c.slice);
   GemmPlan best;
   best.BN = c.BN;
   const int most = std::max(32, c.longest ? (top + c.longest - 1) / c.longest : 0);
@@ -59,6 +63,8 @@ GemmPlan plan_splits(const GemmArgs* g, int n, const GemmCost& c, size_t scratch
       }
     }
     if (p.bytes > scratch) break;
+    const bool best_fits = c.longest == 0 || best.len <= c.longest;
+    if (k > 1 && best_fits && least + moved / 6e6 >= best.us) break;   // (moved grows with k)
     if (k == 1) {
       // every product whole (a one-pair product ends after half of its workgroup's run)
       double work = 0.0;
@@ -67,7 +73,7 @@ GemmPlan plan_splits(const GemmArgs* g, int n, const GemmCost& c, size_t scratch
     } else {
       p.us = rounds_us(wgs, p.len) + (p.bytes ? moved / 6e6 + 4.0 : 0.0);
     }
-    const bool fits = c.longest == 0 || p.len <= c.longest, best_fits = c.longest == 0 || best.len <= c.longest;
+    const bool fits = c.longest == 0 || p.len <= c.longest;
     if (k == 1 || (fits && !best_fits) || (fits == best_fits && p.us < best.us)) best = p;
   }
   return best;

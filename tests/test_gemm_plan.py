@@ -33,3 +33,12 @@ def test_small_scratch_still_cuts_where_that_is_faster(K):
 def test_no_scratch_keeps_contractions_whole():
     for dtype in ("f32", "bf16"):
         assert fd.testing_gemm_plan(dtype, 512, 512, 128256)[2:] == (1, 1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,K", [(512, 3968), (4096, 512), (1504, 512), (28976, 2944)])
+def test_one_plan_for_all_rows_of_a_tile_count(dtype, N, K):
+    """The workspace reserves parts for one row count per 128-row tile count."""
+    for tiles in (1, 2, 3, 5, 9):
+        plans = {fd.testing_gemm_plan(dtype, 128 * tiles - cut, N, K, 1, 512 << 20) for cut in (0, 8, 56, 120)}
+        assert len(plans) == 1, (tiles, plans)
