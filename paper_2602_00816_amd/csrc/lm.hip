@@ -1058,8 +1058,9 @@ __global__ void swiglu_bwd_kernel(PairT<T> dgu, const T* gum, const T* gud, cons
 // e^b and e^-b as c + s and c - s with c = cosh b and s = sinh b: for
 // |b| < 1/16 their Taylor series to b^8 and b^9 (the first omitted terms are
 // below 2^-40 / 10! of the sum), otherwise from exp.
+constexpr double EXP_PM_SERIES = 0.0625;
 __device__ inline void exp_pm(double b, double& ep, double& en) {
-  if (fabs(b) < 0.0625) {
+  if (fabs(b) < EXP_PM_SERIES) {
     const double b2 = b * b;
     const double c = 1.0 + b2 * (1.0 / 2 + b2 * (1.0 / 24 + b2 * (1.0 / 720 + b2 * (1.0 / 40320))));
     const double sn = b * (1.0 + b2 * (1.0 / 6 + b2 * (1.0 / 120 + b2 * (1.0 / 5040 + b2 * (1.0 / 362880)))));
@@ -1098,10 +1099,24 @@ __global__ __launch_bounds__(NTH) void ce_kernel(PairT<T> dl, double* rowloss, c
   auto ld4 = [](const float* p, int64_t i) { return *reinterpret_cast<const float4*>(p + i); };
   // exp(a +- b) = E e^+-b with E = exp(a) shared by both points and e^+-b from
   // exp_pm.  For bf16 models E is taken in fp32 (a common factor of the two
-  // channels, so its rounding never cancels in their half difference).
+  // channels, so its rounding never cancels in their half difference).  fp32
+  // models share E within the series only, and take the maximum over a + |b|
+  // beyond it: a far smaller E with a far larger e^b would be 0 times infinity.
   auto expa = [&](double a) {
     if constexpr (sizeof(T) == 2) return (double)__expf((float)a);
     else return exp(a);
+  };
+  auto both = [&](double a, double b, double& xp, double& xn) {
+    if (sizeof(T) == 4 && fabs(b) >= EXP_PM_SERIES) {
+      xp = exp(a + b);
+      xn = exp(a - b);
+      return;
+    }
+    const double E = expa(a);
+    double ep, en;
+    exp_pm(b, ep, en);
+    xp = E * ep;
+    xn = E * en;
   };
   // one pass for the row maximum and the sums: each thread keeps its sums
   // relative to its own running maximum mt, rescaled by exp(old mt - new mt)
@@ -1110,7 +1125,8 @@ __global__ __launch_bounds__(NTH) void ce_kernel(PairT<T> dl, double* rowloss, c
   double mt = -1e300, zp = 0.0, zm = 0.0;
   for (int j = threadIdx.x; j < n4; j += NTH) {
     const float4 a = ld4(lm, o + 4 * j), b = ld4(ld, o + 4 * j);
-    const double top = (double)fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w));
+    auto high = [](float x, float y) { return sizeof(T) == 4 && fabsf(y) >= (float)EXP_PM_SERIES ? x + fabsf(y) : x; };
+    const double top = (double)fmaxf(fmaxf(high(a.x, b.x), high(a.y, b.y)), fmaxf(high(a.z, b.z), high(a.w, b.w)));
     if (top > mt) {
       const double f = mt > -1e300 ? expa(mt - top) : 0.0;
       zp *= f;
@@ -1119,11 +1135,10 @@ __global__ __launch_bounds__(NTH) void ce_kernel(PairT<T> dl, double* rowloss, c
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const double E = expa((double)f4e(a, e) - mt);
-      double ep, en;
-      exp_pm((double)f4e(b, e), ep, en);
-      zp += E * ep;
-      zm += E * en;
+      double xp, xn;
+      both((double)f4e(a, e) - mt, f4e(b, e), xp, xn);
+      zp += xp;
+      zm += xn;
     }
   }
   const double mx = block_max<NTH>(mt, sh);
@@ -1138,10 +1153,9 @@ __global__ __launch_bounds__(NTH) void ce_kernel(PairT<T> dl, double* rowloss, c
     float om[4], od[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const double E = expa((double)f4e(a, e) - mx);
-      double ep, en;
-      exp_pm((double)f4e(b, e), ep, en);
-      const double pp = E * ep * izp, pn = E * en * izm;
+      double xp, xn;
+      both((double)f4e(a, e) - mx, f4e(b, e), xp, xn);
+      const double pp = xp * izp, pn = xn * izm;
       om[e] = (float)(0.5 * (pp + pn) - (4 * j + e == y ? inv_n : 0.0));
       od[e] = (float)(0.5 * (pp - pn));
     }
