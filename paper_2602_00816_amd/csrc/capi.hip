@@ -433,6 +433,51 @@ extern "C" fdh_status fdh_testing_gemm_channels(int32_t dtype, int32_t M, int32_
   return r == hipSuccess ? FDH_OK : FDH_ERR_HIP;
 }
 
+extern "C" fdh_status fdh_testing_gemm_epilogue(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t batch,
+                                                int32_t a_kmajor, int32_t b_kmajor, const void* A, const void* B,
+                                                const void* A2, const void* B2, void* C, int64_t ldc, int32_t out_op,
+                                                float alpha, float beta, const void* bias_theta, const float* bias_v,
+                                                float bias_v_scale, const float* resid, int32_t causal, int32_t tile,
+                                                int32_t chain, void* scratch, size_t scratch_bytes, void* hip_stream) {
+  if (!A || !B || !C || (!A2) != (!B2) || M < 0 || N < 0 || K < 0 || batch < 1 || ldc < N || causal < 0 || causal > 3 ||
+      tile < 0 || tile > 9 || (scratch_bytes && !scratch) || (uintptr_t)scratch % 256)
+    return FDH_ERR_INVALID_ARG;
+  fdh::GemmArgs g;
+  g.M = M; g.N = N; g.K = K; g.nbatch = batch; g.inner_count = 1;
+  g.npairs = A2 ? 2 : 1;
+  const void* As[2] = {A, A2};
+  const void* Bs[2] = {B, B2};
+  for (int p = 0; p < g.npairs; ++p) {
+    g.A[p].ptr = As[p];
+    g.A[p].s_row = a_kmajor ? K : 1;
+    g.A[p].s_k = a_kmajor ? 1 : M;
+    g.A[p].s_outer = (int64_t)M * K;
+    g.B[p].ptr = Bs[p];
+    g.B[p].s_row = b_kmajor ? K : 1;
+    g.B[p].s_k = b_kmajor ? 1 : N;
+    g.B[p].s_outer = (int64_t)N * K;
+  }
+  g.C = C; g.ldc = ldc; g.c_outer = (int64_t)M * ldc;
+  g.out_type = out_op ? fdh::OUT_OP : fdh::OUT_F32;
+  g.alpha = alpha; g.beta = beta;
+  g.bias_theta = bias_theta;
+  g.bias_v = bias_v; g.bias_v_scale = bias_v_scale;
+  g.resid = resid;
+  g.causal = causal; g.tile = tile; g.f32_chain = chain != 0;
+  const fdh::GemmScratch sc{(float*)scratch, scratch_bytes, scratch_bytes};
+  hipError_t r;
+  if (dtype == FDH_BF16) {
+    if (fdh::gemm_check<fdh::bf16_t>(g)) return FDH_ERR_UNSUPPORTED;
+    r = fdh::gemm<fdh::bf16_t>(&g, 1, sc, (hipStream_t)hip_stream);
+  } else if (dtype == FDH_F32) {
+    if (fdh::gemm_check<float>(g)) return FDH_ERR_UNSUPPORTED;
+    r = fdh::gemm<float>(&g, 1, sc, (hipStream_t)hip_stream);
+  } else {
+    return FDH_ERR_INVALID_ARG;
+  }
+  return r == hipSuccess ? FDH_OK : FDH_ERR_HIP;
+}
+
 extern "C" fdh_status fdh_testing_gemm_plan(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t batch,
                                             size_t scratch_bytes, int32_t* out4) {
   if (!out4 || M < 1 || N < 1 || K < 1 || batch < 1) return FDH_ERR_INVALID_ARG;
