@@ -9,8 +9,11 @@
 //     y.d = x.d theta^T + x.m (eps v)^T
 // and the weight gradient needs only its half difference
 //     (g+ - g-)/2 = dy.m^T x.d + dy.d^T x.m,   so   Hv_W = (dy.m^T x.d + dy.d^T x.m) / eps.
-// Every non-linear step (norms, softmax, GELU/SwiGLU, cross-entropy) is
-// evaluated at both points in fp64 inside its kernel.  theta is never written.
+// Every non-linear step is evaluated at both points inside its kernel, so that
+// the half difference keeps its relative precision however small it is: the
+// norms, GELU and the cross-entropy in fp64, the softmax and SwiGLU from the mean
+// and the half difference themselves, without a difference of nearly equal
+// values.  theta is never written.
 #include "engine.h"
 
 #include <algorithm>
@@ -743,7 +746,7 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     int k = 1;
     if (ln) o.out[k++] = hv + bias.off;
     if (osum) o.out[k++] = hv + before.off;
-    CK(launch_colsum_part(o, part, norm_bwd_groups(T_, d, ln), k * d, d, 1.0 / eps, acc, st));
+    CK(launch_colsum_part(o, part, norm_bwd_groups(T_, d), k * d, d, 1.0 / eps, acc, st));
     return FDH_OK;
   };
   // fp32 pair -> operand pair (aliases in fp32 mode; skipped when the norm

@@ -424,14 +424,10 @@ __device__ inline bf16x8_t frag(const bf16_t* t, int r0, int kk, int lane) {
   }
 }
 
-#ifndef FDH_DMA_STAGES
-#define FDH_DMA_STAGES 4
-#endif
 template <int BN_, int WN, bool AK, bool BKM>
 __global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_dma(GemmArgs a) {
   constexpr int BM_ = 256, WM = 2, NW = WM * WN;
-  // ring depth: 4 stages, or 5 for 256-wide tiles when built with FDH_DMA_STAGES=5
-  constexpr int NS = (BN_ == 256 && FDH_DMA_STAGES == 5) ? 5 : 4;
+  constexpr int NS = 4;                         // ring depth (a fifth stage measured no faster)
   constexpr int WTN = BN_ / WN;                 // wavefront tile: 128 x WTN
   constexpr int IM = 4, JN = WTN / 32;
   constexpr int ASZ = BM_ * KT3, BSZ = BN_ * KT3;              // elements per stage
@@ -442,7 +438,6 @@ __global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_dma(GemmArgs a) {
   __shared__ __attribute__((aligned(1024))) bf16_t st1[ASZ + BSZ];
   __shared__ __attribute__((aligned(1024))) bf16_t st2[ASZ + BSZ];
   __shared__ __attribute__((aligned(1024))) bf16_t st3[ASZ + BSZ];
-  __shared__ __attribute__((aligned(1024))) bf16_t st4[NS == 5 ? ASZ + BSZ : 8];
 
   const int gx = gridDim.x, gy = gridDim.y;
   const int nb = gx * gy * gridDim.z;
@@ -487,8 +482,7 @@ __global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_dma(GemmArgs a) {
     if constexpr (S == 0) return st0;
     else if constexpr (S == 1) return st1;
     else if constexpr (S == 2) return st2;
-    else if constexpr (S == 3) return st3;
-    else return st4;
+    else return st3;
   };
   auto issue = [&](int t, bf16_t* st) {
     const int p = t >= nkt ? 1 : 0;
@@ -511,8 +505,7 @@ __global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_dma(GemmArgs a) {
   auto step = [&](auto s, int t) {
     constexpr int S = decltype(s)::value;
     const int ahead = min(NS - 2, total - 1 - t);
-    if (ahead >= 3) wait_vm<3 * PERT>();
-    else if (ahead == 2) wait_vm<2 * PERT>();
+    if (ahead == 2) wait_vm<2 * PERT>();
     else if (ahead == 1) wait_vm<PERT>();
     else wait_vm<0>();
     __builtin_amdgcn_s_barrier();
@@ -538,14 +531,11 @@ __global__ __launch_bounds__(64 * 2 * WN) void gemm_bf16_dma(GemmArgs a) {
   if (total > 0) issue(0, st0);
   if (total > 1) issue(1, st1);
   if (total > 2) issue(2, st2);
-  if (NS == 5 && total > 3) issue(3, st3);
   for (int t0 = 0; t0 < total; t0 += NS) {
     step(std::integral_constant<int, 0>{}, t0);
     if (t0 + 1 < total) step(std::integral_constant<int, 1>{}, t0 + 1);
     if (t0 + 2 < total) step(std::integral_constant<int, 2>{}, t0 + 2);
     if (t0 + 3 < total) step(std::integral_constant<int, 3>{}, t0 + 3);
-    if constexpr (NS == 5)
-      if (t0 + 4 < total) step(std::integral_constant<int, 4>{}, t0 + 4);
   }
 
   const int64_t coff = batch_off(z, a.inner_count, a.c_outer, a.c_inner, a.c_div);

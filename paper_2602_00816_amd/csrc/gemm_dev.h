@@ -29,13 +29,7 @@ __device__ inline void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// shared epilogue: accumulator block (i, j) of a wavefront whose 32x32 block
-// origin is (rb, cb).  Every MFMA takes the B fragment as its first operand, so
-// the block holds C^T in the MFMA output layout: lane l owns row rb + (l & 31)
-// of C and, for g = 0..3, the four consecutive columns cb + 8g + 4(l >> 5) + 0..3
-// (accumulator elements 4g..4g+3).  Each such quad is stored, and the residual
-// or previous C loaded, as one vector where the addresses are aligned.
-// four consecutive outputs at C[idx..idx+3], 16-byte (fp32) or 8-byte (bf16)
+// Four consecutive outputs at C[idx..idx+3], 16-byte (fp32) or 8-byte (bf16)
 // aligned: one vector store, with the residual and previous C read as vectors
 template <typename T>
 __device__ inline void store_quad(const GemmArgs& a, const float (&x)[4], int64_t idx) {
@@ -64,6 +58,12 @@ __device__ inline void store_quad(const GemmArgs& a, const float (&x)[4], int64_
   }
 }
 
+// Shared epilogue: accumulator block (i, j) of a wavefront whose 32x32 block
+// origin is (rb, cb).  Every MFMA takes the B fragment as its first operand, so
+// the block holds C^T in the MFMA output layout: lane l owns row rb + (l & 31)
+// of C and, for g = 0..3, the four consecutive columns cb + 8g + 4(l >> 5) + 0..3
+// (accumulator elements 4g..4g+3).  Each such quad is stored, and the residual
+// or previous C loaded, as one vector where the addresses are aligned.
 template <typename T>
 __device__ inline void store_block(const GemmArgs& a, const f32x16_t& acc, int64_t coff, int rb, int cb, int lane) {
   const int row = rb + (lane & 31);

@@ -14,7 +14,6 @@
 namespace fdh {
 
 struct GemmPlan {
-  int BN = 0;               // tile width
   int len = 0;              // slices per part
   int splits[2] = {1, 1};   // parts of each product
   size_t bytes = 0;         // scratch

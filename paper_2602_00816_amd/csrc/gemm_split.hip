@@ -44,12 +44,10 @@ GemmPlan plan_splits(const GemmArgs* g, int n, const GemmCost& c, size_t scratch
   double least = 0.0;
   for (int q = 0; q < n; ++q) least += (double)tiles * tot[q] / 256.0 * std::min(c.alone, c.slice);
   GemmPlan best;
-  best.BN = c.BN;
   const int most = std::max(32, c.longest ? (top + c.longest - 1) / c.longest : 0);
   for (int k = 1; k <= most; ++k) {
     if (k > 1 && !cut) break;
     GemmPlan p;
-    p.BN = c.BN;
     p.len = std::max(1, (top + k - 1) / k);
     if (k > 1 && p.len < 4) break;
     int64_t wgs = 0;

@@ -133,12 +133,12 @@ hipError_t launch_norm_fwd(PairT<T> y, const float* xm, const float* xd, int row
 // or 2048 columns; else a workgroup per row (about
 // 1024 workgroups, at most 8 rows each).
 constexpr int NORM_WAVE_ROWS = 16;
-inline bool norm_bwd_waves(int rows, int dm, bool ln) {
+inline bool norm_bwd_waves(int rows, int dm) {
   return rows >= 4096 && (dm == 512 || dm == 1024 || dm == 2048);
 }
 inline int norm_bwd_rows(int rows) { return rows < 2048 ? 1 : rows >= 8192 ? 8 : rows / 1024; }
-inline int norm_bwd_groups(int rows, int dm, bool ln) {
-  const int per = norm_bwd_waves(rows, dm, ln) ? NORM_WAVE_ROWS : norm_bwd_rows(rows);
+inline int norm_bwd_groups(int rows, int dm) {
+  const int per = norm_bwd_waves(rows, dm) ? NORM_WAVE_ROWS : norm_bwd_rows(rows);
   return (rows + per - 1) / per;
 }
 template <typename T>

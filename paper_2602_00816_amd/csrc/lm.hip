@@ -387,15 +387,16 @@ __global__ __launch_bounds__(NTH) void norm_bwd_kernel(PairF dx, PairT<T> dxo, c
 
 // The same with one wavefront per row (rows of 256 CPL columns, lane l at columns
 // 256 c + 4 l) and 4 rows per wavefront, 16 per workgroup, for many rows: no
-// barrier per row and a quarter of the reductions per element (8192 x 1024 with
-// LayerNorm: 65 us against 118, 8192 x 2048: 130 against 148).  x is kept in
-// registers, dy read again from the caches (keeping it too cost 100 and 188 us).
-// Column sums in LDS, at most 4 rows per wavefront: gain and bias terms in fp32,
-// the outputs' half differences in fp64 (as the pass over the stored outputs,
-// which they replace, added them).
-// Two wavefronts per SIMD asked for (at 2048 columns the compiler otherwise takes
-// more registers than leave room for the second: 168 us per call at 8192 x 2048
-// without LayerNorm, 126 with two).
+// barrier per row and a quarter of the reductions per element.  x is kept in
+// registers, dy read again from the caches.  Column sums in LDS, at most 4 rows per
+// wavefront: gain and bias terms in fp32, the outputs' half differences in fp64 (as
+// the pass over the stored outputs, which they replace, added them).
+// 8192 x 1024 with LayerNorm and output sums: 65 us per call; the kernel above 118,
+// dy kept in registers too 100.
+// 8192 x 2048 without LayerNorm: 126 to 130 us (boxes differ), 604 MB at 4.7 TB/s;
+// the kernel above 148, dy kept in registers too 188, the registers that the
+// compiler takes without a bound (one wavefront per SIMD) 168, more than two
+// workgroups per CU (the second read of dy then misses the L2) 158.
 template <typename T, int CPL, bool LN, bool OS>
 __global__ __launch_bounds__(NT, 2) void norm_bwd_wave_kernel(PairF dx, PairT<T> dxo, const float* dresm, const float* dresd,
                                                            const float* xm, const float* xd, const float* dym,
@@ -404,8 +405,7 @@ __global__ __launch_bounds__(NT, 2) void norm_bwd_wave_kernel(PairF dx, PairT<T>
   constexpr int DM = 256 * CPL;
   // per-wavefront column sums (gain, bias, outputs); a lane only touches its own columns
   constexpr int NF = 1 + (LN ? 1 : 0), NS = NF + (OS ? 1 : 0);
-  // (rows of 2048: two workgroups per CU by LDS; with more, the second read of dy
-  // misses the L2: 158 us against 130)
+  // (rows of 2048: two workgroups per CU by LDS)
   constexpr int NL = DM >= 2048 && NS < 2 ? 2 : NF;
   __shared__ float cs[NL][4][DM];
   __shared__ __attribute__((aligned(16))) double so[OS ? 4 : 1][OS ? DM : 2];
@@ -669,84 +669,7 @@ __global__ __launch_bounds__(NT) void qkv_bias_kernel(PairT<T> out, const float*
 }
 
 // ---- causal softmax and its backward, both points ---------------------------------------
-constexpr int MAXE = 16;  // row elements per thread (rows up to 4096)
-
-template <typename T>
-__global__ __launch_bounds__(NT) void attn_softmax_kernel(PairT<T> P, const float* Sm, const float* Sd, int S) {
-  __shared__ double sh[NT / 64];
-  const int64_t r = blockIdx.x;
-  const int i = (int)(r % S);
-  const int64_t base = r * (int64_t)S;
-  const int len = i + 1;
-  double ep[MAXE], em[MAXE];
-  double mx = -1e300;
-#pragma unroll
-  for (int e = 0; e < MAXE; ++e) {
-    const int j = threadIdx.x + e * NT;
-    if (j < len) mx = fmax(mx, (double)Sm[base + j]);
-  }
-  mx = block_max<NT>(mx, sh);
-  double zp = 0.0, zm = 0.0;
-#pragma unroll
-  for (int e = 0; e < MAXE; ++e) {
-    const int j = threadIdx.x + e * NT;
-    ep[e] = em[e] = 0.0;
-    if (j < len) {
-      const double a = (double)Sm[base + j] - mx, b = (double)Sd[base + j];
-      ep[e] = exp(a + b);
-      em[e] = exp(a - b);
-      zp += ep[e];
-      zm += em[e];
-    }
-  }
-  zp = block_sum<NT>(zp, sh);
-  zm = block_sum<NT>(zm, sh);
-  const double izp = 1.0 / zp, izm = 1.0 / zm;
-#pragma unroll
-  for (int e = 0; e < MAXE; ++e) {
-    const int j = threadIdx.x + e * NT;
-    if (j < S) put_pair(P, base + j, ep[e] * izp, em[e] * izm);
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(NT) void attn_dsoftmax_kernel(PairT<T> dS, const T* Pm, const T* Pd, const float* dPm,
-                                                           const float* dPd, int S) {
-  __shared__ double sh[NT / 64];
-  const int64_t r = blockIdx.x;
-  const int i = (int)(r % S);
-  const int64_t base = r * (int64_t)S;
-  const int len = i + 1;
-  double dp = 0.0, dm = 0.0;
-#pragma unroll
-  for (int e = 0; e < MAXE; ++e) {
-    const int j = threadIdx.x + e * NT;
-    if (j < len) {
-      const double pm = ldf(Pm, base + j), pd = ldf(Pd, base + j);
-      const double gm = dPm[base + j], gd = dPd[base + j];
-      dp += (pm + pd) * (gm + gd);
-      dm += (pm - pd) * (gm - gd);
-    }
-  }
-  dp = block_sum<NT>(dp, sh);
-  dm = block_sum<NT>(dm, sh);
-#pragma unroll
-  for (int e = 0; e < MAXE; ++e) {
-    const int j = threadIdx.x + e * NT;
-    if (j < S) {
-      double sp = 0.0, sn = 0.0;
-      if (j < len) {
-        const double pm = ldf(Pm, base + j), pd = ldf(Pd, base + j);
-        const double gm = dPm[base + j], gd = dPd[base + j];
-        sp = (pm + pd) * (gm + gd - dp);
-        sn = (pm - pd) * (gm - gd - dm);
-      }
-      put_pair(dS, base + j, sp, sn);
-    }
-  }
-}
-
-// Wavefront-per-row versions (4 rows per workgroup).  Row i of a causal score
+// One wavefront per row, 4 rows per workgroup.  Row i of a causal score
 // matrix has i+1 live entries; entries i < j < roundup(i+1, 256) are written
 // as zeros, because the MFMA tiles that contract over a row read exactly up
 // to that boundary; entries beyond it are never read and not written.
@@ -1352,8 +1275,8 @@ hipError_t launch_norm_bwd(PairF dx, PairT<T> dxo, const float* dresm, const flo
                            const float* vg, double eps, float neps, double* part, bool osum, hipStream_t s) {
   // (wider rows were never supported)
   if ((size_t)dm * (ln ? 2 : 1) > 8192) return hipErrorInvalidValue;
-  if (norm_bwd_waves(rows, dm, ln)) {
-    const dim3 g(norm_bwd_groups(rows, dm, ln));
+  if (norm_bwd_waves(rows, dm)) {
+    const dim3 g(norm_bwd_groups(rows, dm));
 #define NW(C, L, O)                                                                                                    \
   hipLaunchKernelGGL((norm_bwd_wave_kernel<T, C, L, O>), g, dim3(NT), 0, s, dx, dxo, dresm, dresd, xm, xd, dym, dyd,    \
                      rows, thg, vg, eps, (double)neps, part)
@@ -1372,7 +1295,7 @@ hipError_t launch_norm_bwd(PairF dx, PairT<T> dxo, const float* dresm, const flo
     return hipGetLastError();
   }
   const int per = norm_bwd_rows(rows), ncol = dm * (1 + (ln ? 1 : 0) + (osum ? 1 : 0));
-  const dim3 g(norm_bwd_groups(rows, dm, ln));
+  const dim3 g(norm_bwd_groups(rows, dm));
 #define NB(N, C)                                                                                                        \
   do {                                                                                                                  \
     if (ln) hipLaunchKernelGGL((norm_bwd_kernel<T, N, C, true>), g, dim3(N), 0, s, dx, dxo, dresm, dresd, xm, xd, dym,  \
