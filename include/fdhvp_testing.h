@@ -64,15 +64,13 @@ fdh_status fdh_testing_gemm_channels(int32_t dtype, int32_t M, int32_t N, int32_
  * operands laid out as for fdh_testing_gemm, C and resid [batch][M][ldc], C in
  * float32 or, with out_op != 0, in the operand type (then without resid and
  * beta); bias_theta (operand type) and bias_v (float32) [N], any of the
- * optional pointers NULL.  causal as for fdh_testing_gemm.  chain != 0 runs fp32
- * operands on the fp32 matrix instructions, as batches of more than 4096 tokens
- * do; tile 9 asks for the 128 x 128 bf16 kernel (whole contraction), 0 leaves the
- * choice.  scratch as for fdh_testing_gemm_channels. */
+ * optional pointers NULL.  causal and tile as for fdh_testing_gemm (a tile asked
+ * for takes the contraction whole), scratch as for fdh_testing_gemm_channels. */
 fdh_status fdh_testing_gemm_epilogue(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t batch, int32_t a_kmajor,
                                      int32_t b_kmajor, const void* A, const void* B, const void* A2, const void* B2,
                                      void* C, int64_t ldc, int32_t out_op, float alpha, float beta,
                                      const void* bias_theta, const float* bias_v, float bias_v_scale,
-                                     const float* resid, int32_t causal, int32_t tile, int32_t chain, void* scratch,
+                                     const float* resid, int32_t causal, int32_t tile, void* scratch,
                                      size_t scratch_bytes, void* hip_stream);
 
 /* How fdh_testing_gemm_channels with both outputs would launch that product

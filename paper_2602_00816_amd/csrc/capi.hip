@@ -438,7 +438,7 @@ extern "C" fdh_status fdh_testing_gemm_epilogue(int32_t dtype, int32_t M, int32_
                                                 const void* A2, const void* B2, void* C, int64_t ldc, int32_t out_op,
                                                 float alpha, float beta, const void* bias_theta, const float* bias_v,
                                                 float bias_v_scale, const float* resid, int32_t causal, int32_t tile,
-                                                int32_t chain, void* scratch, size_t scratch_bytes, void* hip_stream) {
+                                                void* scratch, size_t scratch_bytes, void* hip_stream) {
   if (!A || !B || !C || (!A2) != (!B2) || M < 0 || N < 0 || K < 0 || batch < 1 || ldc < N || causal < 0 || causal > 3 ||
       tile < 0 || tile > 9 || (scratch_bytes && !scratch) || (uintptr_t)scratch % 256)
     return FDH_ERR_INVALID_ARG;
@@ -463,7 +463,7 @@ extern "C" fdh_status fdh_testing_gemm_epilogue(int32_t dtype, int32_t M, int32_
   g.bias_theta = bias_theta;
   g.bias_v = bias_v; g.bias_v_scale = bias_v_scale;
   g.resid = resid;
-  g.causal = causal; g.tile = tile; g.f32_chain = chain != 0;
+  g.causal = causal; g.tile = tile;
   const fdh::GemmScratch sc{(float*)scratch, scratch_bytes, scratch_bytes};
   hipError_t r;
   if (dtype == FDH_BF16) {

@@ -131,31 +131,8 @@ Engine::Engine(const fdh_model_config& c, hipStream_t s) : cfg(c), stream(s) {
 // on the 1.3B shapes).
 static int64_t wgrad_tiles(int M, int N) { return (int64_t)((M + 255) / 256) * ((N + 255) / 256); }
 
-// Token slices of a weight-gradient GEMM (M x N output, contraction over the T
-// tokens) whose order of summation is fixed (f32_chain): up to one full wave of
-// 256 tiles for a grid that leaves most compute units idle.
-static int wgrad_splits(int M, int N, int T_) {
-  const int64_t tiles = wgrad_tiles(M, N);
-  if (tiles >= 128) return 1;
-  int best = 1;
-  for (int s : {2, 3, 4, 6, 8})
-    if (T_ % (64 * s) == 0 && T_ / s >= 1024 && tiles * s <= 256) best = s;
-  return best;
-}
-
 // most rows of column sums that the bias kernels write for up to `rows` tokens
 static size_t bias_rows(size_t rows, int cols) { return std::min(rows, (size_t)std::max(1, 1024 / ((cols + 1023) / 1024))); }
-
-// fp32 batches of more than 4096 tokens keep the fp32 matrix instructions and
-// their order of summation.  The split products are faster there too (27.7
-// against 37.6 ms for the 23M-parameter GPT-2's product on 16 x 512 tokens) and
-// nearer to fp64 (2.4e-7 against 5e-7 to 2e-6 over the vector), but the head
-// gradient's row of the most frequent token adds thousands of terms that
-// cancel: in one of eight seeds a single element carries 2.6e-4 of fp32
-// rounding, and moves by that much with any other order of summation (up to
-// 4096 tokens, 1.2e-4 at most over 96 products).
-constexpr int F32_CHAIN = 4096;
-static bool f32_chain(int T_) { return T_ > F32_CHAIN; }
 
 // The weight gradient of the attention output projection (Mo x No) runs in
 // the same launch as the q/k/v one (Mq x Nq) when the q/k/v grid is not cut
@@ -246,15 +223,13 @@ size_t Engine::linear_scratch(int T_) const {
     }
     mx = std::max(mx, bf16 ? gemm_scratch<bf16_t>(g, n, SPLIT_SCRATCH) : gemm_scratch<float>(g, n, SPLIT_SCRATCH));
   };
-  // (products of longer fp32 batches are not cut in their launches)
-  const int top = bf16 ? T_ : std::min(T_, F32_CHAIN);
   for (const auto& sh : shapes) {
-    for (int t = (top + 127) / 128 * 128; t > 0; t -= 128) {
+    for (int t = (T_ + 127) / 128 * 128; t > 0; t -= 128) {
       reserve(t, sh[0], sh[1], 2);
       reserve(t, sh[1], sh[0], 2);
     }
     if (bf16 && wgrad_tiles(sh[0], sh[1]) >= 128) continue;
-    for (int t = (top + 31) / 32 * 32; t > 0; t -= 32) reserve(sh[0], sh[1], t, 1);
+    for (int t = (T_ + 31) / 32 * 32; t > 0; t -= 32) reserve(sh[0], sh[1], t, 1);
   }
   linear_tokens = T_;
   linear_bytes = mx;
@@ -338,11 +313,6 @@ size_t Engine::plan(int B, int S, int m, const fdh_lanczos_opts* o, WsLayout* ou
     {
       const int nu = gpt2 ? F : 2 * F;
       size_t mx = linear_scratch((int)T_);
-      const int shapes[5][2] = {{qkvd, d}, {d, Hq * dh}, {nu, d}, {d, F}, {V, d}};
-      for (const auto& sh : shapes) {
-        const int ns = !bf16 && f32_chain((int)T_) ? wgrad_splits(sh[0], sh[1], (int)T_) : 1;
-        if (ns > 1) mx = std::max(mx, (size_t)ns * sh[0] * sh[1] * 4);
-      }
       // the down projection's slices when the MLP weight gradients share a launch
       const int nm = bf16 && !gpt2 ? mlp_wgrad_split(nu, d, d, F, (int)T_) : 0;
       if (nm > 1) mx = std::max(mx, (size_t)nm * d * F * 4);
@@ -514,7 +484,7 @@ static double gemm_flops(const GemmArgs& g) {
 // one product, or the two channel products of a linear layer (n = 2); scratch
 // for split contractions unless no_split
 template <typename T>
-static int run_gemm(Engine& e, GemmArgs* g, int n, bool chain, bool no_split = false) {
+static int run_gemm(Engine& e, GemmArgs* g, int n, bool no_split = false) {
   double fl = 0.0;
   for (int p = 0; p < n; ++p) {
     const char* msg = gemm_check<T>(g[p]);
@@ -523,7 +493,6 @@ static int run_gemm(Engine& e, GemmArgs* g, int n, bool chain, bool no_split = f
       return FDH_ERR_UNSUPPORTED;
     }
     fl += gemm_flops(g[p]);
-    g[p].f32_chain = chain;
   }
   GemmScratch sc;
   if (!no_split) {
@@ -577,8 +546,8 @@ static int run_gemm_pair(Engine& e, GemmArgs& g0, GemmArgs& g1) {
 // both channel products: g (mean) and h (half difference)
 #define RG2(T, g, h)                         \
   do {                                       \
-    GemmArgs gh_[2] = {h, g};                       \
-    int rc_ = run_gemm<T>(*this, gh_, 2, chain);    \
+    GemmArgs gh_[2] = {h, g};                \
+    int rc_ = run_gemm<T>(*this, gh_, 2);    \
     if (rc_ != FDH_OK) return rc_;           \
   } while (0)
 
@@ -596,7 +565,6 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
   const float feps = (float)eps;
   const float inv_eps = (float)(1.0 / eps);
   const bool ln = gpt2;
-  const bool chain = !bf16 && f32_chain(T_);
   const float neps = cfg.norm_eps;
   const int G = Hq / Hk;
   const float att_scale = (float)(1.0 / std::sqrt((double)dh));
@@ -664,8 +632,6 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
     return FDH_OK;
   };
   // Hv_W = (dY.m^T X.d + dY.d^T X.m) / eps
-  // (with ns > 1 the token range is cut into ns slices, one GEMM batch entry
-  // each, into fp32 partial products that a second pass adds in slice order)
   auto wgrad_args = [&](const T* dYm, const T* dYd, int N, const T* Xm, const T* Xd, int K, const ParamRef& W) {
     GemmArgs g;
     g.M = N; g.N = K; g.K = T_; g.npairs = 2;
@@ -701,27 +667,9 @@ int Engine::hvp_t(const T* th, const float* v, double eps, const int32_t* tok, c
   };
   auto lin_wgrad = [&](const T* dYm, const T* dYd, int N, const T* Xm, const T* Xd, int K, const ParamRef& W) -> int {
     GemmArgs g = wgrad_args(dYm, dYd, N, Xm, Xd, K, W);
-    // (cut, where that pays, inside the launch; chain products into token slices here)
-    const int ns = chain ? wgrad_splits(N, K, T_) : 1;
-    if (ns == 1 || force_unsplit || wsplit.bytes < (size_t)ns * N * K * 4) {
-      if (acc) g.beta = 1.f;
-      return run_gemm<T>(*this, &g, 1, chain, force_unsplit || (bf16 && wgrad_tiles(N, K) >= 128));
-    }
-    const int kc = T_ / ns;
-    g.K = kc;
-    g.nbatch = ns;
-    for (int p = 0; p < 2; ++p) {
-      g.A[p].s_outer = (int64_t)kc * N;
-      g.B[p].s_outer = (int64_t)kc * K;
-    }
-    g.C = F32(wsplit); g.c_outer = (int64_t)N * K;
-    const int rc = run_gemm<T>(*this, &g, 1, chain, true);
-    if (rc != FDH_OK) return rc;
-    int e0 = 0;
-    if (timing.on) CK(timing.begin(st, &e0));
-    CK(launch_sum_splits(hv + W.off, F32(wsplit), ns, (int64_t)N * K, acc, st));
-    if (timing.on) CK(timing.end(st, 0, e0, 0.0, 0.0));
-    return FDH_OK;
+    // (cut, where that pays, inside the launch)
+    if (acc) g.beta = 1.f;
+    return run_gemm<T>(*this, &g, 1, force_unsplit || (bf16 && wgrad_tiles(N, K) >= 128));
   };
   bool op_ready = false;  // dxo holds the operand-type copy of the last norm backward's output
   double* part = (double*)F32(gpart);

@@ -38,7 +38,6 @@ struct GemmArgs {
   float bias_v_scale = 1.f;
   const float* resid = nullptr;           // fp32, same indexing as C, added (OUT_F32 only)
   int causal = CAUSAL_NONE;
-  bool f32_chain = false;                 // fp32 only: one fp32 matrix-instruction chain over k per output
   // 0 automatic; bf16 only: register-staged 1 128x128, 2 256x256, 3 256x128; one fragment
   // set 4 256x256, 5 256x128; ring 6 256x256 on four wavefronts, 8 on eight, 9 128x128; 7 as 6
   // with slices of 64

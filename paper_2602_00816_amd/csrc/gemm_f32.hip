@@ -315,64 +315,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmJob job) {
     }
 }
 
-// The same tiles and ring with v_mfma_f32_32x32x2_f32, k in ascending order in
-// one accumulator and no parts (GemmArgs::f32_chain).  Bound by that
-// instruction's rate (64 cycles for 4096 operations); the 4-byte fragment
-// reads of a step are issued ahead of the matrix operations of the one before.
-template <int BN, bool AK, bool BKM>
-__global__ __launch_bounds__(256, 2) void gemm_f32_chain_kernel(GemmJob job) {
-  typedef Work<BN, AK, BKM> W;
-  constexpr int IM = 2, JN = BN / 64;
-  __shared__ __attribute__((aligned(1024))) float ring[2][W::SSZ];
-  W w;
-  if (!w.init(job, &ring[0][0])) return;
-  const int lane = w.lane, wm = w.wave >> 1, wn = w.wave & 1, h = lane >> 5;
-  f32x16_t acc[IM][JN];
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int j = 0; j < JN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  // element (row r0 + lane % 32, k) of a staged tile
-  auto at = [&](const float* t, int R, bool kmaj, int r0, int k) {
-    const int r = r0 + (lane & 31);
-    return kmaj ? t[r * KT + ((k >> 2) ^ ((r >> 1) & 7)) * 4 + (k & 3)] : t[k * R + (r ^ (32 * ((k >> 2) & 1)))];
-  };
-  if (w.t0 < w.t1) w.issue(w.t0);
-  for (int t = w.t0; t < w.t1; ++t) {
-    // own loads of slice t and own reads of the other stage done, then everyone's
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    w.issue(t + 1);
-    const float* sa = ring[t & 1];
-    const float* sb = sa + BM * KT;
-#pragma unroll
-    for (int kk = 0; kk < KT; kk += 2) {
-      float fa[IM], fb[JN];
-#pragma unroll
-      for (int i = 0; i < IM; ++i) fa[i] = at(sa, BM, AK, wm * 64 + i * 32, kk + h);
-#pragma unroll
-      for (int j = 0; j < JN; ++j) fb[j] = at(sb, BN, BKM, wn * (BN / 2) + j * 32, kk + h);
-#pragma unroll
-      for (int i = 0; i < IM; ++i)
-#pragma unroll
-        for (int j = 0; j < JN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j], fa[i], acc[i][j], 0, 0, 0);
-    }
-  }
-  wait_vm<0>();   // no load may land in LDS after the workgroup ends
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int j = 0; j < JN; ++j) w.store(job, acc[i][j], i, j);
-}
-
 template <int BN, bool AK, bool BKM>
 void launch_t(const GemmJob& j, int blocks, hipStream_t s) {
-  if (j.g[0].f32_chain) hipLaunchKernelGGL((gemm_f32_chain_kernel<BN, AK, BKM>), dim3(blocks), dim3(256), 0, s, j);
-  else hipLaunchKernelGGL((gemm_f32_kernel<BN, AK, BKM>), dim3(blocks), dim3(256), 0, s, j);
+  hipLaunchKernelGGL((gemm_f32_kernel<BN, AK, BKM>), dim3(blocks), dim3(256), 0, s, j);
 }
 template <int BN>
 void launch_bn(const GemmJob& j, int blocks, hipStream_t s) {
@@ -419,7 +364,7 @@ hipError_t gemm_f32(const GemmArgs* g, int n, const GemmScratch& ws, hipStream_t
   if (g[0].M == 0 || g[0].N == 0) return hipSuccess;
   GemmJob j;
   GemmPlan pl;
-  const GemmCost& c = pick(g, n, g[0].f32_chain ? 0 : ws.bytes, pl);
+  const GemmCost& c = pick(g, n, ws.bytes, pl);
   if (pl.bytes > ws.held) return hipErrorInvalidValue;
   const int blocks = make_job(j, g, n, pl, c, ws.p);
   if (c.BN == 64) launch_bn<64>(j, blocks, stream);

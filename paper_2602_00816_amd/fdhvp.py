@@ -101,7 +101,7 @@ def lib():
         "fdh_testing_gemm_channels": (i32, [i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, C.c_float, vp,
                                             C.c_size_t, vp]),
         "fdh_testing_gemm_epilogue": (i32, [i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, i64, i32, C.c_float, C.c_float,
-                                            vp, vp, C.c_float, vp, i32, i32, i32, vp, C.c_size_t, vp]),
+                                            vp, vp, C.c_float, vp, i32, i32, vp, C.c_size_t, vp]),
         "fdh_testing_gemm_plan": (i32, [i32, i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]),
         "fdh_testing_unfused_attention": (i32, [vp, i32]),
         "fdh_testing_unsplit_wgrad": (i32, [vp, i32]),
@@ -491,15 +491,14 @@ def testing_gemm_channels(dtype: str, M, N, K, batch, a_kmajor, b_kmajor, A, B, 
 
 
 def testing_gemm_epilogue(dtype: str, M, N, K, batch, a_kmajor, b_kmajor, A, B, A2, B2, out, ldc=None, alpha=1.0, beta=0.0,
-                          bias_theta=None, bias_v=None, bias_v_scale=1.0, resid=None, causal=0, tile=0, chain=False,
-                          scratch=None):
+                          bias_theta=None, bias_v=None, bias_v_scale=1.0, resid=None, causal=0, tile=0, scratch=None):
     """One product with the whole epilogue (testing); out float32 or of the operand type, A2/B2 may be None."""
     import torch
     st = lib().fdh_testing_gemm_epilogue(DTYPE[dtype], M, N, K, batch, int(a_kmajor), int(b_kmajor), _ptr(A), _ptr(B),
                                          _ptr(A2), _ptr(B2), _ptr(out), N if ldc is None else ldc,
                                          int(out.dtype != torch.float32), float(alpha), float(beta), _ptr(bias_theta),
-                                         _ptr(bias_v), float(bias_v_scale), _ptr(resid), int(causal), int(tile), int(chain),
-                                         _ptr(scratch), 0 if scratch is None else scratch.numel() * scratch.element_size(),
+                                         _ptr(bias_v), float(bias_v_scale), _ptr(resid), int(causal), int(tile), _ptr(scratch),
+                                         0 if scratch is None else scratch.numel() * scratch.element_size(),
                                          _stream())
     if st != OK:
         raise FdhError(st, "fdh_testing_gemm_epilogue")
