@@ -393,7 +393,7 @@ __global__ __launch_bounds__(NTH) void norm_bwd_kernel(PairF dx, PairT<T> dxo, c
 // the pass over the stored outputs, which they replace, added them).
 // 8192 x 1024 with LayerNorm and output sums: 65 us per call; the kernel above 118,
 // dy kept in registers too 100.
-// 8192 x 2048 without LayerNorm: 126 to 130 us (boxes differ), 604 MB at 4.7 TB/s;
+// 8192 x 2048 without LayerNorm: 126 to 130 us, 604 MB at 4.7 TB/s;
 // the kernel above 148, dy kept in registers too 188, the registers that the
 // compiler takes without a bound (one wavefront per SIMD) 168, more than two
 // workgroups per CU (the second read of dy then misses the L2) 158.
@@ -1029,17 +1029,16 @@ __global__ __launch_bounds__(NTH) void ce_kernel(PairT<T> dl, double* rowloss, c
     if constexpr (sizeof(T) == 2) return (double)__expf((float)a);
     else return exp(a);
   };
-  auto both = [&](double a, double b, double& xp, double& xn) {
-    if (sizeof(T) == 4 && fabs(b) >= EXP_PM_SERIES) {
+  auto both = [&](double E, double a, double b, double& xp, double& xn) {
+    if (sizeof(T) == 2 || fabs(b) < EXP_PM_SERIES) {
+      double ep, en;
+      exp_pm(b, ep, en);
+      xp = E * ep;
+      xn = E * en;
+    } else {
       xp = exp(a + b);
       xn = exp(a - b);
-      return;
     }
-    const double E = expa(a);
-    double ep, en;
-    exp_pm(b, ep, en);
-    xp = E * ep;
-    xn = E * en;
   };
   // one pass for the row maximum and the sums: each thread keeps its sums
   // relative to its own running maximum mt, rescaled by exp(old mt - new mt)
@@ -1056,10 +1055,13 @@ __global__ __launch_bounds__(NTH) void ce_kernel(PairT<T> dl, double* rowloss, c
       zm *= f;
       mt = top;
     }
+    double E[4];   // (ahead of the branches, so that the four exponentials overlap)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) E[e] = expa((double)f4e(a, e) - mt);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       double xp, xn;
-      both((double)f4e(a, e) - mt, f4e(b, e), xp, xn);
+      both(E[e], (double)f4e(a, e) - mt, f4e(b, e), xp, xn);
       zp += xp;
       zm += xn;
     }
@@ -1074,10 +1076,13 @@ __global__ __launch_bounds__(NTH) void ce_kernel(PairT<T> dl, double* rowloss, c
     if (j >= n4) continue;
     const float4 a = ld4(lm, o + 4 * j), b = ld4(ld, o + 4 * j);
     float om[4], od[4];
+    double E[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) E[e] = expa((double)f4e(a, e) - mx);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       double xp, xn;
-      both((double)f4e(a, e) - mx, f4e(b, e), xp, xn);
+      both(E[e], (double)f4e(a, e) - mx, f4e(b, e), xp, xn);
       const double pp = xp * izp, pn = xn * izm;
       om[e] = (float)(0.5 * (pp + pn) - (4 * j + e == y ? inv_n : 0.0));
       od[e] = (float)(0.5 * (pp - pn));
