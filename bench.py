@@ -35,7 +35,7 @@ from synth.workloads import WORKLOADS, SEED_PARAMS, SEED_TOKENS, SEED_PROBE  # n
 
 METRIC = "FD-HVPs/sec + Lanczos iters/min at 1.3B bf16; MFMA util % / HBM GB/s"
 PEAK_BF16_TFLOPS = 2500.0
-PEAK_F32_TFLOPS = 157.3
+PEAK_F32_TFLOPS = PEAK_BF16_TFLOPS / 6   # fp32 operands run as six bf16 products on the same matrix cores
 PEAK_HBM_GBPS = 8000.0
 
 
@@ -58,13 +58,14 @@ def alg_flops_per_hvp(w: dict) -> tuple[float, float]:
 
 def committed_gemm_traffic(workload: str):
     """HBM bytes per step of the GEMM launches, from the committed counter
-    summary, or None when the GEMM source changed after the counters were taken."""
+    summary, or None when the bf16 GEMM sources changed after the counters were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", f"gemm_{workload}.md")
-    src = os.path.join(ROOT, "paper_2602_00816_amd", "csrc", "gemm.hip")
+    src = [os.path.join(ROOT, "paper_2602_00816_amd", "csrc", f)
+           for f in ("gemm.hip", "gemm_dev.h", "gemm_split.h", "gemm_split.hip")]
     try:
         txt = open(path).read()
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
+        sha = hashlib.sha256(b"".join(open(f, "rb").read() for f in src)).hexdigest()
     except OSError:
         return None
     vals = dict(l.split(": ", 1) for l in txt.splitlines() if l.startswith(("traffic_bytes_per_step:", "gemm_source_sha256:")))

@@ -16,8 +16,9 @@
 // elements) between the matrix operations of the step before.  Splitting on
 // the way into LDS instead would write 6 bytes per element through the LDS
 // port (ds_write_b128 moves about a fifth of what ds_read_b128 does per clock).
-// 8192 x 2048 x 512, both channels: 302 us (170 TFLOP/s); the fp32 matrix
-// instructions with register-staged tiles took 1080 us for the two launches.
+// 8192 x 2048 x 512, both channels: 302 to 341 us (170 to 151 TFLOP/s, by the
+// clock held under load); the fp32 matrix instructions with register-staged tiles
+// took 1080 us for the two launches.
 // Lanes outside the operand read past the buffer resource's range and get
 // zeros, so K needs no alignment beyond the 16-byte chunk.
 // An infinite element splits into inf and a NaN remainder: its products are NaN.
