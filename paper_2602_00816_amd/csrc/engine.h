@@ -151,7 +151,7 @@ class Engine : public WsLayout {
   std::vector<int64_t> layer_ranges() const;
 
  private:
-  size_t linear_scratch(int T_) const;
+  size_t linear_scratch(size_t tokens) const;
   mutable std::mutex linear_mu;      // linear_scratch(linear_tokens) = linear_bytes
   mutable int linear_tokens = -1;
   mutable size_t linear_bytes = 0;

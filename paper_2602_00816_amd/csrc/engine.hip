@@ -53,6 +53,7 @@ GemmOperand mnmaj(const void* p, int64_t ld) {
 }
 
 constexpr size_t ALIGN = 256;
+constexpr int MAX_TOKENS = 16384;   // of one batch (a plan's largest B and S may come from different batches)
 
 }  // namespace
 
@@ -198,12 +199,13 @@ static int mlp_wgrad_split(int Ma, int Na, int Mb, int Nb, int T_) {
 constexpr size_t SPLIT_SCRATCH = (size_t)512 << 20;
 
 // Scratch for split contractions: the most that any linear product of a batch of
-// up to T_ tokens would use.  Forward and input gradient products have one plan
+// up to `tokens` tokens would use.  Forward and input gradient products have one plan
 // for all token counts of as many 128-row tiles, weight gradients for all of as
 // many slices of 32.
 // (0.4 ms of arithmetic for 8192 tokens; kept for the next plan of as many, as
 // fdh_workspace_bytes and fdh_set_workspace ask in turn.)
-size_t Engine::linear_scratch(int T_) const {
+size_t Engine::linear_scratch(size_t tokens) const {
+  const int T_ = (int)std::min<size_t>(tokens, MAX_TOKENS);
   std::lock_guard<std::mutex> lk(linear_mu);
   if (T_ == linear_tokens) return linear_bytes;
   const int nu = gpt2 ? F : 2 * F;
@@ -312,7 +314,7 @@ size_t Engine::plan(int B, int S, int m, const fdh_lanczos_opts* o, WsLayout* ou
     take(W.da_m, td * 4); take(W.da_d, td * 4);
     {
       const int nu = gpt2 ? F : 2 * F;
-      size_t mx = linear_scratch((int)T_);
+      size_t mx = linear_scratch(T_);
       // the down projection's slices when the MLP weight gradients share a launch
       const int nm = bf16 && !gpt2 ? mlp_wgrad_split(nu, d, d, F, (int)T_) : 0;
       if (nm > 1) mx = std::max(mx, (size_t)nm * d * F * 4);
@@ -1040,7 +1042,7 @@ int Engine::check_batch(const int32_t* tok, int B, int S) {
   if (B < 1 || S < 2) { err = "need B >= 1 and S >= 2"; return FDH_ERR_INVALID_ARG; }
   if (!ws) { err = "no workspace"; return FDH_ERR_WORKSPACE; }
   if (B > planB || S > planS || S > Smax) { err = "batch larger than the workspace plan (or S > max_seq)"; return FDH_ERR_WORKSPACE; }
-  if ((int64_t)B * S > 16384) { err = "B*S must be <= 16384"; return FDH_ERR_UNSUPPORTED; }
+  if ((int64_t)B * S > MAX_TOKENS) { err = "B*S must be <= 16384"; return FDH_ERR_UNSUPPORTED; }
   if (S > 4096) { err = "S must be <= 4096"; return FDH_ERR_UNSUPPORTED; }
   if (S % 8 || dh % 8) { err = "S and head_dim must be multiples of 8"; return FDH_ERR_UNSUPPORTED; }
   if (fused && planS % 128 == 0 && S % 128) {
